@@ -5,9 +5,10 @@
 // P_jt = the monomials of degree <= q at x_j, right-hand sides L applied to
 // phi(||x - x_j||) and to the monomials at x = x_0; w is kept.
 //
-// The paper's stencil (n = 28, cubic polynomials) without the condition
-// estimate goes to k_weights_pair (two systems per wavefront, further
-// below); every other form to k_weights:
+// The paper's stencil (n = 28, cubic polynomials) goes to k_weights_quad for
+// r^7 (four systems per wavefront, weights_quad.h) and to k_weights_pair for
+// other exponents (two systems per wavefront, further below); every other form,
+// and the condition estimate, to k_weights:
 // one wavefront (64 lanes) solves one system.  Lane i owns row i of the
 // augmented matrix (s = n + K_p <= 64 rows) in registers; the monomials of
 // the P block are computed once per stencil node and shared through LDS.
@@ -43,6 +44,8 @@
 // test vector.  A^-T = A^-1 here, so every step is one solve with the LU
 // factors.
 #include <climits>
+#include <type_traits>
+#include <utility>
 
 #include "common.h"
 
@@ -277,7 +280,8 @@ __device__ __forceinline__ void weights_system(const double *__restrict__ xq, in
                                                 const int *__restrict__ idx, int n, int m, int q,
                                                 OpSet ops, double *__restrict__ w,
                                                 double *__restrict__ cond,
-                                                unsigned long long *__restrict__ bad) {
+                                                unsigned long long *__restrict__ bad,
+                                                bool marked) {
     // Right-hand sides held per lane; those beyond the operator count are
     // zero and stay zero, so the loops run over all NO without guards.
     constexpr int NO = FIXED ? NOPS : kMaxOps;
@@ -293,6 +297,9 @@ __device__ __forceinline__ void weights_system(const double *__restrict__ xq, in
     const int kp = (q < 0) ? 0 : (q + 1) * (q + 2) / 2;
     const int s = n + kp;
     const int nops = FIXED ? NOPS : ops.n;
+    // marked: only rows whose first weight is NaN get weights (the others have
+    // theirs from k_weights_quad); the estimate is made for every row.
+    const bool solve = !marked || isnan(w[row]);
 
     // 1. Stencil in shifted coordinates; exact power-of-two scaling.
     // A stencil index outside [0, ns) marks the row bad before any load
@@ -421,83 +428,85 @@ __device__ __forceinline__ void weights_system(const double *__restrict__ xq, in
         }
     }
 
-    // 4. Back substitution: unknown kk lives in the pivot lane of step kk.
+    if (solve) {
+        // 4. Back substitution: unknown kk lives in the pivot lane of step kk.
 #pragma unroll
-    for (int kk = SMAX - 1; kk >= 0; --kk) {
-        if (kk < s) {
-            const int pk = step_lane(mystep, kk);
-            const double uk = (mystep < kk) ? a[kk] : 0.0;
+        for (int kk = SMAX - 1; kk >= 0; --kk) {
+            if (kk < s) {
+                const int pk = step_lane(mystep, kk);
+                const double uk = (mystep < kk) ? a[kk] : 0.0;
 #pragma unroll
-            for (int o = 0; o < NO; ++o) {
-                const double xk = readlane_d(b[o] * myinv, pk);
-                b[o] = fma(-uk, xk, b[o]);
-                if (lane == 0) sol[o][kk] = xk;
+                for (int o = 0; o < NO; ++o) {
+                    const double xk = readlane_d(b[o] * myinv, pk);
+                    b[o] = fma(-uk, xk, b[o]);
+                    if (lane == 0) sol[o][kk] = xk;
+                }
             }
         }
-    }
-    __syncthreads();
+        __syncthreads();
 
-    // 5. One refinement step: r = b0 - A0 x in double-FP64, solve with LU.
-    // Entries are recomputed (same operations as in step 2) one column at a
-    // time; each right-hand side accumulates over j in increasing order.
-    double r[NO], hi[NO], lo[NO];
-#pragma unroll
-    for (int o = 0; o < NO; ++o) {
-        hi[o] = rhs(o);
-        lo[o] = 0.0;
-    }
-#pragma unroll
-    for (int j = 0; j < SMAX; ++j) {
-        if (j < s) {
-            const double aj = entry(j);
-#pragma unroll
-            for (int o = 0; o < NO; ++o) {
-                const double xj = sol[o][j];
-                const double p = aj * xj;
-                const double pe = fma(aj, xj, -p);
-                const double t = hi[o] - p;
-                const double bv = t - hi[o];
-                const double err = (hi[o] - (t - bv)) + (-p - bv);
-                hi[o] = t;
-                lo[o] = lo[o] + (err - pe);
-            }
-        }
-    }
-#pragma unroll
-    for (int o = 0; o < NO; ++o) r[o] = hi[o] + lo[o];
-    // Forward substitution with the stored multipliers (virtual pivoting).
-#pragma unroll
-    for (int kk = 0; kk < SMAX; ++kk) {
-        if (kk < s) {
-            const int pk = step_lane(mystep, kk);
-            const double lk = (mystep > kk && mystep != INT_MAX) ? a[kk] : 0.0;
-#pragma unroll
-            for (int o = 0; o < NO; ++o) r[o] = fma(-lk, readlane_d(r[o], pk), r[o]);
-        }
-    }
-#pragma unroll
-    for (int kk = SMAX - 1; kk >= 0; --kk) {
-        if (kk < s) {
-            const int pk = step_lane(mystep, kk);
-            const double uk = (mystep < kk) ? a[kk] : 0.0;
-#pragma unroll
-            for (int o = 0; o < NO; ++o) {
-                const double dk = readlane_d(r[o] * myinv, pk);
-                r[o] = fma(-uk, dk, r[o]);
-                if (lane == 0) sol[o][kk] += dk;
-            }
-        }
-    }
-    __syncthreads();
-
-    // 6. Weights in physical units; NaN for failed rows.
-    if (lane < n) {
+        // 5. One refinement step: r = b0 - A0 x in double-FP64, solve with LU.
+        // Entries are recomputed (same operations as in step 2) one column at a
+        // time; each right-hand side accumulates over j in increasing order.
+        double r[NO], hi[NO], lo[NO];
 #pragma unroll
         for (int o = 0; o < NO; ++o) {
-            if (o < nops) {
-                double v = ldexp(sol[o][lane], -e * ops.order[o]);
-                if (!isfinite(v)) bad_row = true;
-                w[((int64_t)o * n + lane) * nq + row] = v;
+            hi[o] = rhs(o);
+            lo[o] = 0.0;
+        }
+#pragma unroll
+        for (int j = 0; j < SMAX; ++j) {
+            if (j < s) {
+                const double aj = entry(j);
+#pragma unroll
+                for (int o = 0; o < NO; ++o) {
+                    const double xj = sol[o][j];
+                    const double p = aj * xj;
+                    const double pe = fma(aj, xj, -p);
+                    const double t = hi[o] - p;
+                    const double bv = t - hi[o];
+                    const double err = (hi[o] - (t - bv)) + (-p - bv);
+                    hi[o] = t;
+                    lo[o] = lo[o] + (err - pe);
+                }
+            }
+        }
+#pragma unroll
+        for (int o = 0; o < NO; ++o) r[o] = hi[o] + lo[o];
+        // Forward substitution with the stored multipliers (virtual pivoting).
+#pragma unroll
+        for (int kk = 0; kk < SMAX; ++kk) {
+            if (kk < s) {
+                const int pk = step_lane(mystep, kk);
+                const double lk = (mystep > kk && mystep != INT_MAX) ? a[kk] : 0.0;
+#pragma unroll
+                for (int o = 0; o < NO; ++o) r[o] = fma(-lk, readlane_d(r[o], pk), r[o]);
+            }
+        }
+#pragma unroll
+        for (int kk = SMAX - 1; kk >= 0; --kk) {
+            if (kk < s) {
+                const int pk = step_lane(mystep, kk);
+                const double uk = (mystep < kk) ? a[kk] : 0.0;
+#pragma unroll
+                for (int o = 0; o < NO; ++o) {
+                    const double dk = readlane_d(r[o] * myinv, pk);
+                    r[o] = fma(-uk, dk, r[o]);
+                    if (lane == 0) sol[o][kk] += dk;
+                }
+            }
+        }
+        __syncthreads();
+
+        // 6. Weights in physical units; NaN for failed rows.
+        if (lane < n) {
+#pragma unroll
+            for (int o = 0; o < NO; ++o) {
+                if (o < nops) {
+                    double v = ldexp(sol[o][lane], -e * ops.order[o]);
+                    if (!isfinite(v)) bad_row = true;
+                    w[((int64_t)o * n + lane) * nq + row] = v;
+                }
             }
         }
     }
@@ -525,26 +534,27 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4)))
 k_weights(const double *__restrict__ xq, int64_t nq, const double *__restrict__ xs, int64_t ns,
           const int *__restrict__ idx, int n, int m, int q, OpSet ops, double *__restrict__ w,
           double *__restrict__ cond, unsigned long long *__restrict__ bad) {
-    weights_system<SMAX, FIXED, NOPS, false>(xq, nq, xs, ns, idx, n, m, q, ops, w, cond, bad);
+    weights_system<SMAX, FIXED, NOPS, false>(xq, nq, xs, ns, idx, n, m, q, ops, w, cond, bad, false);
 }
 
 template <int SMAX, bool FIXED, int NOPS, bool COND>
 __global__ void __launch_bounds__(64)
 k_weights_any(const double *__restrict__ xq, int64_t nq, const double *__restrict__ xs, int64_t ns,
               const int *__restrict__ idx, int n, int m, int q, OpSet ops, double *__restrict__ w,
-              double *__restrict__ cond, unsigned long long *__restrict__ bad) {
-    weights_system<SMAX, FIXED, NOPS, COND>(xq, nq, xs, ns, idx, n, m, q, ops, w, cond, bad);
+              double *__restrict__ cond, unsigned long long *__restrict__ bad, bool marked) {
+    weights_system<SMAX, FIXED, NOPS, COND>(xq, nq, xs, ns, idx, n, m, q, ops, w, cond, bad, marked);
 }
 
 // ---------------------------------------------------------------------------
-// Two systems per wavefront for the paper's stencil (n = 28 nodes, cubic
-// polynomials, K_p = 10): lanes 0-31 solve system 2b, lanes 32-63 system
+// Two systems per wavefront for n = 28 nodes and cubic polynomials (K_p = 10),
+// any exponent m: lanes 0-31 solve system 2b, lanes 32-63 system
 // 2b + 1, lane l of a half owning row l of the RBF block A.  Block
 // elimination of [A P; P^T 0] [w; c] = [f; g]:
 //   LU of A with partial pivoting (rows of the half) carried through the
 //   columns [P | f], back substitution gives X = A^-1 P and y = A^-1 f;
 //   the Schur system S c = P^T y - g with S = P^T X (10 x 10) is formed by
 //   dot products over LDS and solved with partial pivoting; w = y - X c.
+// `marked`: only the rows whose first weight is NaN (those k_weights_quad left).
 // One refinement step as in the one-system kernel: the residual of the
 // whole saddle-point system in double-FP64 (entries recomputed), then the
 // same block solve for the correction.  A and the augmented matrix have
@@ -610,7 +620,7 @@ template <int NO>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 k_weights_pair(const double *__restrict__ xq, int64_t nq, const double *__restrict__ xs,
                int64_t ns, const int *__restrict__ idx, int m, OpSet ops,
-               double *__restrict__ w, unsigned long long *__restrict__ bad) {
+               double *__restrict__ w, unsigned long long *__restrict__ bad, bool marked) {
     constexpr int N = kPairN, KP = kPairKP, R = KP + NO;
     __shared__ double sx[2][32], sy[2][32];
     __shared__ double prow[2][2][N + R];  // [buffer][half] pivot row of a step
@@ -622,7 +632,8 @@ k_weights_pair(const double *__restrict__ xq, int64_t nq, const double *__restri
     __shared__ double sr[2][KP][NO];      // [half] constraint residuals, then S right-hand sides
     const int lane = threadIdx.x, h = lane >> 5, l = lane & 31;
     const int64_t row = (int64_t)blockIdx.x * 2 + h;
-    const bool valid = row < nq;
+    const bool valid = row < nq && (!marked || isnan(w[row]));
+    if (!__any(valid)) return;
     const bool live = valid && l < N;
     const int ln = (l < N) ? l : N - 1;   // stand-in row index for idle lanes
     const int lk = (l < KP) ? l : KP - 1;
@@ -925,6 +936,8 @@ k_weights_pair(const double *__restrict__ xq, int64_t nq, const double *__restri
     if (valid && (any_bad || half_nonfinite) && l == 0) atomicMin(bad, (unsigned long long)row);
 }
 
+#include "weights_quad.h"
+
 }  // namespace
 
 extern "C" rbf_status rbf_assemble_weights(const double *xq, int64_t nq, const double *xs,
@@ -958,54 +971,79 @@ extern "C" rbf_status rbf_assemble_weights(const double *xq, int64_t nq, const d
         }
     }
     hipStream_t st = rbf::as_stream(st_);
-    unsigned long long *dbad = nullptr;
-    RBF_HIP(hipMalloc(&dbad, sizeof(unsigned long long)));
-    unsigned long long init = ~0ull;
+    unsigned long long *dbad = nullptr;  // lowest bad row, rows left by k_weights_quad
+    RBF_HIP(hipMalloc(&dbad, 2 * sizeof(unsigned long long)));
+    const unsigned long long init[2] = {~0ull, 0};
+    unsigned long long hb[2] = {~0ull, 0};
     rbf_status rc = RBF_OK;
-    hipError_t e = hipMemcpyAsync(dbad, &init, sizeof(init), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) {
+    hipError_t e = hipMemcpyAsync(dbad, init, sizeof(init), hipMemcpyHostToDevice, st);
+    auto read_back = [&]() {
+        if (e == hipSuccess) e = hipGetLastError();
+        if (e == hipSuccess) e = hipMemcpyAsync(hb, dbad, sizeof(hb), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+    };
+    const dim3 block(64), rgrid((uint32_t)nq), pgrid((uint32_t)((nq + 1) / 2)),
+        qgrid((uint32_t)((nq + 3) / 4));
+#define RBF_WPAIR(NP, MARKED)                                                                      \
+    hipLaunchKernelGGL(k_weights_pair<NP>, pgrid, block, 0, st, xq, nq, xs, ns, idx, m, ops, w, dbad, MARKED)
+#define RBF_WCOND(SM, FX, NP, CD, MARKED)                                                          \
+    hipLaunchKernelGGL((k_weights_any<SM, FX, NP, CD>), rgrid, block, 0, st, xq, nq, xs, ns, idx, k, \
+                       m, q, ops, w, cond_est, dbad, MARKED)
 #define RBF_WLAUNCH(SM, FX, NP)                                                                   \
     do {                                                                                          \
-        if (cond_est)                                                                             \
-            hipLaunchKernelGGL((k_weights_any<SM, FX, NP, true>), dim3((uint32_t)nq), dim3(64), 0, \
-                               st, xq, nq, xs, ns, idx, k, m, q, ops, w, cond_est, dbad);         \
+        if (cond_est) RBF_WCOND(SM, FX, NP, true, quad);                                          \
         else if constexpr (SM <= 40)                                                              \
-            hipLaunchKernelGGL((k_weights<SM, FX, NP>), dim3((uint32_t)nq), dim3(64), 0, st, xq,   \
-                               nq, xs, ns, idx, k, m, q, ops, w, cond_est, dbad);                 \
-        else                                                                                      \
-            hipLaunchKernelGGL((k_weights_any<SM, FX, NP, false>), dim3((uint32_t)nq), dim3(64), 0, \
-                               st, xq, nq, xs, ns, idx, k, m, q, ops, w, cond_est, dbad);         \
+            hipLaunchKernelGGL((k_weights<SM, FX, NP>), rgrid, block, 0, st, xq, nq, xs, ns, idx,  \
+                               k, m, q, ops, w, cond_est, dbad);                                  \
+        else RBF_WCOND(SM, FX, NP, false, false);                                                 \
     } while (0)
-        // The paper's stencil without the condition estimate: two systems
-        // per wavefront.
-        const bool pair = !cond_est && k == kPairN && q == 3 && ops.n >= 1 && ops.n <= 3;
-        const dim3 pgrid((uint32_t)((nq + 1) / 2)), pblock(64);
-        if (pair && ops.n == 1)
-            hipLaunchKernelGGL(k_weights_pair<1>, pgrid, pblock, 0, st, xq, nq, xs, ns, idx, m, ops, w, dbad);
-        else if (pair && ops.n == 2)
-            hipLaunchKernelGGL(k_weights_pair<2>, pgrid, pblock, 0, st, xq, nq, xs, ns, idx, m, ops, w, dbad);
-        else if (pair)
-            hipLaunchKernelGGL(k_weights_pair<3>, pgrid, pblock, 0, st, xq, nq, xs, ns, idx, m, ops, w, dbad);
-        else if (k + kp <= 38 && ops.n == 1) RBF_WLAUNCH(38, true, 1);
-        else if (k + kp <= 38 && ops.n == 2) RBF_WLAUNCH(38, true, 2);
-        else if (k + kp <= 38 && ops.n == 3) RBF_WLAUNCH(38, true, 3);
-        else if (k + kp <= 40) RBF_WLAUNCH(40, false, kMaxOps);
-        else RBF_WLAUNCH(64, false, kMaxOps);
-#undef RBF_WLAUNCH
-        e = hipGetLastError();
+    // The paper's stencil: four systems per wavefront for r^7, whose A is
+    // definite on the null space of the constraints (5.3 ms per 10^6 systems
+    // with three operators, 18.3 ms with two per wavefront and pivoting); two
+    // per wavefront for other exponents.  The condition estimate needs the LU
+    // factors of the one-system kernel, which then solves only the rows that
+    // the first one left.
+    const bool paper = k == kPairN && q == 3 && ops.n >= 1 && ops.n <= 3, quad = paper && m == 7;
+    if (e == hipSuccess) {
+        if (quad) {
+            if (ops.n == 1)
+                hipLaunchKernelGGL(k_weights_quad<1>, qgrid, block, 0, st, xq, nq, xs, ns, idx, ops, w, dbad + 1);
+            else if (ops.n == 2)
+                hipLaunchKernelGGL(k_weights_quad<2>, qgrid, block, 0, st, xq, nq, xs, ns, idx, ops, w, dbad + 1);
+            else
+                hipLaunchKernelGGL(k_weights_quad<3>, qgrid, block, 0, st, xq, nq, xs, ns, idx, ops, w, dbad + 1);
+        } else if (paper && !cond_est) {
+            if (ops.n == 1) RBF_WPAIR(1, false);
+            else if (ops.n == 2) RBF_WPAIR(2, false);
+            else RBF_WPAIR(3, false);
+        }
+        if (!paper || cond_est) {
+            if (k + kp <= 38 && ops.n == 1) RBF_WLAUNCH(38, true, 1);
+            else if (k + kp <= 38 && ops.n == 2) RBF_WLAUNCH(38, true, 2);
+            else if (k + kp <= 38 && ops.n == 3) RBF_WLAUNCH(38, true, 3);
+            else if (k + kp <= 40) RBF_WLAUNCH(40, false, kMaxOps);
+            else RBF_WLAUNCH(64, false, kMaxOps);
+        }
+        read_back();
+        if (e == hipSuccess && !cond_est && hb[1] != 0) {  // rows left by k_weights_quad
+            if (ops.n == 1) RBF_WPAIR(1, true);
+            else if (ops.n == 2) RBF_WPAIR(2, true);
+            else RBF_WPAIR(3, true);
+            read_back();
+        }
     }
-    unsigned long long hb = ~0ull;
-    if (e == hipSuccess) e = hipMemcpyAsync(&hb, dbad, sizeof(hb), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    hipFree(dbad);
+#undef RBF_WLAUNCH
+#undef RBF_WCOND
+#undef RBF_WPAIR
+    (void)hipFree(dbad);
     if (e != hipSuccess) {
         rbf::set_error("rbf_assemble_weights: %s", hipGetErrorString(e));
         return RBF_E_DEVICE;
     }
-    if (hb != ~0ull) {
-        *bad_row = (int64_t)hb;
+    if (hb[0] != ~0ull) {
+        *bad_row = (int64_t)hb[0];
         rbf::set_error("rbf_assemble_weights: singular or non-finite system, or stencil index outside [0, ns), at row %lld",
-                       (long long)hb);
+                       (long long)hb[0]);
         rc = RBF_E_SINGULAR;
     }
     return rc;
