@@ -113,9 +113,9 @@ rbf_status rbf_build_nodes(int32_t kind, int32_t K, double jitter, uint64_t seed
  * d^2 = dx*dx + dy*dy in FP64 with separately rounded products (no fused
  * multiply-add), so ties are broken by the lower index and the result is a
  * unique function of the inputs.  When alpha = beta and nodes are distinct,
- * slot 0 is the node itself.  Synchronises the stream twice (bounding box,
- * end of the search).  Device scratch (cell grid, about 34 bytes per source)
- * is allocated and freed inside the call.
+ * slot 0 is the node itself.  Synchronises the stream at the end of the
+ * search.  Device scratch (cell grid, about 28 bytes per source) is allocated
+ * and freed inside the call.
  * Errors: RBF_E_ARG if k < 1, k > 64, k > ns, nq < 0, ns < 1, a NULL
  * pointer with a non-zero size, or a NaN or infinite coordinate in either
  * node set (checked before any search, so no stencil is written);
@@ -135,7 +135,7 @@ rbf_status rbf_knn(const double *xq, int64_t nq, const double *xs, int64_t ns, i
  * RBF_E_ARG (message naming the limit) before any search.  Every call on a
  * device shares that device's array: calls that overlap on one GPU (two
  * host threads, or two streams) race and must be serialised by the caller.
- * Synchronises the stream twice, like rbf_knn.
+ * Synchronises the stream, like rbf_knn.
  */
 rbf_status rbf_knn_noalloc(const double *xq, int64_t nq, const double *xs, int64_t ns, int32_t k,
                            int32_t *idx, rbf_stream st);
