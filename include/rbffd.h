@@ -607,10 +607,12 @@ rbf_status rbf_solver_forces(rbf_solver *s, const rbf_grid *grid, const rbf_stat
  * dnu: host, accumulated: the derivative with respect to nu (through
  * H = I - (dt nu / 2) D_Lap and the right-hand side of eq. (16)).
  * The transposed solves: the viscous matrix by Jacobi-scaled BiCGSTAB on
- * H^T, the bordered pressure system by BiCGSTAB on (A_s + u1 c 1^T)^T (the
- * transpose of the zero-mean bordered solve), with the solver's tolerances
- * (pressure: a tenth of rtol_p).  The first call builds the transposed
- * operators (rbf_ell_transpose).  Synchronises.
+ * H^T (both components at once), the bordered pressure system (A_s + u1 c
+ * 1^T)^T (the transpose of the zero-mean bordered solve) by flexible GMRES
+ * with the transpose of the auxiliary-lattice preconditioner, or by BiCGSTAB
+ * on node sets that it does not fit and if it fails, with the solver's
+ * tolerances (pressure: a tenth of rtol_p or better).  The first call builds
+ * the transposed operators (rbf_ell_transpose).  Synchronises.
  * Errors: RBF_E_ARG (NULL arguments), RBF_E_NOCONV, RBF_E_NAN, those of
  * rbf_step for the recomputed forward step.
  */

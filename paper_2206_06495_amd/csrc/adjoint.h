@@ -108,3 +108,149 @@ __global__ void k_adj_wallmask(int64_t nwall, const int *__restrict__ list, int8
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i < nwall) tag[list[i]] = 1;
 }
+
+// ------------------------------------ transposed pressure preconditioner --
+// B^-T of the auxiliary-lattice preconditioner (pressure_aux.h), the right
+// preconditioner of flexible GMRES on A^T = A_s^T + c 1 u1^T.  With the smoother
+// pair S = W + w2 W (I - A_s W), the transposed application is, last stage first,
+//   v1 = v - w2 A_s^T W v
+//   v2 = v1 - A_s^T W v1
+//   h  = J^T (v2 - mean v2),  e = (L5)^+ h,
+//   q  = S_r^-1 R^T (e + sum v2 / (m c n^2))   (S_r the row scale; the constant
+//                                              is the transpose of mu)
+//   u  = v2 - A_s^T q
+//   z  = w2 W v + W v1 + q + W u + w2 W (u - A_s^T W u):
+// four products, as the forward application takes, and the same transforms.
+// A_s^T is stored as rows padded to a common length (a multiple of kAtChunk)
+// with zero weights on the row itself, so that a row's loads are independent.
+constexpr int kAtChunk = 8;
+constexpr int kAtMax = 256;  // longest padded row (longer columns: BiCGSTAB)
+
+struct AdjPre {
+    AuxOps<double> P;            // padded A_s^T with W, S_r^-1 and w2
+    const int *jptr, *jcol;      // J^T: rows of the interior lattice points (X order)
+    const double *jval;
+    const int *tq;               // R^T: [4][m] lattice entries (Z order), weight 0 if unused
+    const double *tv;            // [4][m]
+    const double *u1;            // [m] border column
+    double *v1, *g1, *v2, *q, *u, *gu;  // [m] work
+    double *partS, *sum;         // sums of v2: block partials, total
+};
+
+// CSR columns of a transposed ELL operator as rows padded to kt entries.
+__global__ void k_at_pad(int64_t n, int kt, const int64_t *__restrict__ colptr,
+                         const int *__restrict__ src, const double *__restrict__ wt,
+                         int *__restrict__ idx, double *__restrict__ w) {
+    const int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (c >= n) return;
+    const int64_t b = colptr[c], len = colptr[c + 1] - b;
+    for (int s = 0; s < kt; ++s) {
+        idx[(int64_t)s * n + c] = (s < len) ? src[b + s] : (int)c;
+        w[(int64_t)s * n + c] = (s < len) ? wt[b + s] : 0.0;
+    }
+}
+
+// Row r of the padded operator applied to x.
+__device__ __forceinline__ double at_row(const AuxOps<double> &P, int64_t r, const double *x) {
+    double acc = 0.0;
+    for (int q0 = 0; q0 < P.k; q0 += kAtChunk) {
+        int jj[kAtChunk];
+        double ww[kAtChunk];
+#pragma unroll
+        for (int q = 0; q < kAtChunk; ++q) jj[q] = P.idx[(int64_t)(q0 + q) * P.m + r];
+#pragma unroll
+        for (int q = 0; q < kAtChunk; ++q) ww[q] = P.w[(int64_t)(q0 + q) * P.m + r];
+#pragma unroll
+        for (int q = 0; q < kAtChunk; ++q) acc = fma(ww[q], x[jj[q]], acc);
+    }
+    return acc;
+}
+
+// The four products (STAGE 1..4 as v1, v2, u, z above); STAGE 2 sums v2,
+// STAGE 4 u1 z (border term of the product that follows), per block.
+template <int STAGE>
+__global__ void __launch_bounds__(kThreads) k_at_row(AdjPre D, const double *__restrict__ y,
+                                                      const double *__restrict__ yd,
+                                                      const double *ys, double *__restrict__ z,
+                                                      double *part, const int *flag) {
+    if (*flag != 0) return;
+    const AuxOps<double> &P = D.P;
+    const double sc = (STAGE == 1 || STAGE == 4) ? *ys : 0.0;
+    double acc[1] = {0.0};
+    for (int64_t it = 0;; ++it) {
+        const int64_t r = row_of(it);
+        if (r - threadIdx.x >= P.m) break;
+        if (r >= P.m) continue;
+        if constexpr (STAGE == 1) {
+            const double v = sc * (y[r] - P.w2 * at_row(P, r, yd));
+            D.v1[r] = v;
+            D.g1[r] = P.dinv[r] * v;
+        } else if constexpr (STAGE == 2) {
+            const double v = D.v1[r] - at_row(P, r, D.g1);
+            D.v2[r] = v;
+            acc[0] += v;
+        } else if constexpr (STAGE == 3) {
+            const double v = D.v2[r] - at_row(P, r, D.q);
+            D.u[r] = v;
+            D.gu[r] = P.dinv[r] * v;
+        } else {
+            const double u = D.u[r];
+            const double v = D.q[r] + P.dinv[r] * (P.w2 * sc * y[r] + D.v1[r] + u +
+                                                   P.w2 * (u - at_row(P, r, D.gu)));
+            z[r] = v;
+            acc[0] += D.u1[r] * v;
+        }
+    }
+    if constexpr (STAGE == 2 || STAGE == 4) store_partials<1>(acc, part, gridDim.x);
+}
+
+// h = J^T (v2 - mean v2), four lanes per lattice point.
+__global__ void __launch_bounds__(kThreads) k_at_restrict(AdjPre D, Lat L, int nbS) {
+    if (*L.flag != 0) return;
+    double s[1];
+    load_partials<1>(D.partS, nbS, s);
+    const double mean = s[0] / (double)D.P.m;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *D.sum = s[0];
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    const int q = t >> 2, sub = t & 3, nq = L.n * L.n;
+    double g = 0.0;
+    if (q < nq) {
+        const int e1 = D.jptr[q + 1];
+        for (int e = D.jptr[q] + sub; e < e1; e += 4) g += D.jval[e] * (D.v2[D.jcol[e]] - mean);
+    }
+    g += __shfl_xor(g, 1, 64);
+    g += __shfl_xor(g, 2, 64);
+    if (q < nq && sub == 0) lat_store(L, L.X, q, g);
+}
+
+// q = S_r^-1 R^T (e + sum v2 / (m c n^2)).
+__global__ void __launch_bounds__(kThreads) k_at_prolong(AdjPre D, Lat L) {
+    if (*L.flag != 0) return;
+    const int64_t m = D.P.m;
+    const double add = *D.sum / ((double)m * L.c * (double)L.n * (double)L.n);
+    for (int64_t r = blockIdx.x * (int64_t)kThreads + threadIdx.x; r < m;
+         r += (int64_t)gridDim.x * kThreads) {
+        double v = 0.0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            v += D.tv[c * m + r] * (lat_load(L, L.X, D.tq[c * m + r]) + add);
+        D.q[r] = D.P.sinv[r] * v;
+    }
+}
+
+// Block sums of w x (weighted form of k_sum).
+__global__ void __launch_bounds__(kThreads) k_wsum(int64_t n, const double *__restrict__ w,
+                                                    const double *__restrict__ x, double *part) {
+    double acc[1] = {0.0};
+    for (int64_t i = blockIdx.x * (int64_t)kThreads + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * kThreads)
+        acc[0] += w[i] * x[i];
+    store_partials<1>(acc, part, gridDim.x);
+}
+
+// a[i] = c (elementwise constant).
+__global__ void k_adj_fill(int64_t n, double c, double *a) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x)
+        a[i] = c;
+}

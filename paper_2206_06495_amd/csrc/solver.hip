@@ -18,6 +18,7 @@
 #include <string>
 #include <system_error>
 #include <thread>
+#include <tuple>
 #include <type_traits>
 #include <utility>
 #include <vector>
@@ -1858,6 +1859,7 @@ struct rbf_solver {
     } forces;
     double u_conv = 0.0;           // convection velocity of outflow rows
     double *u_bc = nullptr, *v_bc = nullptr;
+    double *xp = nullptr;        // [2][M] P-node coordinates
     double *v_hmin = nullptr;    // [N] nearest stencil-neighbour distance (CFL)
     double *diag_part = nullptr; // [5][kMaxBlocks] diagnostics partials
     int64_t n_interior_p = 0;
@@ -1910,6 +1912,7 @@ struct rbf_solver {
     struct Adj {
         bool ready = false;
         int64_t *cp_vv = nullptr, *cp_vp = nullptr, *cp_pv = nullptr, *cp_pp = nullptr;
+        int *slot_vv = nullptr;
         int *src_vv = nullptr, *src_vp = nullptr, *src_pv = nullptr, *src_pp = nullptr;
         double *dxT_vv = nullptr, *dyT_vv = nullptr, *lapT_vv = nullptr, *dxT_vp = nullptr,
                *dyT_vp = nullptr, *dxT_pv = nullptr, *dyT_pv = nullptr, *aT_pp = nullptr;
@@ -1918,6 +1921,17 @@ struct rbf_solver {
         double *pm[8] = {};      // work vectors over P rows
         double *kr[7] = {};      // Krylov vectors (max(N, M))
         double *part = nullptr;
+        // Transposed pressure solve by flexible GMRES (pre_on), and H^T padded
+        // for the viscous BiCGSTAB (ht_idx null: not built).
+        bool pre_on = false;
+        AdjPre pre{};
+        Lat lat{};
+        FgDev<double> fg{};
+        double *ones = nullptr;
+        int last_p = 0, last_h = 0;
+        int *ht_idx = nullptr;
+        double *ht_w = nullptr, *hb = nullptr, *hx = nullptr;
+        int ht_k = 0;
     } adj;
     // pinned host buffers
     int *hflag = nullptr;
@@ -2107,23 +2121,23 @@ rbf_status bicgstab(rbf_solver *S, KDev &K, EllM A, const double *b, double *x, 
 
 // One application of the lattice preconditioner's interior solve:
 // T = Q^-1 X, tridiagonal solves along y per x-mode, Z = Q W.
-rbf_status pc_apply(rbf_solver *S, bool sample = false) {
-    const dim3 g(S->lat.ntiles), b(64 * kGemmWaves);
-    const dim3 gt(S->lat.n), bt(64);
+rbf_status pc_apply(rbf_solver *S, const Lat &L, bool sample = false) {
+    const dim3 g(L.ntiles), b(64 * kGemmWaves);
+    const dim3 gt(L.n), bt(64);
     // A sample times the first product (its own start and end stamps).
     hipEvent_t e0 = nullptr, e1 = nullptr;
     const bool timed = sample && prof_pair(S, RBF_PROF_GEMM, e0, e1);
-    const int steps = (S->lat.n + 3) / 4;
+    const int steps = (L.n + 3) / 4;
     const bool one = (steps + kGemmWaves - 1) / kGemmWaves <= kGemmChunk;
     auto run = [&](auto tp) {
         using TP = decltype(tp);
-        if (one) hipExtLaunchKernelGGL((k_pc_gemm<0, true, TP>), g, b, 0, S->st, e0, e1, 0, S->lat);
-        else hipExtLaunchKernelGGL((k_pc_gemm<0, false, TP>), g, b, 0, S->st, e0, e1, 0, S->lat);
-        hipLaunchKernelGGL(k_pc_tri<TP>, gt, bt, 0, S->st, S->lat);
-        if (one) hipLaunchKernelGGL((k_pc_gemm<1, true, TP>), g, b, 0, S->st, S->lat);
-        else hipLaunchKernelGGL((k_pc_gemm<1, false, TP>), g, b, 0, S->st, S->lat);
+        if (one) hipExtLaunchKernelGGL((k_pc_gemm<0, true, TP>), g, b, 0, S->st, e0, e1, 0, L);
+        else hipExtLaunchKernelGGL((k_pc_gemm<0, false, TP>), g, b, 0, S->st, e0, e1, 0, L);
+        hipLaunchKernelGGL(k_pc_tri<TP>, gt, bt, 0, S->st, L);
+        if (one) hipLaunchKernelGGL((k_pc_gemm<1, true, TP>), g, b, 0, S->st, L);
+        else hipLaunchKernelGGL((k_pc_gemm<1, false, TP>), g, b, 0, S->st, L);
     };
-    if (S->lat.f32) run(float{});
+    if (L.f32) run(float{});
     else run(double{});
     (void)timed;
     return RBF_OK;
@@ -2180,14 +2194,14 @@ rbf_status pbicgstab(rbf_solver *S, EllM A, const double *b, double *x, double t
             const int par = it & 1;
             const bool sample = S->prof_every > 0 && (S->prof_launches++ % S->prof_every) == 0;
             hipLaunchKernelGGL(k_pc_dir, grid, block, 0, st, K, L, x, m, it, i0);
-            if ((rc = pc_apply(S, sample)) != RBF_OK) return rc;
+            if ((rc = pc_apply(S, S->lat, sample)) != RBF_OK) return rc;
             hipLaunchKernelGGL(k_pc_post, grid, block, 0, st, L, K, K.p[par], K.ph, m, K.partS,
                                K.part1 + nb, nb);
             hipEvent_t e0 = nullptr, e1 = nullptr;
             if (sample) prof_pair(S, RBF_PROF_SPMV, e0, e1);
             av(0, K.ph, K.v, e0, e1);
             hipLaunchKernelGGL(k_pc_s, grid, block, 0, st, K, L, m, it, i0, tol2, win);
-            if ((rc = pc_apply(S)) != RBF_OK) return rc;
+            if ((rc = pc_apply(S, S->lat)) != RBF_OK) return rc;
             hipLaunchKernelGGL(k_pc_post, grid, block, 0, st, L, K, K.s, K.sh, m, K.partS,
                                K.partGs, nb);
             av(1, K.sh, K.t, nullptr, nullptr);
@@ -2745,7 +2759,7 @@ void aux_apply(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, const T *y, const
     });
     hipLaunchKernelGGL(k_aux_restrict<T>, dim3(rbf::blocks_for(4 * (int64_t)nq, 256)), dim3(256), 0,
                        st, P, S->lat, F.res, nq);
-    pc_apply(S, sample);
+    pc_apply(S, S->lat, sample);
     hipLaunchKernelGGL(k_aux_interp<T>, grid, block, 0, st, P, S->lat, u, us, F.t1, F.s.partZ);
     // Post-smoothing: the first sweep adds the border's constant.
     T *zin = F.t1;
@@ -2781,10 +2795,15 @@ constexpr bool kFgReorth = false;
 // preconditioner (x: guess in, solution out).  Every cycle starts from the
 // FP64 residual; with T = float the cycle is one step of iterative
 // refinement (see pressure_aux.h).  maxit counts Arnoldi steps
-// (preconditioner applications).
-template <class T>
-rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, const double *b,
-                      double *x, double tol, int maxit, int &last_iters, rbf_solve_stats *stats) {
+// (preconditioner applications).  apply(y, W y, ys, z, sample): one application
+// of the preconditioner.  sumw: weights of the sum in the border term of x
+// (null: 1; its launches are not sampled).  expect: steps the solve is likely to need (0: unknown).  accept:
+// a cycle that starts with more than half of the last one's true residual ends
+// the solve as converged if that is within accept times the tolerance (1: off).
+template <class T, class Apply>
+rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, const double *sumw,
+                      const double *b, double *x, double tol, int maxit, int expect, double accept,
+                      int &last_iters, rbf_solve_stats *stats, Apply apply) {
     hipStream_t st = S->st;
     const int64_t m = A.n;
     const int nb = nblocks_rows(m);
@@ -2792,12 +2811,9 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
     const int mr = kFgMax;
     const int mixed = std::is_same<T, float>::value ? 1 : 0;
     FgScal &Fs = F.s;
-    S->lat.flag = Fs.flag;  // the transform stages exit with the Krylov flag
     int total = 0, cycles = 0, f = 0;
     bool first = true;
-    // Expected steps of the first cycle: the last solve's count (warm starts
-    // of consecutive steps need about as many).
-    int expect = S->p_nhist ? S->p_hist[(S->p_pos + 2) % 3] : 0;
+    double beta_prev = INFINITY;
     auto status = [&]() -> rbf_status {
         RBF_HIP(hipMemcpyAsync(S->hflag, Fs.flag, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
         RBF_HIP(hipMemcpyAsync(S->hflag + 2, Fs.stat, 5 * sizeof(double), hipMemcpyDeviceToHost, st));
@@ -2807,7 +2823,8 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
     };
     rbf_status rc = RBF_OK;
     for (;;) {
-        if (A.u1) hipLaunchKernelGGL((k_sum<1>), grid, block, 0, st, m, x, S->kp.partX);
+        if (sumw) hipLaunchKernelGGL(k_wsum, grid, block, 0, st, m, sumw, x, S->kp.partX);
+        else if (A.u1) hipLaunchKernelGGL((k_sum<1>), grid, block, 0, st, m, x, S->kp.partX);
         launch_kt(A.k, [&](auto KT) {
             hipLaunchKernelGGL((k_fg_init<decltype(KT)::value, T>), grid, block, 0, st, A, b, x,
                                S->kp.partX, F.V, P.dinv, F.wd, Fs.part);
@@ -2832,9 +2849,10 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
             const int stop = std::min(mr, j + batch);
             for (; j < stop; ++j) {
                 const int64_t o = (int64_t)j * m;
-                const bool sample = S->prof_every > 0 && (S->prof_launches++ % S->prof_every) == 0;
+                const bool sample =
+                    !sumw && S->prof_every > 0 && (S->prof_launches++ % S->prof_every) == 0;
                 S->prof_tag_now = j;
-                aux_apply(S, P, F, F.V + o, F.wd, Fs.vs + j, F.Z + o, sample);
+                apply(F.V + o, F.wd, Fs.vs + j, F.Z + o, sample);
                 hipEvent_t e0 = nullptr, e1 = nullptr, g0 = nullptr, g1 = nullptr;
                 if (sample) {
                     prof_pair(S, RBF_PROF_SPMV, e0, e1);
@@ -2865,6 +2883,15 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
             RBF_CHECK_LAUNCH();
             if ((rc = status()) != RBF_OK) return rc;
             f = S->hflag[0];
+            if (accept > 1.0) {
+                const double *hc = reinterpret_cast<const double *>(S->hflag + 2);
+                if (f >= 0 && f != 1 && hc[4] > 0.5 * beta_prev &&
+                    hc[4] <= accept * tol * std::sqrt(hc[3])) {
+                    f = 1;
+                    break;
+                }
+                beta_prev = (f != 0 || j >= mr) ? hc[4] : beta_prev;
+            }
             if (f != 0 || j >= mr) break;
             // Next batch from the residual's rate over the last four steps.
             const double *hs = reinterpret_cast<const double *>(S->hflag + 2);
@@ -2903,21 +2930,29 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
         rc = RBF_E_NOCONV;
     }
     last_iters = total;
-    if (f == 1) {
-        S->p_hist[S->p_pos] = total;
-        S->p_pos = (S->p_pos + 1) % 3;
-        S->p_nhist = std::min(3, S->p_nhist + 1);
-    }
     return rc;
 }
 
 rbf_status aux_solve(rbf_solver *S, EllM A, const double *b, double *x, rbf_solve_stats *stats) {
     A.vscale *= kAuxBorder;  // as S->lat.c
-    if (S->mixed)
-        return fgmres_run<float>(S, S->ax32, S->fg32, A, b, x, S->rtol_p, S->maxit_p,
-                                 S->last_iters_p, stats);
-    return fgmres_run<double>(S, S->ax64, S->fg64, A, b, x, S->rtol_p, S->maxit_p,
-                              S->last_iters_p, stats);
+    // Expected steps of the first cycle: the last solve's count (warm starts
+    // of consecutive steps need about as many).
+    const int expect = S->p_nhist ? S->p_hist[(S->p_pos + 2) % 3] : 0;
+    auto run = [&](auto &P, auto &F) {
+        S->lat.flag = F.s.flag;  // the transform stages exit with the Krylov flag
+        return fgmres_run(S, P, F, A, nullptr, b, x, S->rtol_p, S->maxit_p, expect, 1.0,
+                          S->last_iters_p, stats,
+                          [&](const auto *y, const auto *yd, const double *ys, auto *z, bool sample) {
+                              aux_apply(S, P, F, y, yd, ys, z, sample);
+                          });
+    };
+    const rbf_status rc = S->mixed ? run(S->ax32, S->fg32) : run(S->ax64, S->fg64);
+    if (rc == RBF_OK) {
+        S->p_hist[S->p_pos] = S->last_iters_p;
+        S->p_pos = (S->p_pos + 1) % 3;
+        S->p_nhist = std::min(3, S->p_nhist + 1);
+    }
+    return rc;
 }
 
 template <class T>
@@ -3361,6 +3396,7 @@ rbf_status create_impl(rbf_solver *S, const rbf_grid *g, const rbf_ops *o, const
     for (double *&q : S->hh) ALLOC(q, 2 * N);
     ALLOC(S->p_rhs_tmp, M);
     ALLOC(S->p_tag, M);
+    ALLOC(S->xp, 2 * M);
     ALLOC(S->u_bc, N);
     ALLOC(S->v_bc, N);
     ALLOC(S->wall_rows, N);
@@ -3410,7 +3446,7 @@ rbf_status create_impl(rbf_solver *S, const rbf_grid *g, const rbf_ops *o, const
               {S->vv_lap, o->vv_lap, kN * db}, {S->pv_dx, o->pv_dx, kM * db},
               {S->pv_dy, o->pv_dy, kM * db},   {S->pp_lap, o->pp_lap, kM * db},
               {S->vp_dx, o->vp_dx, kN * db},   {S->vp_dy, o->vp_dy, kN * db},
-              {S->p_tag, g->p_tag, (size_t)M}, {S->u_bc, u_bc, N * db},
+              {S->p_tag, g->p_tag, (size_t)M}, {S->xp, g->xp, 2 * M * db}, {S->u_bc, u_bc, N * db},
               {S->v_bc, v_bc, N * db}};
     for (auto &c : cp)
         if ((rc = copy_in(S, c.d, c.s, c.b)) != RBF_OK) return rc;
@@ -3718,7 +3754,7 @@ namespace {
 // Column structure and column-ordered weights of the transposes (once).
 rbf_status adj_transpose(rbf_solver *S, int64_t rows, const int *idx, int64_t ncols,
                          std::initializer_list<std::pair<const double *, double **>> ws,
-                         int64_t **cp, int **src) {
+                         int64_t **cp, int **src, int **slot_out = nullptr) {
     const int k = S->k;
     int *slot;
     ALLOC(*cp, ncols + 1);
@@ -3733,7 +3769,162 @@ rbf_status adj_transpose(rbf_solver *S, int64_t rows, const int *idx, int64_t nc
             RBF_OK)
             return rc;
     }
+    if (slot_out) *slot_out = slot;
     return RBF_OK;
+}
+
+// Columns of a transposed operator as rows padded to a multiple of kAtChunk
+// entries; kt = 0 (nothing built) where a column is longer than kAtMax.
+rbf_status adj_pad(rbf_solver *S, int64_t n, const int64_t *colptr, const int *src,
+                   const double *wt, int **idx, double **w, int &kt) {
+    std::vector<int64_t> cp(n + 1);
+    RBF_HIP(hipMemcpyAsync(cp.data(), colptr, (n + 1) * sizeof(int64_t), hipMemcpyDeviceToHost, S->st));
+    RBF_HIP(hipStreamSynchronize(S->st));
+    int64_t longest = 1;
+    for (int64_t c = 0; c < n; ++c) longest = std::max(longest, cp[c + 1] - cp[c]);
+    kt = 0;
+    const int64_t k = (longest + kAtChunk - 1) / kAtChunk * kAtChunk;
+    if (k > kAtMax) return RBF_OK;
+    ALLOC(*idx, k * n);
+    ALLOC(*w, k * n);
+    hipLaunchKernelGGL(k_at_pad, dim3(rbf::blocks_for(n, 256)), dim3(256), 0, S->st, n, (int)k,
+                       colptr, src, wt, *idx, *w);
+    RBF_CHECK_LAUNCH();
+    kt = (int)k;
+    return RBF_OK;
+}
+
+// FP64 auxiliary-lattice structures of the transposed pressure solve: the
+// solver's own, or, where it has none in FP64 (lattice preconditioner, mixed
+// precision, no preconditioner), a set built here and kept apart.
+rbf_status adj_pre_setup(rbf_solver *S) {
+    auto &A = S->adj;
+    const int64_t M = S->M;
+    rbf_status rc;
+    AuxOps<double> ops;
+    if (S->aux_on && !S->mixed) {
+        A.lat = S->lat;
+        A.fg = S->fg64;
+        ops = S->ax64;
+    } else {
+        const auto keep = std::make_tuple(S->lat, S->ax64, S->ax32, S->fg64, S->fg32, S->p_w32,
+                                          S->aux_K, S->aux_on, S->pc_on, S->mixed);
+        S->aux_on = S->pc_on = S->mixed = false;
+        S->lat = Lat{};
+        rbf_grid g{};
+        g.n_v = S->N;
+        g.n_p = M;
+        g.xp = S->xp;
+        g.p_tag = S->p_tag;
+        rc = setup_aux_pc(S, &g, RBF_PRECOND_AUTO);
+        const bool on = rc == RBF_OK && S->aux_on;
+        A.lat = S->lat;
+        A.fg = S->fg64;
+        ops = S->ax64;
+        std::tie(S->lat, S->ax64, S->ax32, S->fg64, S->fg32, S->p_w32, S->aux_K, S->aux_on,
+                 S->pc_on, S->mixed) = keep;
+        if (rc != RBF_OK || !on) return rc;
+    }
+    AdjPre &D = A.pre;
+    int *idx = nullptr;
+    double *w = nullptr;
+    int kt = 0;
+    if ((rc = adj_pad(S, M, A.cp_pp, A.src_pp, A.aT_pp, &idx, &w, kt)) != RBF_OK || kt == 0) return rc;
+    D.P = ops;
+    D.P.idx = idx;
+    D.P.w = w;
+    D.P.k = kt;
+    // J^T by lattice points and R^T by nodes, on the host.
+    const Lat &L = A.lat;
+    const int n = L.n, K1 = L.K + 1;
+    const size_t nn = (size_t)n * n;
+    std::vector<int> cell(M), rptr(nn + 1);
+    std::vector<double> fx(M), fy(M);
+    auto fetch = [&](auto &v, const void *d) {
+        return hipMemcpyAsync(v.data(), d, v.size() * sizeof(v[0]), hipMemcpyDeviceToHost, S->st);
+    };
+    RBF_HIP(fetch(cell, L.cell));
+    RBF_HIP(fetch(fx, L.fx));
+    RBF_HIP(fetch(fy, L.fy));
+    RBF_HIP(fetch(rptr, ops.rptr));
+    RBF_HIP(hipStreamSynchronize(S->st));
+    std::vector<int> rcol(rptr[nn]);
+    std::vector<double> rval(rptr[nn]);
+    if (!rcol.empty()) {
+        RBF_HIP(fetch(rcol, ops.rcol));
+        RBF_HIP(fetch(rval, ops.rval));
+        RBF_HIP(hipStreamSynchronize(S->st));
+    }
+    std::vector<int> jptr(nn + 1, 0), jcol(4 * (size_t)M), fill;
+    std::vector<double> jval(4 * (size_t)M);
+    auto corner = [&](int64_t v, int c) {  // interior point in X order, as aux_lattice reads it
+        const int i = cell[v] % K1 + (c & 1), j = cell[v] / K1 + (c >> 1);
+        const int ci = std::min(std::max(i, 1), L.K - 1), cj = std::min(std::max(j, 1), L.K - 1);
+        return (ci - 1) * n + (cj - 1);
+    };
+    for (int64_t v = 0; v < M; ++v)
+        for (int c = 0; c < 4; ++c) ++jptr[corner(v, c) + 1];
+    for (size_t q = 0; q < nn; ++q) jptr[q + 1] += jptr[q];
+    fill.assign(jptr.begin(), jptr.end() - 1);
+    for (int64_t v = 0; v < M; ++v)
+        for (int c = 0; c < 4; ++c) {
+            const int e = fill[corner(v, c)]++;
+            jcol[e] = (int)v;
+            jval[e] = ((c & 1) ? fx[v] : 1.0 - fx[v]) * ((c >> 1) ? fy[v] : 1.0 - fy[v]);
+        }
+    std::vector<int> tq(4 * (size_t)M, 0), used(M, 0);
+    std::vector<double> tv(4 * (size_t)M, 0.0);
+    for (size_t q = 0; q < nn; ++q)
+        for (int e = rptr[q]; e < rptr[q + 1]; ++e) {
+            const int64_t v = rcol[e];
+            const size_t at = (size_t)used[v]++ * M + v;  // at most the four corners of its cell
+            tq[at] = (int)(q / n) + (int)(q % n) * n;     // Z is column-major
+            tv[at] = rval[e];
+        }
+    auto send = [&](auto **d, const auto &v) -> rbf_status {
+        ALLOC(*d, v.size());
+        RBF_HIP(hipMemcpyAsync(*d, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice, S->st));
+        return RBF_OK;
+    };
+    int *djp, *djc, *dtq;
+    double *djv, *dtv;
+    if ((rc = send(&djp, jptr)) != RBF_OK || (rc = send(&djc, jcol)) != RBF_OK ||
+        (rc = send(&djv, jval)) != RBF_OK || (rc = send(&dtq, tq)) != RBF_OK ||
+        (rc = send(&dtv, tv)) != RBF_OK)
+        return rc;
+    RBF_HIP(hipStreamSynchronize(S->st));
+    D.jptr = djp;
+    D.jcol = djc;
+    D.jval = djv;
+    D.tq = dtq;
+    D.tv = dtv;
+    D.u1 = S->p_u1;
+    for (double **q : {&D.v1, &D.g1, &D.v2, &D.q, &D.u, &D.gu, &A.ones}) ALLOC(*q, M);
+    ALLOC(D.partS, kMaxBlocks);
+    ALLOC(D.sum, 1);
+    hipLaunchKernelGGL(k_adj_fill, dim3(std::min<int64_t>(1024, rbf::blocks_for(M, 256))), dim3(256),
+                       0, S->st, M, 1.0, A.ones);
+    RBF_CHECK_LAUNCH();
+    A.pre_on = true;
+    return RBF_OK;
+}
+
+// One application z = B^-T (ys y) (adjoint.h).
+void adj_pre_apply(rbf_solver *S, const double *y, const double *yd, const double *ys, double *z) {
+    auto &A = S->adj;
+    const AdjPre &D = A.pre;
+    hipStream_t st = S->st;
+    const int nb = nblocks_rows(S->M);
+    const dim3 grid(nb), block(kThreads);
+    const int *flag = A.fg.s.flag;
+    hipLaunchKernelGGL(k_at_row<1>, grid, block, 0, st, D, y, yd, ys, z, nullptr, flag);
+    hipLaunchKernelGGL(k_at_row<2>, grid, block, 0, st, D, y, yd, ys, z, D.partS, flag);
+    hipLaunchKernelGGL(k_at_restrict, dim3(rbf::blocks_for(4 * (int64_t)A.lat.n * A.lat.n, kThreads)),
+                       block, 0, st, D, A.lat, nb);
+    pc_apply(S, A.lat);
+    hipLaunchKernelGGL(k_at_prolong, grid, block, 0, st, D, A.lat);
+    hipLaunchKernelGGL(k_at_row<3>, grid, block, 0, st, D, y, yd, ys, z, nullptr, flag);
+    hipLaunchKernelGGL(k_at_row<4>, grid, block, 0, st, D, y, yd, ys, z, A.fg.s.partO, flag);
 }
 
 rbf_status adj_setup(rbf_solver *S) {
@@ -3742,7 +3933,7 @@ rbf_status adj_setup(rbf_solver *S) {
     rbf_status rc;
     if ((rc = adj_transpose(S, N, S->idx_vv, N,
                             {{S->vv_dx, &A.dxT_vv}, {S->vv_dy, &A.dyT_vv}, {S->vv_lap, &A.lapT_vv}},
-                            &A.cp_vv, &A.src_vv)) != RBF_OK)
+                            &A.cp_vv, &A.src_vv, &A.slot_vv)) != RBF_OK)
         return rc;
     if ((rc = adj_transpose(S, N, S->idx_vp, M, {{S->vp_dx, &A.dxT_vp}, {S->vp_dy, &A.dyT_vp}},
                             &A.cp_vp, &A.src_vp)) != RBF_OK)
@@ -3762,6 +3953,15 @@ rbf_status adj_setup(rbf_solver *S) {
     for (auto &q : A.pm) ALLOC(q, M);
     for (auto &q : A.kr) ALLOC(q, std::max(N, M));
     ALLOC(A.part, 4 * kMaxBlocks);
+    // H^T (identity on wall rows) for the viscous BiCGSTAB of both components.
+    double *hT = nullptr;
+    ALLOC(hT, (int64_t)S->k * N);
+    if ((rc = rbf_ell_transpose_weights(N, S->k, A.src_vv, A.slot_vv, S->h_w, hT, 0, S->st)) != RBF_OK)
+        return rc;
+    if ((rc = adj_pad(S, N, A.cp_vv, A.src_vv, hT, &A.ht_idx, &A.ht_w, A.ht_k)) != RBF_OK) return rc;
+    ALLOC(A.hb, 2 * N);
+    ALLOC(A.hx, 2 * N);
+    if ((rc = adj_pre_setup(S)) != RBF_OK) return rc;
     RBF_HIP(hipStreamSynchronize(S->st));
     A.ready = true;
     return RBF_OK;
@@ -3939,15 +4139,37 @@ extern "C" rbf_status rbf_adjoint_step(rbf_solver *S, const rbf_state *fwd, rbf_
                            dim3(256), 0, st, M, c * d, out);
         return RBF_OK;
     };
-    ADJ(adj_bicgstab(S, M, pois_t, nullptr, y, w, 0.1 * S->rtol_p, std::max(S->maxit_p, 20000),
-                     "rbf_adjoint_step (transposed pressure solve)"));
+    // Flexible GMRES with the transposed preconditioner where it is set up;
+    // unpreconditioned BiCGSTAB otherwise, and if that fails.  BiCGSTAB's last
+    // iterations overshoot its tolerance; FGMRES stops at it, so it gets a tenth
+    // (rtol_p itself, as BiCGSTAB's final check has it, once it stagnates).
+    const double tol_p = 0.1 * S->rtol_p;
+    bool solved = false;
+    if (A.pre_on) {
+        const AuxOps<double> &T = A.pre.P;
+        const EllM AT{T.idx, T.w, nullptr, M, T.k, A.ones, c * kAuxBorder};
+        A.lat.flag = A.fg.s.flag;
+        RBF_HIP(hipMemsetAsync(w, 0, mb, st));
+        rc = fgmres_run(S, T, A.fg, AT, S->p_u1, y, w, 0.1 * tol_p,
+                        std::max(100, std::min(S->maxit_p, 600)), A.last_p, 100.0, A.last_p, nullptr,
+                        [&](const double *v, const double *vd, const double *vs, double *z, bool) {
+                            adj_pre_apply(S, v, vd, vs, z);
+                        });
+        solved = rc == RBF_OK;
+        if (rc == RBF_E_DEVICE || rc == RBF_E_NOMEM) return rc;
+        rbf::clear_error();
+    }
+    if (!solved)
+        ADJ(adj_bicgstab(S, M, pois_t, nullptr, y, w, tol_p, std::max(S->maxit_p, 20000),
+                         "rbf_adjoint_step (transposed pressure solve)"));
     hipLaunchKernelGGL(k_adj_fbar, dim3(std::min<int64_t>(1024, rbf::blocks_for(M, 256))), dim3(256),
                        0, st, M, S->p_tag, S->p_rowscale, w, 1.0 / dt, fb);
     // (17): u**_bar = u_bar + Dx^PV^T F_bar, v likewise
+    double *hb = A.hb;
     ADJ(tpv(A.dxT_pv, fb, t1));
     ADJ(tpv(A.dyT_pv, fb, t2));
-    adj_axpby(S, N, 1.0, ub, 1.0, t1, t1);
-    adj_axpby(S, N, 1.0, vb, 1.0, t2, t2);
+    adj_axpby(S, N, 1.0, ub, 1.0, t1, hb);
+    adj_axpby(S, N, 1.0, vb, 1.0, t2, hb + N);
     // (16): r_bar = H^-T u**_bar, H^T x = x - a L^T (chi x)
     auto helm_t = [&](const double *in, double *out) -> rbf_status {
         hipLaunchKernelGGL(k_adj_split, dim3(std::min<int64_t>(1024, rbf::blocks_for(N, 256))),
@@ -3957,10 +4179,27 @@ extern "C" rbf_status rbf_adjoint_step(rbf_solver *S, const rbf_state *fwd, rbf_
         adj_axpby(S, N, 1.0, in, -a, out, out);
         return RBF_OK;
     };
-    ADJ(adj_bicgstab(S, N, helm_t, S->h_dinv, t1, rub, S->rtol_h, std::max(S->maxit_h, 2000),
-                     "rbf_adjoint_step (transposed viscous solve, u)"));
-    ADJ(adj_bicgstab(S, N, helm_t, S->h_dinv, t2, rvb, S->rtol_h, std::max(S->maxit_h, 2000),
-                     "rbf_adjoint_step (transposed viscous solve, v)"));
+    // Both components at once by the forward step's BiCGSTAB kernels on the
+    // padded H^T; one after the other on the columns if that fails.
+    solved = false;
+    if (A.ht_k > 0) {
+        const EllM HT{A.ht_idx, A.ht_w, S->h_dinv, N, A.ht_k, nullptr, 0.0};
+        RBF_HIP(hipMemsetAsync(A.hx, 0, 2 * nb, st));
+        rc = hbicgstab(S, HT, hb, A.hx, S->rtol_h, S->maxit_h, A.last_h, nullptr);
+        solved = rc == RBF_OK;
+        if (rc == RBF_E_DEVICE || rc == RBF_E_NOMEM) return rc;
+        rbf::clear_error();
+        rub = A.hx;
+        rvb = A.hx + N;
+    }
+    if (!solved) {
+        rub = V[2];
+        rvb = V[3];
+        ADJ(adj_bicgstab(S, N, helm_t, S->h_dinv, hb, rub, S->rtol_h, std::max(S->maxit_h, 2000),
+                         "rbf_adjoint_step (transposed viscous solve, u)"));
+        ADJ(adj_bicgstab(S, N, helm_t, S->h_dinv, hb + N, rvb, S->rtol_h, std::max(S->maxit_h, 2000),
+                         "rbf_adjoint_step (transposed viscous solve, v)"));
+    }
     const dim3 gN(std::min<int64_t>(1024, rbf::blocks_for(N, 256))), b256(256);
     hipLaunchKernelGGL(k_adj_split, gN, b256, 0, st, N, A.vtag, rub, ri, rw);
     hipLaunchKernelGGL(k_adj_split, gN, b256, 0, st, N, A.vtag, rvb, si, sw);
@@ -4119,7 +4358,7 @@ extern "C" rbf_status rbf_solver_apply_precond(rbf_solver *S, const double *y, d
     const int nb = nblocks_rows(m);
     RBF_HIP(hipMemsetAsync(S->pk.flag, 0, sizeof(int), st));
     hipLaunchKernelGGL(k_pc_pre, dim3(nb), dim3(kThreads), 0, st, S->lat, y, m, S->pk.partGs);
-    rbf_status rc = pc_apply(S);
+    rbf_status rc = pc_apply(S, S->lat);
     if (rc != RBF_OK) return rc;
     hipLaunchKernelGGL(k_pc_post, dim3(nb), dim3(kThreads), 0, st, S->lat, S->pk, y, z, m,
                        S->pk.partS, S->pk.partGs, nb);
