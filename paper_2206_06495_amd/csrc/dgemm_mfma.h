@@ -22,6 +22,8 @@
 // LDS.  Ragged edges are zero-filled.  The epilogue functor receives
 // (i, j, value) for every in-range element, on the waves with k-share 0;
 // the return value tells the calling wave whether it holds a result.
+// go() is asked once the first loads are issued; false (uniform over the
+// workgroup) ends the block.
 // Every wave of the workgroup must call it (it synchronises when S > 1).
 #pragma once
 
@@ -48,9 +50,9 @@ struct mfma16<float> {
     static __device__ __forceinline__ int row(int r, int lk) { return 4 * lk + r; }
 };
 
-template <class T, int TM, int TN, int S, int C, bool ONESHOT, class Epi>
+template <class T, int TM, int TN, int S, int C, bool ONESHOT, class Go, class Epi>
 __device__ __forceinline__ bool mfma_block(int n, const T *__restrict__ A, const T *__restrict__ B,
-                                           int bm, int bn, Epi epi) {
+                                           int bm, int bn, Go go, Epi epi) {
     using M = mfma16<T>;
     using acc4 = typename M::acc4;
     constexpr int NT = TM * TN;
@@ -76,6 +78,7 @@ __device__ __forceinline__ bool mfma_block(int n, const T *__restrict__ A, const
     acc4 acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
     T a[C], b[C];
     load(s0, a, b);
+    if (!go()) return false;
     if constexpr (ONESHOT) {
         // The whole k-share fits in one chunk (per <= C, checked by the
         // caller): every operand load is in flight before the first MFMA.

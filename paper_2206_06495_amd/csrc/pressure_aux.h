@@ -156,23 +156,30 @@ __device__ __forceinline__ int64_t row2_of(int &half) {
            (threadIdx.x >> 6) * 32 + (lane & 31);
 }
 
-// Row r of the sparse part applied to f, each lane summing its half of the
-// stencil; both lanes of the pair return the row's sum (half 0 + half 1).
-template <int KT, class T, class F>
-__device__ __forceinline__ T aux_row2(const AuxOps<T> &P, int64_t r, int half, F f) {
+// One lane's half of row r of the sparse part: load() issues the entries' loads,
+// sum(f) applies them to f and adds the pair's halves (0 + 1) in both lanes.
+// Apart, so that whatever else a kernel needs, and the flag that may end it,
+// travels with the entries in one memory round trip.
+template <int KT, class T>
+struct HalfRow {
     static_assert(KT > 0 && KT % 2 == 0, "two halves of a fixed stencil");
-    constexpr int H = KT / 2;
+    static constexpr int H = KT / 2;
     int jj[H];
     T ww[H];
+    __device__ __forceinline__ void load(const AuxOps<T> &P, int64_t r, int half) {
 #pragma unroll
-    for (int q = 0; q < H; ++q) jj[q] = P.idx[(int64_t)(half * H + q) * P.m + r];
+        for (int q = 0; q < H; ++q) jj[q] = P.idx[(int64_t)(half * H + q) * P.m + r];
 #pragma unroll
-    for (int q = 0; q < H; ++q) ww[q] = P.w[(int64_t)(half * H + q) * P.m + r];
-    T acc = 0;
+        for (int q = 0; q < H; ++q) ww[q] = P.w[(int64_t)(half * H + q) * P.m + r];
+    }
+    template <class F>
+    __device__ __forceinline__ T sum(F f) const {
+        T acc = 0;
 #pragma unroll
-    for (int q = 0; q < H; ++q) acc = fma(ww[q], f(jj[q]), acc);
-    return acc + __shfl_xor(acc, 32, 64);
-}
+        for (int q = 0; q < H; ++q) acc = fma(ww[q], f(jj[q]), acc);
+        return acc + __shfl_xor(acc, 32, 64);
+    }
+};
 
 // Grid of the smoothing products: one row pair per thread for KT > 0, the
 // grid-stride row loop otherwise.
@@ -188,15 +195,19 @@ __global__ void __launch_bounds__(kThreads) k_aux_pre(AuxOps<T> P, const T *__re
                                                        const T *__restrict__ yd,
                                                        const double *ys, T *__restrict__ x1,
                                                        const int *flag) {
-    if (*flag != 0) return;
-    const T sc = (T)*ys;
     if constexpr (KT > 0) {
         int half;
         const int64_t r = row2_of(half);
         const int64_t rr = (r < P.m) ? r : P.m - 1;
-        const T ax = aux_row2<KT>(P, rr, half, [&](int j) { return yd[j]; });
-        if (half == 0 && r < P.m) x1[r] = sc * (yd[r] + (T)P.w2 * P.dinv[r] * (y[r] - ax));
+        HalfRow<KT, T> row;
+        row.load(P, rr, half);
+        const T sc = (T)*ys, yr = y[rr], ydr = yd[rr], di = P.dinv[rr];
+        if (*flag != 0) return;
+        const T ax = row.sum([&](int j) { return yd[j]; });
+        if (half == 0 && r < P.m) x1[r] = sc * (ydr + (T)P.w2 * di * (yr - ax));
     } else {
+        if (*flag != 0) return;
+        const T sc = (T)*ys;
         for (int64_t it = 0;; ++it) {
             const int64_t r = row_of(it);
             if (r - threadIdx.x >= P.m) break;
@@ -215,15 +226,19 @@ __global__ void __launch_bounds__(kThreads) k_aux_res(AuxOps<T> P, const T *__re
                                                        const double *ys, const T *__restrict__ u,
                                                        const double *us, T *__restrict__ res,
                                                        const int *flag) {
-    if (*flag != 0) return;
-    const T sc = (T)*ys, su = (T)*us;
     if constexpr (KT > 0) {
         int half;
         const int64_t r = row2_of(half);
         const int64_t rr = (r < P.m) ? r : P.m - 1;
-        const T ax = aux_row2<KT>(P, rr, half, [&](int j) { return u[j]; });
-        if (half == 0 && r < P.m) res[r] = P.sinv[r] * (sc * y[r] - su * ax);
+        HalfRow<KT, T> row;
+        row.load(P, rr, half);
+        const T sc = (T)*ys, su = (T)*us, yr = y[rr], si = P.sinv[rr];
+        if (*flag != 0) return;
+        const T ax = row.sum([&](int j) { return u[j]; });
+        if (half == 0 && r < P.m) res[r] = si * (sc * yr - su * ax);
     } else {
+        if (*flag != 0) return;
+        const T sc = (T)*ys, su = (T)*us;
         for (int64_t it = 0;; ++it) {
             const int64_t r = row_of(it);
             if (r - threadIdx.x >= P.m) break;
@@ -278,14 +293,18 @@ __global__ void k_aux_scale(AuxOps<T> P, const T *__restrict__ y, T *__restrict_
 template <class T>
 __global__ void __launch_bounds__(256) k_aux_restrict(AuxOps<T> P, Lat L,
                                                        const T *__restrict__ res, int nq) {
-    if (*L.flag != 0) return;
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    const int q = t >> 2, sub = t & 3;
+    const int q = t >> 2, sub = t & 3, qc = min(q, nq - 1);
     double g = 0.0;
-    if (q < nq) {
-        const int e1 = P.rptr[q + 1];
-        for (int e = P.rptr[q] + sub; e < e1; e += 4)
-            g += (double)P.rval[e] * (double)res[P.rcol[e]];
+    const int e0 = P.rptr[qc] + sub, e1 = P.rptr[qc + 1];
+    if (*L.flag != 0) return;
+    // Two entries of a lane at a time (a point has about five entries).
+    for (int e = e0; e < e1; e += 8) {
+        const int f = min(e + 4, e1 - 1);
+        const int c0 = P.rcol[e], c1 = P.rcol[f];
+        const double v0 = (double)P.rval[e], v1 = (double)P.rval[f];
+        g += v0 * (double)res[c0];
+        if (e + 4 < e1) g += v1 * (double)res[c1];
     }
     g += __shfl_xor(g, 1, 64);
     g += __shfl_xor(g, 2, 64);
@@ -306,22 +325,34 @@ __global__ void __launch_bounds__(kThreads) k_aux_interp(AuxOps<T> P, Lat L,
                                                           const T *__restrict__ u,
                                                           const double *us, T *__restrict__ t1,
                                                           double *partZ) {
-    if (*L.flag != 0) return;
-    const T su = (T)*us;
     const int K1 = L.K + 1;
     double acc[1] = {0.0};
+    // The first row's data travel with the flag (every block has one).
+    int64_t r = row_of(0);
+    const int64_t rc = min(r, P.m - 1);
+    int c = L.cell[rc];
+    double fx = L.fx[rc], fy = L.fy[rc];
+    T ur = u[rc];
+    const T su = (T)*us;
+    if (*L.flag != 0) return;
     for (int64_t it = 0;; ++it) {
-        const int64_t r = row_of(it);
-        if (r - threadIdx.x >= P.m) break;
+        if (it > 0) {
+            r = row_of(it);
+            if (r - threadIdx.x >= P.m) break;
+            if (r < P.m) {
+                c = L.cell[r];
+                fx = L.fx[r];
+                fy = L.fy[r];
+                ur = u[r];
+            }
+        }
         if (r < P.m) {
-            const int c = L.cell[r];
             const int i0 = c % K1, j0 = c / K1;
-            const double fx = L.fx[r], fy = L.fy[r];
             const double z = (1.0 - fy) * ((1.0 - fx) * aux_lattice(L, i0, j0) +
                                            fx * aux_lattice(L, i0 + 1, j0)) +
                              fy * ((1.0 - fx) * aux_lattice(L, i0, j0 + 1) +
                                    fx * aux_lattice(L, i0 + 1, j0 + 1));
-            t1[r] = su * u[r] + (T)z;
+            t1[r] = su * ur + (T)z;
             acc[0] += z;
         }
     }
@@ -370,27 +401,31 @@ k_aux_post2(AuxOps<T> P, Lat L,
                                                            const T *__restrict__ t1,
                                                            const double *partZ,
                                                            T *__restrict__ z, double *partO) {
-    if (*L.flag != 0) return;
     __shared__ double lds[2 * kThreads / 64];
     const int lane = threadIdx.x & 63, half = lane >> 5, wv = threadIdx.x >> 6;
     const int nb = gridDim.x;  // <= kMaxBlocks = 2 blockDim.x: two partials per thread
-    // The partials of mu and the first row iteration's product (every block
-    // has one) are loaded before mu is reduced, so that the reduction
-    // overlaps the gathers.
-    const double pz0 = (MU && (int)threadIdx.x < nb) ? partZ[threadIdx.x] : 0.0;
-    const double pz1 =
-        (MU && (int)threadIdx.x + 2 * kThreads < nb) ? partZ[threadIdx.x + 2 * kThreads] : 0.0;
+    // Everything that the first row iteration (every block has one) needs, the
+    // partials of mu included, travels with the flag in one round trip; mu is
+    // reduced while the gathers are in flight.
     const int64_t bx = rbf::xcd_block(blockIdx.x, nb);
     int64_t r = bx * kThreads + wv * 32 + (lane & 31);
     int64_t rr = (r < P.m) ? r : P.m - 1;
-    T at = aux_row2<28>(P, rr, half, [&](int j) { return t1[j]; });
+    HalfRow<28, T> row;
+    row.load(P, rr, half);
+    const double pz0 = (MU && (int)threadIdx.x < nb) ? partZ[threadIdx.x] : 0.0;
+    const double pz1 =
+        (MU && (int)threadIdx.x + 2 * kThreads < nb) ? partZ[threadIdx.x + 2 * kThreads] : 0.0;
+    T tr = t1[rr], yr = y[rr], di = P.dinv[rr];
+    const T sc = (T)*ys;
+    const double mean = MU ? *L.mean : 0.0;
+    if (*L.flag != 0) return;
+    T at = row.sum([&](int j) { return t1[j]; });
     double mu = 0.0;
     if constexpr (MU) {
         double sz[1] = {pz0 + pz1};
         rbf::block_sum<1>(sz, lds);
-        mu = (*L.mean / L.c - sz[0]) / (double)P.m;
+        mu = (mean / L.c - sz[0]) / (double)P.m;
     }
-    const T sc = (T)*ys;
     double acc[1] = {0.0};
 #pragma unroll 1
     for (int64_t it = 0;; ++it) {
@@ -398,10 +433,12 @@ k_aux_post2(AuxOps<T> P, Lat L,
         if (it > 0) {
             r = (bx + it * nb) * kThreads + wv * 32 + (lane & 31);
             rr = (r < P.m) ? r : P.m - 1;
-            at = aux_row2<28>(P, rr, half, [&](int j) { return t1[j]; });
+            row.load(P, rr, half);
+            tr = t1[rr], yr = y[rr], di = P.dinv[rr];
+            at = row.sum([&](int j) { return t1[j]; });
         }
         if (half == 0 && r < P.m) {
-            const T zr = t1[r] + (T)mu + (MU ? (T)1 : (T)P.w2) * P.dinv[r] * (sc * y[r] - at);
+            const T zr = tr + (T)mu + (MU ? (T)1 : (T)P.w2) * di * (sc * yr - at);
             z[r] = zr;
             acc[0] += (double)zr;
         }
@@ -556,7 +593,7 @@ constexpr int kFgSlots = (kFgMax + 1) / 2;  // basis vectors per half-wave
 // (half 1), owned by the wave's lane 0.  fg_slot_add adds one pass's
 // products (half-wave sums by DPP; every lane must be active);
 // fg_slot_partials sums the waves in a fixed order and writes the block
-// partials of rows i <= j of part, scaled by vs_i.
+// partials of rows i <= j of part, scaled by vs_i (vsq: thread i's).
 template <int NW>
 __device__ __forceinline__ void fg_slot_zero(int ns, double *lds) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -581,7 +618,7 @@ __device__ __forceinline__ void fg_slot_add(const double (&prod)[kFgSlots], int 
 }
 
 template <int NW>
-__device__ __forceinline__ void fg_slot_partials(int j, const double *vs, double *part,
+__device__ __forceinline__ void fg_slot_partials(int j, double vsq, double *part,
                                                  const double *lds) {
     __syncthreads();
     if ((int)threadIdx.x <= j) {
@@ -589,34 +626,50 @@ __device__ __forceinline__ void fg_slot_partials(int j, const double *vs, double
         double t = 0.0;
 #pragma unroll
         for (int v = 0; v < NW; ++v) t += lds[q * NW + v];
-        part[(int64_t)q * kMaxBlocks + blockIdx.x] = t * vs[q];
+        part[(int64_t)q * kMaxBlocks + blockIdx.x] = t * vsq;
     }
 }
 
-template <class T>
-__global__ void __launch_bounds__(kAvThreads) __attribute__((amdgpu_waves_per_eu(4))) k_fg_av2(AuxOps<T> P, const double *__restrict__ u1,
-                                                       double vscale, FgDev<T> F, int j) {
-    if (*F.s.flag != 0) return;
+// EARLY: the basis values are loaded with the row's entries, before the product
+// (for grids of at most one block per CU, where registers are not scarce).
+template <class T, bool EARLY>
+__device__ __forceinline__ void fg_av2_rows(const AuxOps<T> &P, const double *__restrict__ u1,
+                                            double vscale, const FgDev<T> &F, int j) {
     constexpr int NW = kAvThreads / 64;
     __shared__ double lds[2 * kFgSlots * NW];
     const int lane = threadIdx.x & 63, half = lane >> 5, wv = threadIdx.x >> 6;
     const int nb = gridDim.x;  // <= kMaxBlocks = 2 blockDim.x: two partials per thread
     const T *z = F.Z + (int64_t)j * P.m;
     T *w = F.V + (int64_t)(j + 1) * P.m;
-    // The partials of 1^T z and the first row iteration's product (every
-    // block has one) are loaded before the border sum is reduced, so that
-    // the reduction overlaps the gathers.
-    const double po0 = ((int)threadIdx.x < nb) ? F.s.partO[threadIdx.x] : 0.0;
-    const double po1 =
-        ((int)threadIdx.x + kAvThreads < nb) ? F.s.partO[threadIdx.x + kAvThreads] : 0.0;
+    const int ns = (j + 2) >> 1;
+    // What the first row iteration (every block has one) needs, the partials of
+    // 1^T z included, travels with the flag in one round trip; the border sum is
+    // reduced while the gathers are in flight.
     const int64_t bx = rbf::xcd_block(blockIdx.x, nb);
     int64_t r = bx * kThreads + wv * 32 + (lane & 31);
     int64_t rr = (r < P.m) ? r : P.m - 1;
-    T az = aux_row2<28>(P, rr, half, [&](int c) { return z[c]; });
+    HalfRow<28, T> row;
+    row.load(P, rr, half);
+    const double po0 = ((int)threadIdx.x < nb) ? F.s.partO[threadIdx.x] : 0.0;
+    const double po1 =
+        ((int)threadIdx.x + kAvThreads < nb) ? F.s.partO[threadIdx.x + kAvThreads] : 0.0;
+    double ur = u1[rr];
+    const double vsq = ((int)threadIdx.x <= j) ? F.s.vs[threadIdx.x] : 0.0;
+    // Slot c of half 1 reads V[j+1] (this row of w, not yet stored) when
+    // 2c + 1 > j; that value is not used.
+    double vv[kFgSlots];
+    auto basis = [&]() {
+        const T *Vh = F.V + (int64_t)half * P.m + rr;
+#pragma unroll
+        for (int c = 0; c < kFgSlots; ++c)
+            vv[c] = (c < ns) ? (double)Vh[(int64_t)(2 * c) * P.m] : 0.0;
+    };
+    if constexpr (EARLY) basis();
+    if (*F.s.flag != 0) return;
+    T az = row.sum([&](int c) { return z[c]; });
     double sz[1] = {po0 + po1};
     rbf::block_sum<1>(sz, lds);
     const double bterm = vscale * sz[0];  // border: u1 c (1^T z)
-    const int ns = (j + 2) >> 1;
     fg_slot_zero<NW>(ns, lds);
 #pragma unroll 1
     for (int64_t it = 0;; ++it) {
@@ -624,29 +677,37 @@ __global__ void __launch_bounds__(kAvThreads) __attribute__((amdgpu_waves_per_eu
         if (it > 0) {
             r = (bx + it * nb) * kThreads + wv * 32 + (lane & 31);
             rr = (r < P.m) ? r : P.m - 1;
-            az = aux_row2<28>(P, rr, half, [&](int c) { return z[c]; });
+            row.load(P, rr, half);
+            ur = u1[rr];
+            az = row.sum([&](int c) { return z[c]; });
         }
-        const T wt = (T)((double)az + u1[rr] * bterm);
-        // The basis is read after the product, so that the two sets of
-        // loads in flight do not share the registers.  Slot c of half 1
-        // reads V[j+1] (this row of w, not yet stored) when 2c + 1 > j; that
-        // value is not used.
-        __builtin_amdgcn_sched_barrier(0);
-        const T *Vh = F.V + (int64_t)half * P.m + rr;
+        const T wt = (T)((double)az + ur * bterm);
+        // Not EARLY: the basis is read after the product, so that the two sets
+        // of loads in flight do not share the registers.
+        if (!EARLY || it > 0) {
+            __builtin_amdgcn_sched_barrier(0);
+            basis();
+        }
         const double wr = (r < P.m) ? (double)wt : 0.0;
         double prod[kFgSlots];
 #pragma unroll
-        for (int c = 0; c < kFgSlots; ++c) {
-            prod[c] = 0.0;
-            if (c < ns) {
-                const double v = (double)Vh[(int64_t)(2 * c) * P.m];
-                if (2 * c + half <= j) prod[c] = v * wr;
-            }
-        }
+        for (int c = 0; c < kFgSlots; ++c) prod[c] = (c < ns && 2 * c + half <= j) ? vv[c] * wr : 0.0;
         if (half == 0 && r < P.m) w[r] = wt;
         fg_slot_add<NW>(prod, ns, lds);
     }
-    fg_slot_partials<NW>(j, F.s.vs, F.s.part, lds);
+    fg_slot_partials<NW>(j, vsq, F.s.part, lds);
+}
+
+template <class T>
+__global__ void __launch_bounds__(kAvThreads) __attribute__((amdgpu_waves_per_eu(4)))
+k_fg_av2(AuxOps<T> P, const double *__restrict__ u1, double vscale, FgDev<T> F, int j) {
+    fg_av2_rows<T, false>(P, u1, vscale, F, j);
+}
+
+template <class T>
+__global__ void __launch_bounds__(kAvThreads) __attribute__((amdgpu_waves_per_eu(2)))
+k_fg_av2_few(AuxOps<T> P, const double *__restrict__ u1, double vscale, FgDev<T> F, int j) {
+    fg_av2_rows<T, true>(P, u1, vscale, F, j);
 }
 
 // Gram-Schmidt update w -= sum_i h_i vs_i V_i (i <= j).  PASS 1 (the first
@@ -657,58 +718,100 @@ __global__ void __launch_bounds__(kAvThreads) __attribute__((amdgpu_waves_per_eu
 // of a wave share row l, each reading the basis vectors of one parity
 // (slot c: i = 2c + h), which serve both the update and, in PASS 1, the
 // dots with the updated w.
-template <class T, int PASS>
+constexpr int kSumBlocks = 64;         // SUM: largest grid
+constexpr int kNormRow = kFgMax + 1;   // row of part that takes ||w||^2
+template <class T, int PASS, bool SUM>
 __global__ void __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_fg_gs(FgDev<T> F, const double *h,
                                                          const T *__restrict__ dinv, int64_t m,
                                                          int j) {
-    if (*F.s.flag != 0) return;
     constexpr int NW = 2 * kThreads / 64;
     __shared__ double c[kFgMax + 1];
     __shared__ double lds[2 * kFgSlots * NW];
-    for (int i = threadIdx.x; i <= j; i += blockDim.x) c[i] = h[i] * F.s.vs[i];
-    __syncthreads();
     const int lane = threadIdx.x & 63, half = lane >> 5, wv = threadIdx.x >> 6;
     const int nb = gridDim.x;
     const int ns = (j + 2) >> 1;
     const int64_t bx = rbf::xcd_block(blockIdx.x, nb);
     T *w = F.V + (int64_t)(j + 1) * m;
     double nrm[1] = {0.0};
+    int64_t r, rr;
+    double vv[kFgSlots], wr;
+    T di;
+    auto rows = [&](int64_t it) {
+        r = (bx + it * nb) * kThreads + wv * 32 + (lane & 31);
+        rr = (r < m) ? r : m - 1;
+        // Slot q of half 1 reads V[j+1] = w when 2q + 1 > j (not used).
+        const T *Vh = F.V + (int64_t)half * m + rr;
+#pragma unroll
+        for (int q = 0; q < kFgSlots; ++q) vv[q] = (q < ns) ? (double)Vh[(int64_t)(2 * q) * m] : 0.0;
+        wr = (double)w[rr];
+        di = (PASS == 2) ? dinv[rr] : (T)0;
+    };
+    // The first row iteration's loads, the coefficients and the flag in one
+    // round trip.  SUM: the coefficients are summed here from the block partials
+    // of the dots, 16 lanes each (grids of at most kSumBlocks blocks: one launch
+    // less per step); block 0 stores them for k_fg_tail.
+    rows(0);
+    const int q16 = threadIdx.x >> 4, l16 = threadIdx.x & 15;
+    double hs = 0.0, vsq = 0.0;
+    if constexpr (SUM) {
+        double pt[kSumBlocks / 16];
+#pragma unroll
+        for (int b = 0; b < kSumBlocks / 16; ++b) {
+            const int at = l16 + 16 * b;
+            pt[b] = (q16 <= j && at < nb) ? F.s.part[(int64_t)q16 * kMaxBlocks + at] : 0.0;
+        }
+#pragma unroll
+        for (int b = 0; b < kSumBlocks / 16; ++b) hs += pt[b];
+        vsq = (q16 <= j) ? F.s.vs[q16] : 0.0;
+    } else if ((int)threadIdx.x <= j) {
+        hs = h[threadIdx.x];
+        vsq = F.s.vs[threadIdx.x];
+    }
+    if (*F.s.flag != 0) return;
+    if constexpr (SUM) {
+        hs += rbf::dpp_move<0x128>(hs);
+        hs += rbf::dpp_move<0x124>(hs);
+        hs += rbf::dpp_move<0x4E>(hs);
+        hs += rbf::dpp_move<0xB1>(hs);
+        if (l16 == 0 && q16 <= j) {
+            c[q16] = hs * vsq;
+            if (blockIdx.x == 0) F.s.h1[q16] = hs;
+        }
+    } else if ((int)threadIdx.x <= j) {
+        c[threadIdx.x] = hs * vsq;
+    }
+    __syncthreads();
     if constexpr (PASS == 1) fg_slot_zero<NW>(ns, lds);
 #pragma unroll 1
     for (int64_t it = 0;; ++it) {
         if ((bx + it * nb) * kThreads >= m) break;
-        const int64_t r = (bx + it * nb) * kThreads + wv * 32 + (lane & 31);
-        const int64_t rr = (r < m) ? r : m - 1;
-        // Slot q of half 1 reads V[j+1] = w when 2q + 1 > j (not used).
-        const T *Vh = F.V + (int64_t)half * m + rr;
-        double vv[kFgSlots];
-#pragma unroll
-        for (int q = 0; q < kFgSlots; ++q) vv[q] = (q < ns) ? (double)Vh[(int64_t)(2 * q) * m] : 0.0;
+        if (it > 0) rows(it);
         double s = 0.0;
 #pragma unroll
         for (int q = 0; q < kFgSlots; ++q)
             if (q < ns && 2 * q + half <= j) s += c[2 * q + half] * vv[q];
         s += __shfl_xor(s, 32, 64);
-        const T wt = (T)((double)w[rr] - s);
+        const T wt = (T)(wr - s);
         if (half == 0 && r < m) {
             w[r] = wt;
-            if constexpr (PASS == 2) F.wd[r] = wt * dinv[r];
+            if constexpr (PASS == 2) F.wd[r] = wt * di;
             nrm[0] += (double)wt * (double)wt;
         }
         if constexpr (PASS == 1) {
-            const double wr = (r < m) ? (double)wt : 0.0;
+            const double wq = (r < m) ? (double)wt : 0.0;
             double prod[kFgSlots];
 #pragma unroll
             for (int q = 0; q < kFgSlots; ++q)
-                prod[q] = (q < ns && 2 * q + half <= j) ? vv[q] * wr : 0.0;
+                prod[q] = (q < ns && 2 * q + half <= j) ? vv[q] * wq : 0.0;
             fg_slot_add<NW>(prod, ns, lds);
         }
     }
     if constexpr (PASS == 1) {
-        fg_slot_partials<NW>(j, F.s.vs, F.s.part, lds);
+        fg_slot_partials<NW>(j, ((int)threadIdx.x <= j) ? F.s.vs[threadIdx.x] : 0.0, F.s.part, lds);
     } else {
+        // Row kNormRow: the partials of the dots (row 0 on) may still be read.
         rbf::block_sum<1>(nrm, lds);
-        if (threadIdx.x == 0) F.s.part[blockIdx.x] = nrm[0];
+        if (threadIdx.x == 0) F.s.part[(int64_t)kNormRow * kMaxBlocks + blockIdx.x] = nrm[0];
     }
 }
 
@@ -716,53 +819,56 @@ __global__ void __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_
 // H(j+1, j) = ||w||, previous rotations applied, a new rotation, the
 // residual estimate |g_{j+1}| and the status (4: the cycle's target met or
 // an exact breakdown; 3: the cycle is full; -1: non-finite).
-// ||w||^2 is reduced here from the block partials of k_fg_gs<2> (row 0 of
-// part, nb blocks), in the order k_fg_reduce uses.
+// ||w||^2 is reduced here from the block partials of k_fg_gs<2> (row kNormRow of
+// part, nb blocks).  One wave per quarter of the partials, every load in one
+// round trip; the column and the rotations are held one entry per lane of wave
+// 0, which runs the recurrence on values read by lane.
 __global__ void __launch_bounds__(256) k_fg_tail(FgScal F, int j, int mr, int nb) {
+    const int t = threadIdx.x, lane = t & 63;
+    const double *pn = F.part + (int64_t)kNormRow * kMaxBlocks;
+    double pv[kMaxBlocks / 256];
+#pragma unroll
+    for (int q = 0; q < kMaxBlocks / 256; ++q) {
+        const int b = t + 256 * q;
+        pv[q] = (b < nb) ? pn[b] : 0.0;
+    }
+    const bool first = t < 64;
+    const double hl = (first && lane <= j) ? F.h1[lane] + F.h2[lane] : 0.0;
+    const double cl = (first && lane < j) ? F.cs[lane] : 0.0;
+    const double sl = (first && lane < j) ? F.sn[lane] : 0.0;
+    const double gj = F.g[j], target = F.stat[2], back = F.resh[max(0, j + 1 - 4)];
     if (*F.flag != 0) return;
-    __shared__ double col[kFgMax + 1], cs[kFgMax], sn[kFgMax];
-    const int lane = threadIdx.x;
-    double v[1] = {0.0};
-    for (int b = lane; b < nb; b += 256) v[0] += F.part[b];
+    double v[1] = {(pv[0] + pv[1]) + (pv[2] + pv[3])};
+    static_assert(kMaxBlocks == 4 * 256, "four partials per thread");
     __shared__ double lds[4];
     rbf::block_sum<1>(v, lds);
-    for (int i = lane; i <= j; i += 256) {
-        col[i] = F.h1[i] + F.h2[i];
-        if (i < j) {
-            cs[i] = F.cs[i];
-            sn[i] = F.sn[i];
-        }
-    }
-    __syncthreads();
-    if (lane != 0) return;
-    double *Hc = F.H + (int64_t)j * (mr + 1);
-    F.hn2[0] = v[0];
+    if (!first) return;
     const double hn = sqrt(v[0]);
-    col[j + 1] = hn;
+    double a = rbf::readlane_double(hl, 0), col = 0.0;
     for (int i = 0; i < j; ++i) {
-        const double a = col[i], b = col[i + 1];
-        col[i] = cs[i] * a + sn[i] * b;
-        col[i + 1] = -sn[i] * a + cs[i] * b;
+        const double b = rbf::readlane_double(hl, i + 1), c = rbf::readlane_double(cl, i),
+                     s = rbf::readlane_double(sl, i);
+        if (lane == i) col = c * a + s * b;
+        a = c * b - s * a;
     }
-    const double a = col[j], b = col[j + 1];
-    const double den = hypot(a, b);
-    const double c = (den > 0.0) ? a / den : 1.0, s = (den > 0.0) ? b / den : 0.0;
+    const double den = hypot(a, hn);
+    const double c = (den > 0.0) ? a / den : 1.0, s = (den > 0.0) ? hn / den : 0.0;
+    if (lane == j) col = den;
+    if (lane <= j + 1) F.H[(int64_t)j * (mr + 1) + lane] = (lane <= j) ? col : 0.0;
+    if (lane != 0) return;
+    const double res = fabs(s * gj);
+    F.hn2[0] = v[0];
     F.cs[j] = c;
     F.sn[j] = s;
-    col[j] = den;
-    for (int i = 0; i <= j; ++i) Hc[i] = col[i];
-    Hc[j + 1] = 0.0;
-    const double gj = F.g[j];
     F.g[j] = c * gj;
     F.g[j + 1] = -s * gj;
-    const double res = fabs(s * gj);
     F.vs[j + 1] = (hn > 0.0) ? 1.0 / hn : 0.0;
     F.resh[j + 1] = res;
     F.step[0] = j + 1;
     F.stat[0] = res;
-    F.stat[1] = F.resh[max(0, j + 1 - 4)];
+    F.stat[1] = back;
     if (!isfinite(res) || !isfinite(den)) F.flag[0] = -1;
-    else if (res <= F.stat[2] || hn == 0.0 || den == 0.0) F.flag[0] = 4;
+    else if (res <= target || hn == 0.0 || den == 0.0) F.flag[0] = 4;
     else if (j + 1 >= mr) F.flag[0] = 3;
 }
 

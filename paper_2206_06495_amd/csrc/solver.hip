@@ -34,6 +34,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kMaxBlocks = 1024;
 constexpr int kMaxNR = 2;
+constexpr int kFewBlocks = 256;  // grids of at most one block per CU
 
 // ------------------------------------------------------------ gathers --
 template <int NR>
@@ -783,17 +784,16 @@ constexpr int kGemmWaves = 8;
 constexpr int kGemmChunk = 14;
 template <int STAGE, bool ONESHOT, class TP>
 __global__ void __launch_bounds__(64 * kGemmWaves) k_pc_gemm(Lat L) {
-    // The flag is tested first: a launch after convergence would otherwise
-    // fetch its whole operand share before exiting.
-    if (*L.flag != 0) return;
     const int n = L.n, nt = (n + 15) / 16;
     const int ti = (int)(blockIdx.x % nt), tj = (int)(blockIdx.x / nt);
     const TP *A = static_cast<const TP *>(STAGE == 0 ? L.Qi : L.Q);
     const TP *B = static_cast<const TP *>(STAGE == 0 ? L.X : L.W);
     TP *C = static_cast<TP *>(STAGE == 0 ? L.T : L.X);
     // T row-major (one mode per row, read whole by k_pc_tri), Z column-major.
+    // The flag travels with the first operand loads; the block ends there once
+    // it is set.
     rbf::mfma_block<TP, 1, 1, kGemmWaves, kGemmChunk, ONESHOT>(
-        n, A, B, ti, tj, [&](int i, int j, TP v) {
+        n, A, B, ti, tj, [&]() { return *L.flag == 0; }, [&](int i, int j, TP v) {
             if constexpr (STAGE == 0) C[(int64_t)i * n + j] = v;
             else C[i + (int64_t)j * n] = v;
         });
@@ -2904,24 +2904,32 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
                     prof_pair(S, RBF_PROF_SPMV, e0, e1);
                     prof_pair(S, RBF_PROF_GS, g0, g1);
                 }
-                if (P.k == 28)
+                if (P.k == 28 && nb <= kFewBlocks)
+                    hipExtLaunchKernelGGL((k_fg_av2_few<T>), grid, dim3(kAvThreads), 0, st, e0, e1, 0,
+                                          P, A.u1, A.vscale, F, j);
+                else if (P.k == 28)
                     hipExtLaunchKernelGGL((k_fg_av2<T>), grid, dim3(kAvThreads), 0, st, e0, e1, 0, P,
                                           A.u1, A.vscale, F, j);
                 else
                     hipExtLaunchKernelGGL((k_fg_av<0, T>), grid, block, 0, st, e0, e1, 0, P, A.u1,
                                           A.vscale, F, j);
-                hipLaunchKernelGGL(k_fg_reduce<true>, dim3(j + 1), red, 0, st, Fs.part, nb, j + 1,
-                                   Fs.h1, Fs.flag);
+                const bool sum = !kFgReorth && nb <= kSumBlocks;
+                if (!sum)
+                    hipLaunchKernelGGL(k_fg_reduce<true>, dim3(j + 1), red, 0, st, Fs.part, nb, j + 1,
+                                       Fs.h1, Fs.flag);
+                const dim3 b2(2 * kThreads);
                 if constexpr (kFgReorth) {
-                    hipExtLaunchKernelGGL((k_fg_gs<T, 1>), grid, dim3(2 * kThreads), 0, st, g0, g1, 0,
-                                          F, Fs.h1, P.dinv, m, j);
+                    hipExtLaunchKernelGGL((k_fg_gs<T, 1, false>), grid, b2, 0, st, g0, g1, 0, F,
+                                          Fs.h1, P.dinv, m, j);
                     hipLaunchKernelGGL(k_fg_reduce<true>, dim3(j + 1), red, 0, st, Fs.part, nb, j + 1,
                                        Fs.h2, Fs.flag);
-                    hipLaunchKernelGGL((k_fg_gs<T, 2>), grid, dim3(2 * kThreads), 0, st, F, Fs.h2,
-                                       P.dinv, m, j);
+                    hipLaunchKernelGGL((k_fg_gs<T, 2, false>), grid, b2, 0, st, F, Fs.h2, P.dinv, m, j);
+                } else if (sum) {
+                    hipExtLaunchKernelGGL((k_fg_gs<T, 2, true>), grid, b2, 0, st, g0, g1, 0, F, Fs.h1,
+                                          P.dinv, m, j);
                 } else {
-                    hipExtLaunchKernelGGL((k_fg_gs<T, 2>), grid, dim3(2 * kThreads), 0, st, g0, g1, 0,
-                                          F, Fs.h1, P.dinv, m, j);
+                    hipExtLaunchKernelGGL((k_fg_gs<T, 2, false>), grid, b2, 0, st, g0, g1, 0, F, Fs.h1,
+                                          P.dinv, m, j);
                 }
                 hipLaunchKernelGGL(k_fg_tail, one, red, 0, st, Fs, j, mr, nb);
                 S->prof_tag_now = -1;
