@@ -189,7 +189,7 @@ rbf_status rbf_assemble_weights(const double *xq, int64_t nq, const double *xs, 
  * w: device [k][rows]; x: device vector indexed by idx; y: device [rows].
  * dtype 0: w, x, y FP64, FP64 accumulation; dtype 1: w, x, y FP32, FP32
  * accumulation.  Launch shape: the one rbf_ell_autotune recorded for this
- * (dtype, k, rows), else the default.  No synchronisation.  Errors:
+ * (dtype, k, rows), else one by size.  No synchronisation.  Errors:
  * RBF_E_ARG for bad sizes/dtype.
  */
 rbf_status rbf_ell_apply(int64_t rows, int32_t k, const int32_t *idx, const void *w,
@@ -200,8 +200,10 @@ rbf_status rbf_ell_apply(int64_t rows, int32_t k, const int32_t *idx, const void
  * operator size by timing (for the 28-wide operators of Sec. 4; other
  * widths keep the default shape).  Shapes: block size 64, 128, 256 or
  * 512 threads (one row per thread) x blocks remapped to one contiguous row
- * range per XCD or not x operator loads non-temporal or not; shape 0 is the
- * default (256, remapped, non-temporal).  Every shape sums each row in the
+ * range per XCD or not x operator loads non-temporal or not.  Without tuning,
+ * operators of up to 84 MB run with 64 threads and temporal loads, larger
+ * ones with non-temporal loads and 64 (FP64) or 256 (FP32) threads, all
+ * remapped.  Every shape sums each row in the
  * same order, so results are bit-identical across shapes.  Each shape runs
  * once untimed and `reps` times timed with HIP events on `st`; the fastest
  * (the lower shape on ties) is recorded for (dtype, k, rows) in a

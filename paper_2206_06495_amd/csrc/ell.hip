@@ -35,6 +35,7 @@ __device__ __forceinline__ T ell_load(const T *p) {
     else return *p;
 }
 
+constexpr int kEllChunk = 8;
 template <class T, int KT, bool XCD = true, bool NT = true>
 __global__ void __launch_bounds__(512) k_ell_apply(int64_t rows, int k, const int *__restrict__ idx,
                                                    const T *__restrict__ w, const T *__restrict__ x,
@@ -53,10 +54,24 @@ __global__ void __launch_bounds__(512) k_ell_apply(int64_t rows, int k, const in
 #pragma unroll
         for (int s = 0; s < KT; ++s) acc = fma_t<T>(ww[s], x[jj[s]], acc);
     } else {
-#pragma unroll 4
-        for (int s = 0; s < k; ++s)
-            acc = fma_t<T>(rbf::ld_stream(w + (int64_t)s * rows + r),
-                           x[rbf::ld_stream(idx + (int64_t)s * rows + r)], acc);
+        // Chunks of kEllChunk slots with their loads in flight together (10^6 rows
+        // FP64: 32 slots 84.4 -> 77.1 us, 24 slots 62.2 -> 57.4).
+        int s0 = 0;
+        for (; s0 + kEllChunk <= k; s0 += kEllChunk) {
+            int jj[kEllChunk];
+            T ww[kEllChunk];
+#pragma unroll
+            for (int s = 0; s < kEllChunk; ++s)
+                jj[s] = ell_load<int, NT>(idx + (int64_t)(s0 + s) * rows + r);
+#pragma unroll
+            for (int s = 0; s < kEllChunk; ++s)
+                ww[s] = ell_load<T, NT>(w + (int64_t)(s0 + s) * rows + r);
+#pragma unroll
+            for (int s = 0; s < kEllChunk; ++s) acc = fma_t<T>(ww[s], x[jj[s]], acc);
+        }
+        for (; s0 < k; ++s0)
+            acc = fma_t<T>(ell_load<T, NT>(w + (int64_t)s0 * rows + r),
+                           x[ell_load<int, NT>(idx + (int64_t)s0 * rows + r)], acc);
     }
     y[r] = acc;
 }
@@ -225,14 +240,38 @@ __global__ void __launch_bounds__(64 * kTrWaves) k_ell_apply_t(int64_t ncols,
     const int64_t b = (c < ncols) ? colptr[c] : E1, e = (c < ncols) ? colptr[c + 1] : E1;
     T *pw = prod[wv];
     T acc = T(0);
+    // The weights and sources of the next chunk are loaded before this chunk's
+    // products are summed, which only waits for LDS (0.09 million columns FP64, 28
+    // wide: 15.6 -> 12.0 us; 10^6: 78.5 -> 77.1, the operator's own stream).
+    constexpr int PER = kTrChunk / 64;
+    T wv_[PER];
+    int sv[PER];
+    auto load = [&](int64_t ch) {
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            const int64_t e = ch + lane + 64 * q, ec = (e < E1) ? e : E1 - 1;
+            wv_[q] = wt[ec];
+            sv[q] = src[ec];
+        }
+    };
+    if (E0 < E1) load(E0);
     for (int64_t ch = E0; ch < E1; ch += kTrChunk) {
         const int64_t n = min((int64_t)kTrChunk, E1 - ch);
-#pragma unroll 4
-        for (int t = lane; t < n; t += 64) pw[t] = wt[ch + t] * y[src[ch + t]];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) pw[lane + 64 * q] = wv_[q] * y[sv[q]];
+        if (ch + kTrChunk < E1) load(ch + kTrChunk);
         __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS writes are done
         __builtin_amdgcn_wave_barrier();
-        const int64_t lo = max(b, ch), hi = min(e, ch + n);
-        for (int64_t i = lo; i < hi; ++i) acc += pw[i - ch];
+        int i = (int)(max(b, ch) - ch);
+        const int hi = (int)(min(e, ch + n) - ch);
+        for (; i + 3 < hi; i += 4) {  // four reads in flight, added in order
+            const T p0 = pw[i], p1 = pw[i + 1], p2 = pw[i + 2], p3 = pw[i + 3];
+            acc += p0;
+            acc += p1;
+            acc += p2;
+            acc += p3;
+        }
+        for (; i < hi; ++i) acc += pw[i];
         __builtin_amdgcn_wave_barrier();
     }
     if (c < ncols) z[c] = acc;
@@ -243,7 +282,7 @@ __global__ void __launch_bounds__(64 * kTrWaves) k_ell_apply_t(int64_t ncols,
 namespace {
 
 // Launch shapes of the 28-wide product: block size x XCD remap x operator
-// load kind.  Shape 0 is the default (256 threads, remap, non-temporal).
+// load kind.
 constexpr int kEllShapes = 16;
 struct EllShape {
     int block;
@@ -259,10 +298,24 @@ constexpr EllShape kShapes[kEllShapes] = {
 std::mutex g_tune_mu;
 std::map<std::tuple<int, int, int64_t>, int> g_tuned;
 
+// Whether an operator is read with temporal loads by default: where several of
+// its size fit the 256 MB last-level cache together, so that a program that goes
+// through a few of them finds each there again (0.25 million rows FP64, three
+// operators in turn: 17.3 us with non-temporal loads, 15.6 with temporal ones).
+// Larger ones push each other out, and temporal loads then cost more: 10^6 rows
+// FP32, three operators in turn, 45.7 and 52.7 us.
+bool ell_temporal(int dtype, int k, int64_t rows) {
+    return rows * k * (dtype == 0 ? 12 : 8) <= (int64_t)84 << 20;
+}
+
+// Shape of the 28-wide product: tuned, else 64 threads (65.5 against 66.3 us at 10^6
+// rows FP64, 2.6 against 3.3 at 3,600) with the remap and the load kind above; 256
+// threads for FP32 operators above that size (10^6 rows: 46.0 us with 64, 45.85).
 int tuned_shape(int dtype, int k, int64_t rows) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tuned.find(std::make_tuple(dtype, k, rows));
-    return it == g_tuned.end() ? 0 : it->second;
+    if (it != g_tuned.end()) return it->second;
+    return ell_temporal(dtype, k, rows) ? 9 : dtype == 0 ? 1 : 0;
 }
 
 template <class T>
@@ -365,18 +418,16 @@ extern "C" rbf_status rbf_ell_apply(int64_t rows, int32_t k, const int32_t *idx,
         RBF_CHECK_LAUNCH();
         return RBF_OK;
     }
-    const dim3 grid(rbf::blocks_for(rows, 256)), block(256);
-    if (dtype == 0) {
-        auto W = static_cast<const double *>(w);
-        auto X = static_cast<const double *>(x);
-        auto Y = static_cast<double *>(y);
-        hipLaunchKernelGGL((k_ell_apply<double, 0>), grid, block, 0, st, rows, k, idx, W, X, Y);
-    } else {
-        auto W = static_cast<const float *>(w);
-        auto X = static_cast<const float *>(x);
-        auto Y = static_cast<float *>(y);
-        hipLaunchKernelGGL((k_ell_apply<float, 0>), grid, block, 0, st, rows, k, idx, W, X, Y);
-    }
+    const dim3 grid(rbf::blocks_for(rows, 64)), block(64);
+#define RBF_ELL(T, NTL)                                                                            \
+    hipLaunchKernelGGL((k_ell_apply<T, 0, true, NTL>), grid, block, 0, st, rows, k, idx,            \
+                       static_cast<const T *>(w), static_cast<const T *>(x), static_cast<T *>(y))
+    const bool nt = !ell_temporal(dtype, k, rows);
+    if (dtype == 0 && nt) RBF_ELL(double, true);
+    else if (dtype == 0) RBF_ELL(double, false);
+    else if (nt) RBF_ELL(float, true);
+    else RBF_ELL(float, false);
+#undef RBF_ELL
     RBF_CHECK_LAUNCH();
     return RBF_OK;
 }
