@@ -63,6 +63,14 @@ __device__ __forceinline__ T ld_stream(const T *p) {
     return __builtin_nontemporal_load(p);
 }
 
+// Store to pinned host memory, past the caches, for a host that polls it.
+__device__ __forceinline__ void publish(uint64_t *p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void publish(uint64_t *p, double v) {
+    publish(p, (uint64_t)__double_as_longlong(v));
+}
+
 // A double moved across lanes by one DPP control (both 32-bit halves with
 // the same pattern; every lane active).
 template <int CTRL>

@@ -87,20 +87,27 @@ struct FgScal {
     double *vs;      // [mr+1] inverse norms
     double *part;    // [kFgMax + 2][kMaxBlocks] partial sums
     double *h1, *h2; // [mr+1] Gram-Schmidt coefficients of the two passes
-    double *hn2;     // [1] ||w||^2 after the last Gram-Schmidt pass
     double *H;       // [(mr+1) * mr] Hessenberg matrix, column-major
     double *cs, *sn; // [mr] Givens rotations
     double *g;       // [mr+1] rotated right-hand side
     double *y;       // [mr] coefficients of the update
-    double *resh;    // [mr+1] |g_{j}| per step of the cycle
     double *partZ;   // [kMaxBlocks] sums of J e (interpolated correction)
     double *partO;   // [kMaxBlocks] sums of z (border term of A z)
     double *one;     // [1] = 1.0 (unit scale of an explicit input vector)
-    // status, read by the host in one copy: flag, step, then (as doubles)
-    // |g_{j+1}| now, 4 steps earlier, the cycle's target, ||b||^2, beta.
-    int *flag, *step;
-    double *stat;
+    int *flag;
+    double *stat;    // the cycle's target, ||b||^2
+    // pinned host memory (fg_word): the word of the newest start or step, then
+    // ||b||^2 and beta of the cycle
+    uint64_t *pub;
 };
+
+// What the host follows a cycle by: the cycle's number, the residual estimate
+// over its target (the upper half of a float), the steps done and the flag.  One
+// 8-byte store, so it is read whole, without a copy or a synchronisation.
+__device__ __forceinline__ uint64_t fg_word(uint32_t seq, double ratio, int step, int flag) {
+    return (uint64_t)seq << 32 | (uint64_t)(__float_as_uint((float)ratio) & 0xffff0000u) |
+           (uint32_t)(step & 0xff) << 8 | (uint32_t)(flag & 0xff);
+}
 
 template <class T>
 struct FgDev {
@@ -498,28 +505,29 @@ __global__ void __launch_bounds__(256) k_fg_reduce(const double *part, int nb, i
 // tol ||b||; mixed: also kMixedInner beta), convergence of the true
 // residual (flag 1), g = beta e_1.  red: {||r||^2, ||b||^2}; ||b|| is
 // taken from the first cycle.
-__global__ void k_fg_start(FgScal F, const double *red, double tol, int mixed, int first) {
-    const double rr = red[0], bbv = first ? red[1] : F.stat[3];
+__global__ void k_fg_start(FgScal F, const double *red, double tol, int mixed, int first,
+                           uint32_t seq) {
+    const double rr = red[0], bbv = first ? red[1] : F.stat[1];
     const double beta = sqrt(rr);
     const double goal = tol * sqrt(fmax(bbv, 1e-300));
-    F.step[0] = 0;
-    F.stat[0] = beta;
-    F.stat[1] = beta;
-    F.stat[3] = bbv;
-    F.stat[4] = beta;
-    F.resh[0] = beta;
+    F.stat[1] = bbv;
+    int flag = 0;
+    double target = 1.0;
     if (!isfinite(beta)) {
-        F.flag[0] = -1;
-        return;
+        flag = -1;
+    } else if (beta <= goal || beta == 0.0) {
+        flag = 1;
+    } else {
+        target = mixed ? fmax(goal, kMixedInner * beta) : goal;
+        F.stat[0] = target;
+        F.vs[0] = 1.0 / beta;
+        F.g[0] = beta;
     }
-    if (beta <= goal || beta == 0.0) {
-        F.flag[0] = 1;
-        return;
-    }
-    F.stat[2] = mixed ? fmax(goal, kMixedInner * beta) : goal;
-    F.vs[0] = 1.0 / beta;
-    F.g[0] = beta;
-    F.flag[0] = 0;
+    F.flag[0] = flag;
+    rbf::publish(F.pub + 1, bbv);
+    rbf::publish(F.pub + 2, beta);
+    __hip_atomic_store(F.pub, fg_word(seq, beta / target, 0, flag), __ATOMIC_RELEASE,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Block partial dots (V_i vs_i, w) for i <= j, kFgChunk at a time; w is
@@ -823,7 +831,8 @@ __global__ void __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_
 // part, nb blocks).  One wave per quarter of the partials, every load in one
 // round trip; the column and the rotations are held one entry per lane of wave
 // 0, which runs the recurrence on values read by lane.
-__global__ void __launch_bounds__(256) k_fg_tail(FgScal F, int j, int mr, int nb) {
+__global__ void __launch_bounds__(256) k_fg_tail(FgScal F, int j, int mr, int nb,
+                                                  uint32_t seq) {
     const int t = threadIdx.x, lane = t & 63;
     const double *pn = F.part + (int64_t)kNormRow * kMaxBlocks;
     double pv[kMaxBlocks / 256];
@@ -836,7 +845,7 @@ __global__ void __launch_bounds__(256) k_fg_tail(FgScal F, int j, int mr, int nb
     const double hl = (first && lane <= j) ? F.h1[lane] + F.h2[lane] : 0.0;
     const double cl = (first && lane < j) ? F.cs[lane] : 0.0;
     const double sl = (first && lane < j) ? F.sn[lane] : 0.0;
-    const double gj = F.g[j], target = F.stat[2], back = F.resh[max(0, j + 1 - 4)];
+    const double gj = F.g[j], target = F.stat[0];
     if (*F.flag != 0) return;
     double v[1] = {(pv[0] + pv[1]) + (pv[2] + pv[3])};
     static_assert(kMaxBlocks == 4 * 256, "four partials per thread");
@@ -857,19 +866,17 @@ __global__ void __launch_bounds__(256) k_fg_tail(FgScal F, int j, int mr, int nb
     if (lane <= j + 1) F.H[(int64_t)j * (mr + 1) + lane] = (lane <= j) ? col : 0.0;
     if (lane != 0) return;
     const double res = fabs(s * gj);
-    F.hn2[0] = v[0];
     F.cs[j] = c;
     F.sn[j] = s;
     F.g[j] = c * gj;
     F.g[j + 1] = -s * gj;
     F.vs[j + 1] = (hn > 0.0) ? 1.0 / hn : 0.0;
-    F.resh[j + 1] = res;
-    F.step[0] = j + 1;
-    F.stat[0] = res;
-    F.stat[1] = back;
-    if (!isfinite(res) || !isfinite(den)) F.flag[0] = -1;
-    else if (res <= target || hn == 0.0 || den == 0.0) F.flag[0] = 4;
-    else if (j + 1 >= mr) F.flag[0] = 3;
+    const int flag = (!isfinite(res) || !isfinite(den))              ? -1
+                     : (res <= target || hn == 0.0 || den == 0.0) ? 4
+                     : (j + 1 >= mr)                              ? 3
+                                                                  : 0;
+    if (flag != 0) F.flag[0] = flag;
+    rbf::publish(F.pub, fg_word(seq, res / target, j + 1, flag));
 }
 
 // End of a cycle of nstep steps, one thread: back substitution H y = g.

@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <cstring>
 #include <string>
 #include <system_error>
 #include <thread>
@@ -1115,8 +1116,15 @@ struct HKry {
     double *rec;    // [iteration][component] {rho, alpha, omega, ||r||^2}
     double *bb, *rhrh;
     double *best;   // [parity][component][2] {best ||r||^2, its iteration}
-    int *flag, *iters;
+    int *flag;
+    uint64_t *pub;  // pinned host memory, an h_word per component
 };
+
+// What the host follows a viscous solve by: the solve's number, the newest
+// iteration or sweep tested (of at most 10^6) and the flag, in one 8-byte store.
+__device__ __forceinline__ uint64_t h_word(uint32_t seq, int i, int flag) {
+    return (uint64_t)seq << 32 | (uint64_t)((uint32_t)i << 8) | (uint32_t)(flag & 0xff);
+}
 
 __device__ __forceinline__ bool h_done(const int *flag) { return flag[0] != 0 && flag[1] != 0; }
 
@@ -1144,10 +1152,7 @@ __global__ void __launch_bounds__(kThreads) k_h_init(EllM A, const double *__res
         }
     }
     store_partials<2 * kHR>(acc, K.partI, nb);
-    if (blockIdx.x == 0 && threadIdx.x < kHR) {
-        K.flag[threadIdx.x] = 0;
-        K.iters[threadIdx.x] = 0;
-    }
+    if (blockIdx.x == 0 && threadIdx.x < kHR) K.flag[threadIdx.x] = 0;
 }
 
 // Finish iteration i-1 and build the new direction (see k_pc_dir).
@@ -1258,7 +1263,8 @@ __global__ void __launch_bounds__(kThreads) k_h_av(EllM A, HKry K, const double 
 // Stagnation (no 0.1% decrease of a component's best ||r||^2 for win
 // iterations) is handled like a breakdown, as in k_pc_s.
 __global__ void __launch_bounds__(kThreads) k_h_s(HKry K, const double *__restrict__ dinv,
-                                                   int64_t n, int i, int i0, double tol2, int win) {
+                                                   int64_t n, int i, int i0, double tol2, int win,
+                                                   uint32_t seq) {
     if (h_done(K.flag)) return;
     const int nb = gridDim.x;
     double q1[kHR], q3[kHR];
@@ -1291,11 +1297,9 @@ __global__ void __launch_bounds__(kThreads) k_h_s(HKry K, const double *__restri
             double *bnext = K.best + (((i & 1) * kHR) + c) * 2;
             bnext[0] = better ? rr : best;
             bnext[1] = better ? (double)i : (double)best_it;
-            if (bad) K.flag[c] = -1;
-            else if (conv || brk) {
-                K.flag[c] = conv ? 1 : 2;
-                K.iters[c] = i;
-            }
+            const int flag = bad ? -1 : conv ? 1 : brk ? 2 : 0;
+            if (flag != 0) K.flag[c] = flag;
+            rbf::publish(K.pub + c, h_word(seq, i, flag));
         }
         if (bad || conv || brk) act[c] = false;
     }
@@ -1334,6 +1338,7 @@ struct JKry {
     double *part;   // [2 parities][2 kHR][kMaxBlocks]
     double *bb;     // ||b||^2 per component
     int *flag;      // flag, then the index of the accepted iterate
+    uint64_t *pub;  // pinned host memory, an h_word
 };
 
 struct GatherI2 {
@@ -1348,7 +1353,7 @@ struct GatherI2 {
 
 template <int KT, bool FIRST>
 __global__ void __launch_bounds__(kThreads) k_h_jac(EllM A, const double *__restrict__ b, JKry J,
-                                                     int i, double tol2) {
+                                                     int i, double tol2, uint32_t seq) {
     const int nb = gridDim.x;
     const int fl = J.flag[0];
     double q[2 * kHR] = {};
@@ -1368,15 +1373,17 @@ __global__ void __launch_bounds__(kThreads) k_h_jac(EllM A, const double *__rest
             bad = bad || !isfinite(q[c]);
             conv = conv && (q[c] <= tol2 * fmax(q[kHR + c], 1e-300) || q[c] == 0.0);
         }
-        if (bad || conv) {
-            if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            const int flag = bad ? -1 : conv ? 1 : 0;
+            if (flag != 0) {
 #pragma unroll
                 for (int c = 0; c < kHR; ++c) J.bb[c] = q[kHR + c];
                 J.flag[1] = i - 1;
-                J.flag[0] = bad ? -1 : 1;
+                J.flag[0] = flag;
             }
-            return;
+            rbf::publish(J.pub, h_word(seq, i, flag));
         }
+        if (bad || conv) return;
     }
     // Iterate i: the caller's [2][N] guess for i = 0, else J.x[i & 1].
     const double2 *xin = reinterpret_cast<const double2 *>(J.x[i & 1]);
@@ -1426,7 +1433,8 @@ __global__ void __launch_bounds__(kThreads) k_h_jac(EllM A, const double *__rest
 // halves of row l's stencil.
 template <bool FIRST>
 __global__ void __launch_bounds__(2 * kThreads) k_h_jac2(EllM A, const double *__restrict__ b,
-                                                        JKry J, int i, double tol2) {
+                                                        JKry J, int i, double tol2,
+                                                        uint32_t seq) {
     constexpr int NW = 2 * kThreads / 64;
     __shared__ double lds[2 * kHR * NW];
     const int nb = gridDim.x;
@@ -1447,15 +1455,17 @@ __global__ void __launch_bounds__(2 * kThreads) k_h_jac2(EllM A, const double *_
             bad = bad || !isfinite(q[c]);
             conv = conv && (q[c] <= tol2 * fmax(q[kHR + c], 1e-300) || q[c] == 0.0);
         }
-        if (bad || conv) {
-            if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            const int flag = bad ? -1 : conv ? 1 : 0;
+            if (flag != 0) {
 #pragma unroll
                 for (int c = 0; c < kHR; ++c) J.bb[c] = q[kHR + c];
                 J.flag[1] = i - 1;
-                J.flag[0] = bad ? -1 : 1;
+                J.flag[0] = flag;
             }
-            return;
+            rbf::publish(J.pub, h_word(seq, i, flag));
         }
+        if (bad || conv) return;
     }
     const double2 *xin = reinterpret_cast<const double2 *>(J.x[i & 1]);
     double2 *xout = reinterpret_cast<double2 *>(J.x[(i & 1) ^ 1]);
@@ -1504,13 +1514,29 @@ __global__ void __launch_bounds__(2 * kThreads) k_h_jac2(EllM A, const double *_
     }
 }
 
-// x ([2][N]) from an interleaved iterate ([N][2]).
-__global__ void k_h_deint(int64_t n, const double2 *__restrict__ xi, double *__restrict__ x) {
+// x ([2][N]) from an interleaved iterate ([N][2]), and the block partials of the
+// accepted iterate's residual and of ||b||^2 (4 rows of nb, nb <= n) to the host.
+__global__ void k_h_deint(int64_t n, const double2 *__restrict__ xi, double *__restrict__ x,
+                          const double *__restrict__ part, const double *__restrict__ partb, int nb,
+                          uint64_t *host) {
     const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (r < kHR * nb) rbf::publish(host + r, part[(r / nb) * kMaxBlocks + r % nb]);
+    else if (r < 2 * kHR * nb)
+        rbf::publish(host + r, partb[(r / nb - kHR) * kMaxBlocks + r % nb]);
     if (r >= n) return;
     const double2 t = xi[r];
     x[r] = t.x;
     x[n + r] = t.y;
+}
+
+// The block partials of the final residual (2 rows of nb) and ||b||^2 (null: left) to the
+// host, as k_h_deint.
+__global__ void k_h_publish(const double *__restrict__ part, const double *__restrict__ bb, int nb,
+                            uint64_t *host) {
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < kHR * nb) rbf::publish(host + r, part[r]);
+    else if (bb && r < 2 * kHR * nb)
+        rbf::publish(host + r, (r % nb == 0) ? bb[r / nb - kHR] : 0.0);
 }
 
 // Block maxima of |1/h_ii| sum_{j != i} |h_ij| (the Jacobi bound above).
@@ -1872,7 +1898,7 @@ struct rbf_solver {
     KDev kp{};
     double *rpart = nullptr;
     int last_iters_h = 0, last_iters_p = 0;
-    int p_hist[3] = {0, 0, 0};  // iteration counts of the last pressure solves (ring)
+    int p_hist[3] = {0, 0, 0};  // iterations of the last lattice-preconditioned solves (ring)
     int p_nhist = 0, p_pos = 0;
     // optional sampling of the Poisson SpMV duration with HIP events
     // Sampled kernel durations (rbf_solver_profile): event pairs recorded
@@ -1936,6 +1962,9 @@ struct rbf_solver {
     // pinned host buffers
     int *hflag = nullptr;
     double *hred = nullptr;
+    uint64_t *pub = nullptr;  // words and values stored by kernels (kPub*)
+    uint32_t pub_seq = 0;     // number of the newest cycle or viscous solve
+    int pend_nb = 0;          // blocks of the viscous residual at pub + kPubStat (0: none)
     std::vector<void *> allocs;
 };
 
@@ -1969,6 +1998,65 @@ void prof_flush(rbf_solver *S, int steps_done = 1 << 30) {
         }
         S->prof_pending[q] = 0;
     }
+}
+
+// Layout of S->pub: words of FGMRES (three), of the viscous solve (one per
+// component), block partials of the viscous residual.
+constexpr int kPubVisc = 4, kPubStat = 8;
+
+// Wait until ok(word) holds for a word that a launched kernel publishes.  The
+// kernels store it by themselves, so a wait costs the host a few microseconds
+// after the store and the stream no copy and no drain (a copy of a status block and
+// a synchronisation: 45 us, nine of them in a time step at h = 1/40).  The stream
+// is looked at now and then: one that has failed, or has ended without the
+// word, is an error here instead of a wait without end.
+template <class Ok>
+rbf_status wait_word(rbf_solver *S, const uint64_t *word, Ok ok) {
+    for (unsigned n = 1;; ++n) {
+        if (ok(__atomic_load_n(word, __ATOMIC_ACQUIRE))) return RBF_OK;
+        __builtin_ia32_pause();
+        if (n % 256 == 0) std::this_thread::yield();
+        if (n % 8192 != 0) continue;
+        const hipError_t e = hipStreamQuery(S->st);
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();
+            continue;
+        }
+        RBF_HIP(e);
+        if (ok(__atomic_load_n(word, __ATOMIC_ACQUIRE))) return RBF_OK;
+        rbf::set_error("solver: the stream ended without its status");
+        return RBF_E_DEVICE;
+    }
+}
+
+// The flag and index of viscous solve seq, component c: waits until it has a flag
+// or has tested index `least`.
+rbf_status wait_visc(rbf_solver *S, uint32_t seq, int c, int least, int &flag, int &index) {
+    return wait_word(S, S->pub + kPubVisc + c, [&](uint64_t w) {
+        if ((uint32_t)(w >> 32) != seq) return false;
+        flag = (int8_t)(w & 0xff);
+        index = (int)((uint32_t)w >> 8);
+        return flag != 0 || index >= least;
+    });
+}
+
+// Relative residuals of the last viscous solve from the block partials it left at
+// the host, once the stream has passed the kernel that stored them.
+void visc_residuals(rbf_solver *S, rbf_solve_stats *stats) {
+    const uint64_t *w = S->pub + kPubStat;
+    const int nb = S->pend_nb;
+    for (int c = 0; c < kHR && nb > 0; ++c) {
+        double rr = 0.0, bb = 0.0;
+        for (int b = 0; b < nb; ++b) {
+            double r, q;
+            std::memcpy(&r, w + c * nb + b, sizeof(r));
+            std::memcpy(&q, w + (kHR + c) * nb + b, sizeof(q));
+            rr += r;
+            bb += q;
+        }
+        stats[c].rel_residual = (bb > 0.0) ? std::sqrt(rr / bb) : std::sqrt(rr);
+    }
+    S->pend_nb = 0;
 }
 
 rbf_status dalloc(rbf_solver *S, void **p, size_t bytes) {
@@ -2286,78 +2374,63 @@ rbf_status hjacobi(rbf_solver *S, EllM A, const double *b, double *x, double tol
     const double tol2 = tol * tol;
     const bool k28 = A.k == 28;
     RBF_HIP(hipMemsetAsync(J.flag, 0, 2 * sizeof(int), st));
+    const uint32_t seq = ++S->pub_seq;
     // Sweep i tests x_{i-1}; x_maxit is tested by sweep maxit + 1.
-    int it = 0, f = 0;
+    int it = 0, f = 0, at = 0;
     int batch = std::max(2, last_iters + 2);
     for (;;) {
         const int stop = std::min(maxit + 2, it + batch);
         for (; it < stop; ++it) {
             if (it == 0) {
-                if (k28) hipLaunchKernelGGL((k_h_jac2<true>), grid, dim3(2 * kThreads), 0, st, A, b, J, it, tol2);
-                else hipLaunchKernelGGL((k_h_jac<0, true>), grid, block, 0, st, A, b, J, it, tol2);
+                if (k28) hipLaunchKernelGGL((k_h_jac2<true>), grid, dim3(2 * kThreads), 0, st, A, b, J, it, tol2, seq);
+                else hipLaunchKernelGGL((k_h_jac<0, true>), grid, block, 0, st, A, b, J, it, tol2, seq);
             } else {
-                if (k28) hipLaunchKernelGGL((k_h_jac2<false>), grid, dim3(2 * kThreads), 0, st, A, b, J, it, tol2);
-                else hipLaunchKernelGGL((k_h_jac<0, false>), grid, block, 0, st, A, b, J, it, tol2);
+                if (k28) hipLaunchKernelGGL((k_h_jac2<false>), grid, dim3(2 * kThreads), 0, st, A, b, J, it, tol2, seq);
+                else hipLaunchKernelGGL((k_h_jac<0, false>), grid, block, 0, st, A, b, J, it, tol2, seq);
             }
         }
         RBF_CHECK_LAUNCH();
-        RBF_HIP(hipMemcpyAsync(S->hflag, J.flag, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
-        RBF_HIP(hipStreamSynchronize(st));
-        f = S->hflag[0];
+        rbf_status wrc = wait_visc(S, seq, 0, it - 1, f, at);
+        if (wrc != RBF_OK) return wrc;
         if (f != 0 || it >= maxit + 2) break;
         batch = 2;
     }
     // The accepted iterate, or the newest one when the sweeps ran out.
-    const int fin = (f != 0) ? S->hflag[1] : it;
-    if (fin > 0)  // iterate fin lives in J.x[fin & 1], interleaved
-        hipLaunchKernelGGL(k_h_deint, dim3(rbf::blocks_for(n, 256)), dim3(256), 0, st, n,
-                           reinterpret_cast<const double2 *>(J.x[fin & 1]), x);
+    const int fin = (f != 0) ? at - 1 : it;
     // Statistics: the sweep that produced the accepted iterate's test left
     // the partials of its true residual and of ||b||^2 (slot fin & 1); after
     // running out of sweeps the newest iterate's residual is recomputed.
     const double *pf = J.part + (int64_t)(fin & 1) * 2 * kHR * kMaxBlocks;
-    if (f != 1) {
-        if (k28) hipLaunchKernelGGL((k_resid<kHR, 28>), grid, block, 0, st, A, b, x, S->rpart, nullptr);
-        else hipLaunchKernelGGL((k_resid<kHR, 0>), grid, block, 0, st, A, b, x, S->rpart, nullptr);
-        RBF_CHECK_LAUNCH();
-        RBF_HIP(hipMemcpyAsync(S->hred, S->rpart, (size_t)kHR * nb * sizeof(double), hipMemcpyDeviceToHost, st));
-    } else {
-        for (int c = 0; c < kHR; ++c)
-            RBF_HIP(hipMemcpyAsync(S->hred + c * nb, pf + (int64_t)c * kMaxBlocks, nb * sizeof(double),
-                                   hipMemcpyDeviceToHost, st));
-    }
     // ||b||^2 partials (b is fixed): from the same sweep, or from the last
     // sweep launched when none was accepted (every launched sweep ran).
     const double *pb = ((f == 1) ? pf : J.part + (int64_t)((std::max(it, 1) - 1) & 1) * 2 * kHR * kMaxBlocks) +
                        (int64_t)kHR * kMaxBlocks;
-    for (int c = 0; c < kHR; ++c)
-        RBF_HIP(hipMemcpyAsync(S->hred + kMaxNR * nb + c * nb, pb + (int64_t)c * kMaxBlocks,
-                               nb * sizeof(double), hipMemcpyDeviceToHost, st));
-    RBF_HIP(hipStreamSynchronize(st));
-    rbf_status rc = RBF_OK;
-    for (int c = 0; c < kHR; ++c) {
-        double rr = 0.0, bb = 0.0;
-        for (int bidx = 0; bidx < nb; ++bidx) {
-            rr += S->hred[c * nb + bidx];
-            bb += S->hred[kMaxNR * nb + c * nb + bidx];
-        }
-        if (stats) {
-            stats[c].iterations = fin;
-            stats[c].converged = (f == 1);
-            stats[c].rel_residual = (bb > 0.0) ? std::sqrt(rr / bb) : std::sqrt(rr);
-            stats[c].restarts = 0;
-            stats[c].final_flag = f;
-        }
+    // Iterate fin > 0 lives in J.x[fin & 1], interleaved.
+    hipLaunchKernelGGL(k_h_deint, dim3(rbf::blocks_for(n, 256)), dim3(256), 0, st, fin > 0 ? n : 0,
+                       reinterpret_cast<const double2 *>(J.x[fin & 1]), x, pf, pb, nb, S->pub + kPubStat);
+    RBF_CHECK_LAUNCH();
+    for (int c = 0; c < kHR && stats; ++c) {
+        stats[c].iterations = fin;
+        stats[c].converged = (f == 1);
+        stats[c].restarts = 0;
+        stats[c].final_flag = f;
     }
+    S->pend_nb = nb;
+    last_iters = fin;
+    if (f == 1) return RBF_OK;
+    if (k28) hipLaunchKernelGGL((k_resid<kHR, 28>), grid, block, 0, st, A, b, x, S->rpart, nullptr);
+    else hipLaunchKernelGGL((k_resid<kHR, 0>), grid, block, 0, st, A, b, x, S->rpart, nullptr);
+    hipLaunchKernelGGL(k_h_publish, dim3(rbf::blocks_for(2 * kHR * nb, 256)), dim3(256), 0, st,
+                       S->rpart, nullptr, nb, S->pub + kPubStat);
+    RBF_CHECK_LAUNCH();
+    RBF_HIP(hipStreamSynchronize(st));
+    if (stats) visc_residuals(S, stats);
     if (f == -1) {
         rbf::set_error("Jacobi sweeps: non-finite residual (sweep %d)", fin);
-        rc = RBF_E_NAN;
-    } else if (f != 1) {
-        rbf::set_error("Jacobi sweeps: no convergence (%d of %d sweeps)", it, maxit);
-        rc = RBF_E_NOCONV;
+        return RBF_E_NAN;
     }
-    last_iters = fin;
-    return rc;
+    rbf::set_error("Jacobi sweeps: no convergence (%d of %d sweeps)", it, maxit);
+    return RBF_E_NOCONV;
 }
 
 // Mixed-precision viscous solve (see k_hm_res): outer FP64 residuals with
@@ -2373,10 +2446,11 @@ rbf_status hmixed(rbf_solver *S, EllM A, const double *b, double *x, double tol,
     const double tol2 = tol * tol;
     const bool k28 = A.k == 28;
     hipLaunchKernelGGL(k_hm_clear, dim3(1), dim3(64), 0, st, X.flag);
+    const uint32_t seq = ++S->pub_seq;
     auto sweeps = [&](int i) {
         for (int s = 0; s < kHMixSweeps; ++s) {
             const bool test = s == 0, last = s == kHMixSweeps - 1;
-#define HM_SWEEP(KT, T, L) hipLaunchKernelGGL((k_hm_sweep<KT, T, L>), grid, block, 0, st, X, i, s, tol2, nb)
+#define HM_SWEEP(KT, T, L) hipLaunchKernelGGL((k_hm_sweep<KT, T, L>), grid, block, 0, st, X, i, s, tol2, nb, seq)
             if (k28) {
                 if (test && last) HM_SWEEP(28, true, true);
                 else if (test) HM_SWEEP(28, true, false);
@@ -2393,7 +2467,7 @@ rbf_status hmixed(rbf_solver *S, EllM A, const double *b, double *x, double tol,
     };
     // Outer iteration i launches r_i (tested by the sweep after it) and its
     // sweeps; iteration maxit only tests.
-    int i = 0, f = 0;
+    int i = 0, f = 0, at = 0;
     int batch = std::max(1, last_iters + 1);
     for (;;) {
         const int stop = std::min(maxit + 1, i + batch);
@@ -2408,45 +2482,34 @@ rbf_status hmixed(rbf_solver *S, EllM A, const double *b, double *x, double tol,
             sweeps(i);
         }
         RBF_CHECK_LAUNCH();
-        RBF_HIP(hipMemcpyAsync(S->hflag, X.flag, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
-        RBF_HIP(hipStreamSynchronize(st));
-        f = S->hflag[0];
+        rbf_status wrc = wait_visc(S, seq, 0, i - 1, f, at);
+        if (wrc != RBF_OK) return wrc;
         if (f != 0 || i > maxit) break;
         batch = 1;
     }
     // The iterate X.x is x_fin when accepted (the sweeps after the test exit).
-    const int fin = (f != 0) ? S->hflag[1] : maxit;
-    hipLaunchKernelGGL(k_h_deint, dim3(rbf::blocks_for(n, 256)), dim3(256), 0, st, n, X.x, x);
-    RBF_CHECK_LAUNCH();
+    const int fin = (f != 0) ? at : maxit;
     const double *pf = X.part + (int64_t)(fin & 1) * 2 * kHR * kMaxBlocks;
-    for (int c = 0; c < 2 * kHR; ++c)
-        RBF_HIP(hipMemcpyAsync(S->hred + c * nb, pf + (int64_t)c * kMaxBlocks, nb * sizeof(double),
-                               hipMemcpyDeviceToHost, st));
-    RBF_HIP(hipStreamSynchronize(st));
-    rbf_status rc = RBF_OK;
-    for (int c = 0; c < kHR; ++c) {
-        double rr = 0.0, bb = 0.0;
-        for (int bidx = 0; bidx < nb; ++bidx) {
-            rr += S->hred[c * nb + bidx];
-            bb += S->hred[(kHR + c) * nb + bidx];
-        }
-        if (stats) {
-            stats[c].iterations = fin;
-            stats[c].converged = (f == 1);
-            stats[c].rel_residual = (bb > 0.0) ? std::sqrt(rr / bb) : std::sqrt(rr);
-            stats[c].restarts = 0;
-            stats[c].final_flag = f;
-        }
+    hipLaunchKernelGGL(k_h_deint, dim3(rbf::blocks_for(n, 256)), dim3(256), 0, st, n, X.x, x, pf,
+                       pf + (int64_t)kHR * kMaxBlocks, nb, S->pub + kPubStat);
+    RBF_CHECK_LAUNCH();
+    for (int c = 0; c < kHR && stats; ++c) {
+        stats[c].iterations = fin;
+        stats[c].converged = (f == 1);
+        stats[c].restarts = 0;
+        stats[c].final_flag = f;
     }
+    S->pend_nb = nb;
+    last_iters = fin;
+    if (f == 1) return RBF_OK;
+    RBF_HIP(hipStreamSynchronize(st));
+    if (stats) visc_residuals(S, stats);
     if (f == -1) {
         rbf::set_error("mixed-precision viscous solve: non-finite residual (outer step %d)", fin);
-        rc = RBF_E_NAN;
-    } else if (f != 1) {
-        rbf::set_error("mixed-precision viscous solve: no convergence (%d outer steps)", maxit);
-        rc = RBF_E_NOCONV;
+        return RBF_E_NAN;
     }
-    last_iters = fin;
-    return rc;
+    rbf::set_error("mixed-precision viscous solve: no convergence (%d outer steps)", maxit);
+    return RBF_E_NOCONV;
 }
 
 // Viscous solve (both components): Jacobi right-preconditioned BiCGSTAB
@@ -2476,9 +2539,14 @@ rbf_status hbicgstab(rbf_solver *S, EllM A, const double *b, double *x, double t
         }
     };
     init();
+    uint32_t seq = ++S->pub_seq;
     int it = 0, i0 = 0, restarts = 0;
     rbf_status rc = RBF_OK;
-    int batch = std::max(2, last_iters > 0 ? last_iters : 4);
+    int flag[kHR] = {}, at[kHR] = {};
+    // The first batch ends with the iteration that tested the last solve's
+    // solution; from there one at a time, so that what is launched depends on the
+    // solves alone and not on when the host looks.
+    int batch = std::max(2, last_iters > 0 ? last_iters + 1 : 4);
     int win = kStall;
     bool done = false;
     while (!done) {
@@ -2486,53 +2554,41 @@ rbf_status hbicgstab(rbf_solver *S, EllM A, const double *b, double *x, double t
         for (; it < stop; ++it) {
             hipLaunchKernelGGL(k_h_dir, grid, block, 0, st, K, A.dinv, x, n, it, i0);
             av(0, K.ph, K.v);
-            hipLaunchKernelGGL(k_h_s, grid, block, 0, st, K, A.dinv, n, it, i0, tol2, win);
+            hipLaunchKernelGGL(k_h_s, grid, block, 0, st, K, A.dinv, n, it, i0, tol2, win, seq);
             av(1, K.sh, K.t);
         }
         RBF_CHECK_LAUNCH();
-        RBF_HIP(hipMemcpyAsync(S->hflag, K.flag, kHR * sizeof(int), hipMemcpyDeviceToHost, st));
-        RBF_HIP(hipMemcpyAsync(S->hflag + kMaxNR, K.iters, kHR * sizeof(int), hipMemcpyDeviceToHost, st));
-        RBF_HIP(hipStreamSynchronize(st));
-        prof_flush(S);
+        for (int c = 0; c < kHR; ++c)
+            if ((rc = wait_visc(S, seq, c, it - 1, flag[c], at[c])) != RBF_OK) return rc;
         done = true;
         bool restart = false;
         int brk_at = it;
         for (int c = 0; c < kHR; ++c) {
-            if (S->hflag[c] == 0) done = false;
-            if (S->hflag[c] == 2) {
+            if (flag[c] == 0) done = false;
+            if (flag[c] == 2) {
                 restart = true;
-                brk_at = std::min(brk_at, S->hflag[kMaxNR + c]);
+                brk_at = std::min(brk_at, at[c]);
             }
         }
         if (restart && it <= maxit && restarts < 50) {
             ++restarts;
             it = i0 = brk_at;
             init();
+            seq = ++S->pub_seq;
             done = false;
             win = std::min(2 * win, 1 << 20);
             continue;
         }
         if (!done && it > maxit) break;
-        batch = 2;
+        batch = 1;
     }
-    if (k28) hipLaunchKernelGGL((k_resid<kHR, 28>), grid, block, 0, st, A, b, x, S->rpart, nullptr);
-    else hipLaunchKernelGGL((k_resid<kHR, 0>), grid, block, 0, st, A, b, x, S->rpart, nullptr);
-    RBF_CHECK_LAUNCH();
-    RBF_HIP(hipMemcpyAsync(S->hred, S->rpart, (size_t)kHR * nb * sizeof(double), hipMemcpyDeviceToHost, st));
-    RBF_HIP(hipMemcpyAsync(S->hred + kMaxNR * kMaxBlocks, K.bb, kHR * sizeof(double), hipMemcpyDeviceToHost, st));
-    RBF_HIP(hipStreamSynchronize(st));
     int maxi = 0;
     for (int c = 0; c < kHR; ++c) {
-        double rr = 0.0;
-        for (int bidx = 0; bidx < nb; ++bidx) rr += S->hred[c * nb + bidx];
-        const double bb = S->hred[kMaxNR * kMaxBlocks + c];
-        const int f = S->hflag[c];
-        const int iters = (f == 1) ? S->hflag[kMaxNR + c] : it;
+        const int f = flag[c], iters = (f == 1) ? at[c] : it;
         maxi = std::max(maxi, iters);
         if (stats) {
             stats[c].iterations = iters;
             stats[c].converged = (f == 1);
-            stats[c].rel_residual = (bb > 0.0) ? std::sqrt(rr / bb) : std::sqrt(rr);
             stats[c].restarts = restarts;
             stats[c].final_flag = f;
         }
@@ -2546,6 +2602,18 @@ rbf_status hbicgstab(rbf_solver *S, EllM A, const double *b, double *x, double t
         }
     }
     last_iters = maxi;
+    if (stats) {  // the true residual
+        if (k28) hipLaunchKernelGGL((k_resid<kHR, 28>), grid, block, 0, st, A, b, x, S->rpart, nullptr);
+        else hipLaunchKernelGGL((k_resid<kHR, 0>), grid, block, 0, st, A, b, x, S->rpart, nullptr);
+        hipLaunchKernelGGL(k_h_publish, dim3(rbf::blocks_for(2 * kHR * nb, 256)), dim3(256), 0, st,
+                           S->rpart, K.bb, nb, S->pub + kPubStat);
+        RBF_CHECK_LAUNCH();
+        S->pend_nb = nb;
+        if (rc != RBF_OK) {
+            RBF_HIP(hipStreamSynchronize(st));
+            visc_residuals(S, stats);
+        }
+    }
     return rc;
 }
 
@@ -2843,12 +2911,17 @@ constexpr bool kFgReorth = false;
 // refinement (see pressure_aux.h).  maxit counts Arnoldi steps
 // (preconditioner applications).  apply(y, W y, ys, z, sample): one application
 // of the preconditioner.  sumw: weights of the sum in the border term of x
-// (null: 1; its launches are not sampled).  expect: steps the solve is likely to need (0: unknown).  accept:
-// a cycle that starts with more than half of the last one's true residual ends
-// the solve as converged if that is within accept times the tolerance (1: off).
+// (null: 1; its launches are not sampled).  accept: a cycle that starts with more
+// than half of the last one's true residual ends the solve as converged if that is
+// within accept times the tolerance (1: off).
+//
+// The host follows the words that k_fg_start and k_fg_tail publish and keeps a few
+// steps queued ahead of the device, as many as the residual's rate still asks
+// for: launches after the one that ends a cycle exit at the flag, and about 13 of
+// them are a step (25 us at h = 1/40, where a step takes 60).
 template <class T, class Apply>
 rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, const double *sumw,
-                      const double *b, double *x, double tol, int maxit, int expect, double accept,
+                      const double *b, double *x, double tol, int maxit, double accept,
                       int &last_iters, rbf_solve_stats *stats, Apply apply) {
     hipStream_t st = S->st;
     const int64_t m = A.n;
@@ -2858,14 +2931,22 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
     const int mixed = std::is_same<T, float>::value ? 1 : 0;
     FgScal &Fs = F.s;
     int total = 0, cycles = 0, f = 0;
-    bool first = true;
-    double beta_prev = INFINITY;
-    auto status = [&]() -> rbf_status {
-        RBF_HIP(hipMemcpyAsync(S->hflag, Fs.flag, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
-        RBF_HIP(hipMemcpyAsync(S->hflag + 2, Fs.stat, 5 * sizeof(double), hipMemcpyDeviceToHost, st));
-        RBF_HIP(hipStreamSynchronize(st));
-        prof_flush(S, S->hflag[1]);
-        return RBF_OK;
+    double beta_prev = INFINITY, bb = 0.0, beta = 0.0;
+    uint32_t seq = 0;
+    // The newest word of this cycle, waiting for one of a step >= least or a flag.
+    int done = 0;
+    double ratio = 0.0;
+    auto word = [&](int least) {
+        return wait_word(S, Fs.pub, [&](uint64_t w) {
+            if ((uint32_t)(w >> 32) != seq) return least < 0;
+            const uint32_t rb = (uint32_t)w & 0xffff0000u;
+            float r;
+            std::memcpy(&r, &rb, sizeof(r));
+            f = (int8_t)(w & 0xff);
+            done = (int)(w >> 8 & 0xff);
+            ratio = r;
+            return f != 0 || done >= least;
+        });
     };
     rbf_status rc = RBF_OK;
     for (;;) {
@@ -2876,99 +2957,98 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
                                S->kp.partX, F.V, P.dinv, F.wd, Fs.part);
         });
         hipLaunchKernelGGL(k_fg_reduce<false>, dim3(2), red, 0, st, Fs.part, nb, 2, Fs.h1, Fs.flag);
-        hipLaunchKernelGGL(k_fg_start, one, one, 0, st, Fs, Fs.h1, tol, mixed, first ? 1 : 0);
-        first = false;
-        if (total >= maxit) {  // only the convergence test of the iterate
-            if ((rc = status()) != RBF_OK) return rc;
-            f = S->hflag[0];
-            break;
-        }
-        int j = 0;
-        // First batch of a cycle: the steps the last solve needed beyond
-        // those already taken, less one (later batches follow the
-        // residual's rate); 6 when nothing is known.
-        int batch = 6;
-        if (expect > 0)
-            batch = (cycles == 0) ? std::max(2, std::min(mr, expect - 2))
-                                  : std::max(2, std::min(6, expect - total - 1));
-        for (;;) {
-            const int stop = std::min(mr, j + batch);
-            for (; j < stop; ++j) {
-                const int64_t o = (int64_t)j * m;
-                const bool sample =
-                    !sumw && S->prof_every > 0 && (S->prof_launches++ % S->prof_every) == 0;
-                S->prof_tag_now = j;
-                apply(F.V + o, F.wd, Fs.vs + j, F.Z + o, sample);
-                hipEvent_t e0 = nullptr, e1 = nullptr, g0 = nullptr, g1 = nullptr;
-                if (sample) {
-                    prof_pair(S, RBF_PROF_SPMV, e0, e1);
-                    prof_pair(S, RBF_PROF_GS, g0, g1);
-                }
-                if (P.k == 28 && nb <= kFewBlocks)
-                    hipExtLaunchKernelGGL((k_fg_av2_few<T>), grid, dim3(kAvThreads), 0, st, e0, e1, 0,
-                                          P, A.u1, A.vscale, F, j);
-                else if (P.k == 28)
-                    hipExtLaunchKernelGGL((k_fg_av2<T>), grid, dim3(kAvThreads), 0, st, e0, e1, 0, P,
-                                          A.u1, A.vscale, F, j);
-                else
-                    hipExtLaunchKernelGGL((k_fg_av<0, T>), grid, block, 0, st, e0, e1, 0, P, A.u1,
-                                          A.vscale, F, j);
-                const bool sum = !kFgReorth && nb <= kSumBlocks;
-                if (!sum)
-                    hipLaunchKernelGGL(k_fg_reduce<true>, dim3(j + 1), red, 0, st, Fs.part, nb, j + 1,
-                                       Fs.h1, Fs.flag);
-                const dim3 b2(2 * kThreads);
-                if constexpr (kFgReorth) {
-                    hipExtLaunchKernelGGL((k_fg_gs<T, 1, false>), grid, b2, 0, st, g0, g1, 0, F,
-                                          Fs.h1, P.dinv, m, j);
-                    hipLaunchKernelGGL(k_fg_reduce<true>, dim3(j + 1), red, 0, st, Fs.part, nb, j + 1,
-                                       Fs.h2, Fs.flag);
-                    hipLaunchKernelGGL((k_fg_gs<T, 2, false>), grid, b2, 0, st, F, Fs.h2, P.dinv, m, j);
-                } else if (sum) {
-                    hipExtLaunchKernelGGL((k_fg_gs<T, 2, true>), grid, b2, 0, st, g0, g1, 0, F, Fs.h1,
-                                          P.dinv, m, j);
-                } else {
-                    hipExtLaunchKernelGGL((k_fg_gs<T, 2, false>), grid, b2, 0, st, g0, g1, 0, F, Fs.h1,
-                                          P.dinv, m, j);
-                }
-                hipLaunchKernelGGL(k_fg_tail, one, red, 0, st, Fs, j, mr, nb);
-                S->prof_tag_now = -1;
+        hipLaunchKernelGGL(k_fg_start, one, one, 0, st, Fs, Fs.h1, tol, mixed,
+                           cycles == 0 ? 1 : 0, ++S->pub_seq);
+        RBF_CHECK_LAUNCH();
+        seq = S->pub_seq;
+        f = done = 0;
+        // A cycle after the first starts with the test of the solution: what it
+        // finds is waited for.
+        if (cycles > 0) {
+            if ((rc = word(0)) != RBF_OK) return rc;
+            std::memcpy(&beta, Fs.pub + 2, sizeof(beta));
+            if (f == 0 && total < maxit && accept > 1.0 && beta > 0.5 * beta_prev) {
+                std::memcpy(&bb, Fs.pub + 1, sizeof(bb));
+                if (beta <= accept * tol * std::sqrt(bb)) f = 1;
             }
+            if (f != 0 || total >= maxit) break;
+        }
+        double last = 0.0, rate = 0.0;  // ratio at step last_at, its factor per step
+        int last_at = -1;
+        for (int j = 0;;) {
+            if ((rc = word(j == 0 ? -1 : 0)) != RBF_OK) return rc;
+            if (f != 0) break;
+            if (done > last_at && ratio > 0.0) {
+                if (last_at >= 0) rate = std::pow(ratio / last, 1.0 / (done - last_at));
+                last = ratio;
+                last_at = done;
+            }
+            // Steps the target is away at this rate (a little under: a step
+            // launched late costs less than one launched in vain).
+            int ahead = 2;
+            if (rate > 0.0 && rate < 1.0)
+                ahead = (int)std::fmin(
+                    4.0, std::fmax(1.0, std::ceil(std::log(1.2 / ratio) / std::log(rate))));
+            if (j >= std::min(mr, done + ahead)) {
+                if ((rc = word(done + 1)) != RBF_OK) return rc;
+                continue;
+            }
+            const int64_t o = (int64_t)j * m;
+            const bool sample =
+                !sumw && S->prof_every > 0 && (S->prof_launches++ % S->prof_every) == 0;
+            S->prof_tag_now = j;
+            apply(F.V + o, F.wd, Fs.vs + j, F.Z + o, sample);
+            hipEvent_t e0 = nullptr, e1 = nullptr, g0 = nullptr, g1 = nullptr;
+            if (sample) {
+                prof_pair(S, RBF_PROF_SPMV, e0, e1);
+                prof_pair(S, RBF_PROF_GS, g0, g1);
+            }
+            if (P.k == 28 && nb <= kFewBlocks)
+                hipExtLaunchKernelGGL((k_fg_av2_few<T>), grid, dim3(kAvThreads), 0, st, e0, e1, 0,
+                                      P, A.u1, A.vscale, F, j);
+            else if (P.k == 28)
+                hipExtLaunchKernelGGL((k_fg_av2<T>), grid, dim3(kAvThreads), 0, st, e0, e1, 0, P,
+                                      A.u1, A.vscale, F, j);
+            else
+                hipExtLaunchKernelGGL((k_fg_av<0, T>), grid, block, 0, st, e0, e1, 0, P, A.u1,
+                                      A.vscale, F, j);
+            const bool sum = !kFgReorth && nb <= kSumBlocks;
+            if (!sum)
+                hipLaunchKernelGGL(k_fg_reduce<true>, dim3(j + 1), red, 0, st, Fs.part, nb, j + 1,
+                                   Fs.h1, Fs.flag);
+            const dim3 b2(2 * kThreads);
+            if constexpr (kFgReorth) {
+                hipExtLaunchKernelGGL((k_fg_gs<T, 1, false>), grid, b2, 0, st, g0, g1, 0, F,
+                                      Fs.h1, P.dinv, m, j);
+                hipLaunchKernelGGL(k_fg_reduce<true>, dim3(j + 1), red, 0, st, Fs.part, nb, j + 1,
+                                   Fs.h2, Fs.flag);
+                hipLaunchKernelGGL((k_fg_gs<T, 2, false>), grid, b2, 0, st, F, Fs.h2, P.dinv, m, j);
+            } else if (sum) {
+                hipExtLaunchKernelGGL((k_fg_gs<T, 2, true>), grid, b2, 0, st, g0, g1, 0, F, Fs.h1,
+                                      P.dinv, m, j);
+            } else {
+                hipExtLaunchKernelGGL((k_fg_gs<T, 2, false>), grid, b2, 0, st, g0, g1, 0, F, Fs.h1,
+                                      P.dinv, m, j);
+            }
+            hipLaunchKernelGGL(k_fg_tail, one, red, 0, st, Fs, j, mr, nb, seq);
+            S->prof_tag_now = -1;
             RBF_CHECK_LAUNCH();
-            if ((rc = status()) != RBF_OK) return rc;
-            f = S->hflag[0];
-            if (accept > 1.0) {
-                const double *hc = reinterpret_cast<const double *>(S->hflag + 2);
-                if (f >= 0 && f != 1 && hc[4] > 0.5 * beta_prev &&
-                    hc[4] <= accept * tol * std::sqrt(hc[3])) {
-                    f = 1;
-                    break;
-                }
-                beta_prev = (f != 0 || j >= mr) ? hc[4] : beta_prev;
-            }
-            if (f != 0 || j >= mr) break;
-            // Next batch from the residual's rate over the last four steps.
-            const double *hs = reinterpret_cast<const double *>(S->hflag + 2);
-            batch = 4;
-            if (hs[0] > 0.0 && hs[1] > hs[0] && hs[2] > 0.0) {
-                const double rate = std::log(hs[0] / hs[1]) / 4.0;
-                const double need = std::log(hs[2] / hs[0]) / rate;
-                if (std::isfinite(need)) batch = std::max(1, std::min(12, (int)std::ceil(need)));
-            }
+            ++j;
         }
-        const int nstep = S->hflag[1];
+        const int nstep = done;
         total += nstep;
-        if (f == 1 || f == -1) break;
-        if (nstep <= 0) {  // no step was taken: nothing would change
-            f = 0;
-            break;
+        if (S->prof_every > 0) {
+            RBF_HIP(hipStreamSynchronize(st));
+            prof_flush(S, nstep);
         }
+        if (f == 1 || f == -1) break;
+        std::memcpy(&beta_prev, Fs.pub + 2, sizeof(beta_prev));
         hipLaunchKernelGGL(k_fg_solve, one, red, 0, st, Fs, nstep, mr);
         hipLaunchKernelGGL((k_fg_x<T>), grid, block, 0, st, F.Z, Fs.y, nstep, m, x);
         ++cycles;
     }
-    const double *hs = reinterpret_cast<const double *>(S->hflag + 2);
-    const double bb = hs[3], beta = hs[4];
+    std::memcpy(&bb, Fs.pub + 1, sizeof(bb));
+    std::memcpy(&beta, Fs.pub + 2, sizeof(beta));
     if (stats) {
         stats->iterations = total;
         stats->converged = (f == 1);
@@ -2989,24 +3069,15 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
 
 rbf_status aux_solve(rbf_solver *S, EllM A, const double *b, double *x, rbf_solve_stats *stats) {
     A.vscale *= kAuxBorder;  // as S->lat.c
-    // Expected steps of the first cycle: the last solve's count (warm starts
-    // of consecutive steps need about as many).
-    const int expect = S->p_nhist ? S->p_hist[(S->p_pos + 2) % 3] : 0;
     auto run = [&](auto &P, auto &F) {
         S->lat.flag = F.s.flag;  // the transform stages exit with the Krylov flag
-        return fgmres_run(S, P, F, A, nullptr, b, x, S->rtol_p, S->maxit_p, expect, 1.0,
+        return fgmres_run(S, P, F, A, nullptr, b, x, S->rtol_p, S->maxit_p, 1.0,
                           S->last_iters_p, stats,
                           [&](const auto *y, const auto *yd, const double *ys, auto *z, bool sample) {
                               aux_apply(S, P, F, y, yd, ys, z, sample);
                           });
     };
-    const rbf_status rc = S->mixed ? run(S->ax32, S->fg32) : run(S->ax64, S->fg64);
-    if (rc == RBF_OK) {
-        S->p_hist[S->p_pos] = S->last_iters_p;
-        S->p_pos = (S->p_pos + 1) % 3;
-        S->p_nhist = std::min(3, S->p_nhist + 1);
-    }
-    return rc;
+    return S->mixed ? run(S->ax32, S->fg32) : run(S->ax64, S->fg64);
 }
 
 template <class T>
@@ -3025,22 +3096,20 @@ rbf_status alloc_fg(rbf_solver *S, FgDev<T> &F, int64_t M) {
     ALLOC(s.h1, mr + 1);
     ALLOC(s.h2, mr + 1);
     RBF_HIP(hipMemsetAsync(s.h2, 0, (mr + 1) * sizeof(double), S->st));
-    ALLOC(s.hn2, 1);
     ALLOC(s.H, (int64_t)(mr + 1) * mr);
     ALLOC(s.cs, mr);
     ALLOC(s.sn, mr);
     ALLOC(s.g, mr + 1);
     ALLOC(s.y, mr);
-    ALLOC(s.resh, mr + 1);
     ALLOC(s.partZ, kMaxBlocks);
     ALLOC(s.partO, kMaxBlocks);
     ALLOC(s.one, 1);
     const double unit = 1.0;
     RBF_HIP(hipMemcpyAsync(s.one, &unit, sizeof(double), hipMemcpyHostToDevice, S->st));
-    ALLOC(s.flag, 16);  // flag, step, 5 status doubles (8-byte aligned at +2 ints)
-    s.step = s.flag + 1;
-    s.stat = reinterpret_cast<double *>(s.flag + 2);
-    RBF_HIP(hipMemsetAsync(s.flag, 0, 16 * sizeof(int), S->st));
+    ALLOC(s.flag, 1);
+    ALLOC(s.stat, 2);
+    s.pub = S->pub;
+    RBF_HIP(hipMemsetAsync(s.flag, 0, sizeof(int), S->st));
     return RBF_OK;
 }
 
@@ -3482,10 +3551,13 @@ rbf_status create_impl(rbf_solver *S, const rbf_grid *g, const rbf_ops *o, const
         ALLOC(J.part, 2 * 2 * kHR * kMaxBlocks);
         ALLOC(J.bb, kHR);
         ALLOC(J.flag, 2);
-        ALLOC(H.iters, kHR);
     }
     if ((rc = alloc_krylov(S, S->kp, 1, M, S->maxit_p)) != RBF_OK) return rc;
     RBF_HIP(hipHostMalloc((void **)&S->hflag, 64 * sizeof(int), hipHostMallocDefault));
+    RBF_HIP(hipHostMalloc((void **)&S->pub, (kPubStat + 2 * kHR * kMaxBlocks) * sizeof(uint64_t),
+                          hipHostMallocCoherent));
+    std::memset(S->pub, 0, (kPubStat + 2 * kHR * kMaxBlocks) * sizeof(uint64_t));
+    S->hk.pub = S->jk.pub = S->hm.pub = S->pub + kPubVisc;
     RBF_HIP(hipHostMalloc((void **)&S->hred, (2 * kMaxNR * kMaxBlocks + kMaxNR) * sizeof(double),
                           hipHostMallocDefault));
 
@@ -3658,7 +3730,7 @@ rbf_status step_once(rbf_solver *S, bool first, rbf_step_stats *stats) {
                                       S->u_conv});
         });
     RBF_CHECK_LAUNCH();
-    rbf_solve_stats hs[2];
+    rbf_solve_stats hs[2] = {};
     EllM H{S->idx_vv, S->h_w, S->h_dinv, N, k, nullptr, 0.0};
     rbf_status rc = S->h_mixed
                         ? hmixed(S, H, S->hrhs, S->uvss, S->rtol_h, S->maxit_h, S->last_iters_h, hs)
@@ -3671,6 +3743,7 @@ rbf_status step_once(rbf_solver *S, bool first, rbf_step_stats *stats) {
         stats->helmholtz_iters += hs[0].iterations + hs[1].iterations;
     }
     if (rc != RBF_OK) return rc;
+    // (The residuals of hs follow below, once the stream is past them.)
     // Stage 3: divergence, Poisson (warm start from p~_j), pressure, correction.
     launch_kt(k, [&](auto KT) {
         hipLaunchKernelGGL((k_divergence<decltype(KT)::value>), gM, blk, 0, st, M, k, S->idx_pv, S->pv_dx,
@@ -3702,7 +3775,11 @@ rbf_status step_once(rbf_solver *S, bool first, rbf_step_stats *stats) {
         hipLaunchKernelGGL(k_sub_mean, dim3(nbm), dim3(kThreads), 0, st, M, S->kp.partX, nbm,
                            S->p_warm, S->ptn);
     }
+    if (rc != RBF_OK) (void)hipStreamSynchronize(st);
+    visc_residuals(S, hs);
     if (stats) {
+        stats->last_helmholtz_u.rel_residual = hs[0].rel_residual;
+        stats->last_helmholtz_v.rel_residual = hs[1].rel_residual;
         stats->last_poisson = ps;
         stats->poisson_iters += ps.iterations;
     }
@@ -4224,7 +4301,7 @@ extern "C" rbf_status rbf_adjoint_step(rbf_solver *S, const rbf_state *fwd, rbf_
         A.lat.flag = A.fg.s.flag;
         RBF_HIP(hipMemsetAsync(w, 0, mb, st));
         rc = fgmres_run(S, T, A.fg, AT, S->p_u1, y, w, 0.1 * tol_p,
-                        std::max(100, std::min(S->maxit_p, 600)), A.last_p, 100.0, A.last_p, nullptr,
+                        std::max(100, std::min(S->maxit_p, 600)), 100.0, A.last_p, nullptr,
                         [&](const double *v, const double *vd, const double *vs, double *z, bool) {
                             adj_pre_apply(S, v, vd, vs, z);
                         });
@@ -4664,5 +4741,6 @@ extern "C" void rbf_solver_destroy(rbf_solver *S) {
     for (void *p : S->allocs) hipFree(p);
     if (S->hflag) hipHostFree(S->hflag);
     if (S->hred) hipHostFree(S->hred);
+    if (S->pub) hipHostFree(S->pub);
     delete S;
 }

@@ -29,6 +29,7 @@ struct HMix {
     float2 *d[2];         // [N] FP32 corrections, by sweep parity
     double *part;         // [2 parities][4][kMaxBlocks]: ||r_c||^2, ||b_c||^2
     int *flag;            // flag (0 running, 1 accepted, -1 non-finite), accepted index
+    uint64_t *pub;        // pinned host memory, an h_word
 };
 
 __global__ void k_hm_clear(int *flag) {
@@ -86,7 +87,8 @@ __global__ void __launch_bounds__(kThreads) k_hm_res(EllM A, const double *__res
 // all stop when x_i passes, or when a partial is not finite.  LAST: the
 // correction is added to the FP64 iterate instead of being stored.
 template <int KT, bool TEST, bool LAST>
-__global__ void __launch_bounds__(kThreads) k_hm_sweep(HMix X, int i, int s, double tol2, int nbres) {
+__global__ void __launch_bounds__(kThreads) k_hm_sweep(HMix X, int i, int s, double tol2, int nbres,
+                                                       uint32_t seq) {
     if constexpr (TEST) {
         double q[2 * kHR] = {};
         const double *pp = X.part + (int64_t)(i & 1) * 2 * kHR * kMaxBlocks;
@@ -102,13 +104,15 @@ __global__ void __launch_bounds__(kThreads) k_hm_sweep(HMix X, int i, int s, dou
             bad = bad || !isfinite(q[c]) || !isfinite(q[kHR + c]);
             conv = conv && (q[c] <= tol2 * fmax(q[kHR + c], 1e-300) || q[c] == 0.0);
         }
-        if (bad || conv) {
-            if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            const int flag = bad ? -1 : conv ? 1 : 0;
+            if (flag != 0) {
                 X.flag[1] = i;
-                X.flag[0] = bad ? -1 : 1;
+                X.flag[0] = flag;
             }
-            return;
+            rbf::publish(X.pub, h_word(seq, i, flag));
         }
+        if (bad || conv) return;
     } else {
         if (X.flag[0] != 0) return;
     }
