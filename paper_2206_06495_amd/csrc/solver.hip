@@ -3268,37 +3268,31 @@ rbf_status setup_aux_pc(rbf_solver *S, const rbf_grid *g, int mode) {
     // their solves fail.
     {
         struct Scratch {
-            double *x = nullptr, *y = nullptr, *part = nullptr;
-            ~Scratch() {
-                (void)hipFree(x);
-                (void)hipFree(y);
-                (void)hipFree(part);
-            }
+            double *x = nullptr;
+            ~Scratch() { (void)hipFree(x); }
         } P;
-        RBF_HIP(hipMalloc(&P.x, M * sizeof(double)));
-        RBF_HIP(hipMalloc(&P.y, M * sizeof(double)));
-        RBF_HIP(hipMalloc(&P.part, kMaxBlocks * sizeof(double)));
+        RBF_HIP(hipMalloc(&P.x, (2 * M + 2 * kMaxBlocks) * sizeof(double)));
+        double *const xs[2] = {P.x, P.x + M};
+        double *const parts[2] = {P.x + 2 * M, P.x + 2 * M + kMaxBlocks};
         const int nbp = nblocks_rows(M);
         std::vector<double> hp(nbp);
-        hipLaunchKernelGGL(k_aux_power_start, dim3(rbf::blocks_for(M, 256)), dim3(256), 0, st, M, P.x);
-        double scale = 1.0 / std::sqrt((double)M / 3.0), nu = 0.0;
-        for (int it = 0; it < 80; ++it) {
-            hipLaunchKernelGGL((k_aux_power<double>), dim3(nbp), dim3(kThreads), 0, st, S->ax64, P.x,
-                               scale, P.y, P.part);
-            RBF_CHECK_LAUNCH();
-            RBF_HIP(hipMemcpyAsync(hp.data(), P.part, nbp * sizeof(double), hipMemcpyDeviceToHost, st));
-            RBF_HIP(hipStreamSynchronize(st));
-            double ss = 0.0;
-            for (double v : hp) ss += v;
-            const double nrm = std::sqrt(ss);
-            if (!(nrm > 0.0) || !std::isfinite(nrm)) {
-                nu = 0.0;
-                break;
-            }
-            nu = nrm;  // ||W A_s x|| with ||x|| = 1 from the second step on
-            scale = 1.0 / nrm;
-            std::swap(P.x, P.y);
-        }
+        hipLaunchKernelGGL(k_aux_power_start, dim3(rbf::blocks_for(M, 256)), dim3(256), 0, st, M, xs[0]);
+        constexpr int kSteps = 80;
+        for (int it = 0; it < kSteps; ++it)
+            launch_kt(S->k, [&](auto KT) {
+                hipLaunchKernelGGL((k_aux_power<decltype(KT)::value, double>), dim3(nbp),
+                                   dim3(kThreads), 0, st, S->ax64, xs[it & 1],
+                                   it ? parts[(it & 1) ^ 1] : nullptr, 1.0 / std::sqrt((double)M / 3.0),
+                                   xs[(it & 1) ^ 1], parts[it & 1]);
+            });
+        RBF_CHECK_LAUNCH();
+        RBF_HIP(hipMemcpyAsync(hp.data(), parts[(kSteps - 1) & 1], nbp * sizeof(double),
+                               hipMemcpyDeviceToHost, st));
+        RBF_HIP(hipStreamSynchronize(st));
+        double ss = 0.0;
+        for (double v : hp) ss += v;
+        double nu = std::sqrt(ss);  // ||W A_s x|| with ||x|| = 1
+        if (!(nu > 0.0) || !std::isfinite(nu)) nu = 0.0;
         const double nus = 1.05 * nu;
         double w2 = (nus > 1.0) ? 0.85 / (nus - 1.0) : 1.6;
         S->ax64.w2 = (nu > 0.0) ? std::min(1.6, std::max(1.0, w2)) : 1.0;
