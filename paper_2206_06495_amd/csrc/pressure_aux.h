@@ -156,10 +156,10 @@ constexpr int kRowsPerBlock2 = kThreads / 2;
 
 // This lane's row in the two-lanes-per-row layout (one row pair per thread,
 // no grid-stride loop) and the half of the stencil it takes.
-__device__ __forceinline__ int64_t row2_of(int &half) {
+__device__ __forceinline__ int64_t row2_of(int &half, uint32_t nb) {
     const int lane = threadIdx.x & 63;
     half = lane >> 5;
-    return (int64_t)rbf::xcd_block(blockIdx.x, gridDim.x) * kRowsPerBlock2 +
+    return (int64_t)rbf::xcd_block(blockIdx.x, nb) * kRowsPerBlock2 +
            (threadIdx.x >> 6) * 32 + (lane & 31);
 }
 
@@ -195,32 +195,105 @@ inline dim3 aux_grid(int64_t m, int nb) {
     return (KT > 0) ? dim3(rbf::blocks_for(m, kRowsPerBlock2)) : dim3(nb);
 }
 
-// Pre-smoothing sweep from x = W y: x1 = sc (yd + W (y - A_s yd)), y
-// scaled by sc = *ys, yd = W y unscaled (one gathered value per neighbour).
+constexpr int kNormRow = kFgMax + 1;  // row of FgScal::part that takes ||w||^2
+
+// Arnoldi step j, one workgroup: Hessenberg column j = h1 + h2 with
+// H(j+1, j) = ||w||, previous rotations applied, a new rotation, the
+// residual estimate |g_{j+1}| and the status (4: the cycle's target met or
+// an exact breakdown; 3: the cycle is full; -1: non-finite).
+// ||w||^2 is reduced here from the block partials of k_fg_gs<2> (row kNormRow of
+// part, nb blocks).  One wave per quarter of the partials, every load in one
+// round trip; the column and the rotations are held one entry per lane of wave
+// 0, which runs the recurrence on values read by lane.
+__device__ __forceinline__ void fg_tail(const FgScal &F, int j, int mr, int nb, uint32_t seq) {
+    const int t = threadIdx.x, lane = t & 63;
+    const double *pn = F.part + (int64_t)kNormRow * kMaxBlocks;
+    double pv[kMaxBlocks / 256];
+#pragma unroll
+    for (int q = 0; q < kMaxBlocks / 256; ++q) {
+        const int b = t + 256 * q;
+        pv[q] = (b < nb) ? pn[b] : 0.0;
+    }
+    const bool first = t < 64;
+    const double hl = (first && lane <= j) ? F.h1[lane] + F.h2[lane] : 0.0;
+    const double cl = (first && lane < j) ? F.cs[lane] : 0.0;
+    const double sl = (first && lane < j) ? F.sn[lane] : 0.0;
+    const double gj = F.g[j], target = F.stat[0];
+    if (*F.flag != 0) return;
+    double v[1] = {(pv[0] + pv[1]) + (pv[2] + pv[3])};
+    static_assert(kMaxBlocks == 4 * 256, "four partials per thread");
+    __shared__ double lds[4];
+    rbf::block_sum<1>(v, lds);
+    if (!first) return;
+    const double hn = sqrt(v[0]);
+    double a = rbf::readlane_double(hl, 0), col = 0.0;
+    for (int i = 0; i < j; ++i) {
+        const double b = rbf::readlane_double(hl, i + 1), c = rbf::readlane_double(cl, i),
+                     s = rbf::readlane_double(sl, i);
+        if (lane == i) col = c * a + s * b;
+        a = c * b - s * a;
+    }
+    const double den = hypot(a, hn);
+    const double c = (den > 0.0) ? a / den : 1.0, s = (den > 0.0) ? hn / den : 0.0;
+    if (lane == j) col = den;
+    if (lane <= j + 1) F.H[(int64_t)j * (mr + 1) + lane] = (lane <= j) ? col : 0.0;
+    if (lane != 0) return;
+    const double res = fabs(s * gj);
+    F.cs[j] = c;
+    F.sn[j] = s;
+    F.g[j] = c * gj;
+    F.g[j + 1] = -s * gj;
+    F.vs[j + 1] = (hn > 0.0) ? 1.0 / hn : 0.0;
+    const int flag = (!isfinite(res) || !isfinite(den))              ? -1
+                     : (res <= target || hn == 0.0 || den == 0.0) ? 4
+                     : (j + 1 >= mr)                              ? 3
+                                                                  : 0;
+    if (flag != 0) F.flag[0] = flag;
+    rbf::publish(F.pub, fg_word(seq, res / target, j + 1, flag));
+}
+
+__global__ void __launch_bounds__(256) k_fg_tail(FgScal F, int j, int mr, int nb, uint32_t seq) {
+    fg_tail(F, j, mr, nb, seq);
+}
+
+// The tail of an Arnoldi step as work for the next kernel's last block (j < 0: none).
+struct FgTail {
+    FgScal F;
+    int j, mr, nb;
+    uint32_t seq;
+};
+
+// Pre-smoothing sweep from x = W y: x1 = yd + W (y - A_s yd) with yd = W y (one
+// gathered value per neighbour), unscaled: the scale of y may still be in the
+// making, by the last block's tail of the step before.  As a launch of its own
+// the tail, one workgroup, takes 3.4 us of a step's 57 at h = 1/40.
 template <int KT, class T>
 __global__ void __launch_bounds__(kThreads) k_aux_pre(AuxOps<T> P, const T *__restrict__ y,
-                                                       const T *__restrict__ yd,
-                                                       const double *ys, T *__restrict__ x1,
-                                                       const int *flag) {
+                                                       const T *__restrict__ yd, T *__restrict__ x1,
+                                                       const int *flag, FgTail tail) {
     if constexpr (KT > 0) {
+        const uint32_t nb = gridDim.x - (tail.j >= 0 ? 1 : 0);
+        if (blockIdx.x == nb) {
+            fg_tail(tail.F, tail.j, tail.mr, tail.nb, tail.seq);
+            return;
+        }
         int half;
-        const int64_t r = row2_of(half);
+        const int64_t r = row2_of(half, nb);
         const int64_t rr = (r < P.m) ? r : P.m - 1;
         HalfRow<KT, T> row;
         row.load(P, rr, half);
-        const T sc = (T)*ys, yr = y[rr], ydr = yd[rr], di = P.dinv[rr];
+        const T yr = y[rr], ydr = yd[rr], di = P.dinv[rr];
         if (*flag != 0) return;
         const T ax = row.sum([&](int j) { return yd[j]; });
-        if (half == 0 && r < P.m) x1[r] = sc * (ydr + (T)P.w2 * di * (yr - ax));
+        if (half == 0 && r < P.m) x1[r] = ydr + (T)P.w2 * di * (yr - ax);
     } else {
         if (*flag != 0) return;
-        const T sc = (T)*ys;
         for (int64_t it = 0;; ++it) {
             const int64_t r = row_of(it);
             if (r - threadIdx.x >= P.m) break;
             if (r < P.m) {
                 const T ax = aux_row<KT, 1>(P, r, [&](int j) { return yd[j]; });
-                x1[r] = sc * (yd[r] + (T)P.w2 * P.dinv[r] * (y[r] - ax));
+                x1[r] = yd[r] + (T)P.w2 * P.dinv[r] * (y[r] - ax);
             }
         }
     }
@@ -235,7 +308,7 @@ __global__ void __launch_bounds__(kThreads) k_aux_res(AuxOps<T> P, const T *__re
                                                        const int *flag) {
     if constexpr (KT > 0) {
         int half;
-        const int64_t r = row2_of(half);
+        const int64_t r = row2_of(half, gridDim.x);
         const int64_t rr = (r < P.m) ? r : P.m - 1;
         HalfRow<KT, T> row;
         row.load(P, rr, half);
@@ -738,7 +811,6 @@ k_fg_av2_few(AuxOps<T> P, const double *__restrict__ u1, double vscale, FgDev<T>
 // (slot c: i = 2c + h), which serve both the update and, in PASS 1, the
 // dots with the updated w.
 constexpr int kSumBlocks = 64;         // SUM: largest grid
-constexpr int kNormRow = kFgMax + 1;   // row of part that takes ||w||^2
 template <class T, int PASS, bool SUM>
 __global__ void __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_fg_gs(FgDev<T> F, const double *h,
                                                          const T *__restrict__ dinv, int64_t m,
@@ -832,62 +904,6 @@ __global__ void __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_
         rbf::block_sum<1>(nrm, lds);
         if (threadIdx.x == 0) F.s.part[(int64_t)kNormRow * kMaxBlocks + blockIdx.x] = nrm[0];
     }
-}
-
-// Arnoldi step j, one workgroup: Hessenberg column j = h1 + h2 with
-// H(j+1, j) = ||w||, previous rotations applied, a new rotation, the
-// residual estimate |g_{j+1}| and the status (4: the cycle's target met or
-// an exact breakdown; 3: the cycle is full; -1: non-finite).
-// ||w||^2 is reduced here from the block partials of k_fg_gs<2> (row kNormRow of
-// part, nb blocks).  One wave per quarter of the partials, every load in one
-// round trip; the column and the rotations are held one entry per lane of wave
-// 0, which runs the recurrence on values read by lane.
-__global__ void __launch_bounds__(256) k_fg_tail(FgScal F, int j, int mr, int nb,
-                                                  uint32_t seq) {
-    const int t = threadIdx.x, lane = t & 63;
-    const double *pn = F.part + (int64_t)kNormRow * kMaxBlocks;
-    double pv[kMaxBlocks / 256];
-#pragma unroll
-    for (int q = 0; q < kMaxBlocks / 256; ++q) {
-        const int b = t + 256 * q;
-        pv[q] = (b < nb) ? pn[b] : 0.0;
-    }
-    const bool first = t < 64;
-    const double hl = (first && lane <= j) ? F.h1[lane] + F.h2[lane] : 0.0;
-    const double cl = (first && lane < j) ? F.cs[lane] : 0.0;
-    const double sl = (first && lane < j) ? F.sn[lane] : 0.0;
-    const double gj = F.g[j], target = F.stat[0];
-    if (*F.flag != 0) return;
-    double v[1] = {(pv[0] + pv[1]) + (pv[2] + pv[3])};
-    static_assert(kMaxBlocks == 4 * 256, "four partials per thread");
-    __shared__ double lds[4];
-    rbf::block_sum<1>(v, lds);
-    if (!first) return;
-    const double hn = sqrt(v[0]);
-    double a = rbf::readlane_double(hl, 0), col = 0.0;
-    for (int i = 0; i < j; ++i) {
-        const double b = rbf::readlane_double(hl, i + 1), c = rbf::readlane_double(cl, i),
-                     s = rbf::readlane_double(sl, i);
-        if (lane == i) col = c * a + s * b;
-        a = c * b - s * a;
-    }
-    const double den = hypot(a, hn);
-    const double c = (den > 0.0) ? a / den : 1.0, s = (den > 0.0) ? hn / den : 0.0;
-    if (lane == j) col = den;
-    if (lane <= j + 1) F.H[(int64_t)j * (mr + 1) + lane] = (lane <= j) ? col : 0.0;
-    if (lane != 0) return;
-    const double res = fabs(s * gj);
-    F.cs[j] = c;
-    F.sn[j] = s;
-    F.g[j] = c * gj;
-    F.g[j + 1] = -s * gj;
-    F.vs[j + 1] = (hn > 0.0) ? 1.0 / hn : 0.0;
-    const int flag = (!isfinite(res) || !isfinite(den))              ? -1
-                     : (res <= target || hn == 0.0 || den == 0.0) ? 4
-                     : (j + 1 >= mr)                              ? 3
-                                                                  : 0;
-    if (flag != 0) F.flag[0] = flag;
-    rbf::publish(F.pub, fg_word(seq, res / target, j + 1, flag));
 }
 
 // End of a cycle of nstep steps, one thread: back substitution H y = g.

@@ -2846,25 +2846,28 @@ rbf_status copy_in(rbf_solver *S, void *dst, const void *src, size_t bytes) {
 // ------------------------------------- auxiliary-lattice pressure path --
 // One application z = B^-1 (ys y) of the two-level preconditioner
 // (pressure_aux.h): smoother, residual, restriction, lattice transform
-// solve, interpolation, smoother.
+// solve, interpolation, smoother.  tail: the Arnoldi step before, whose tail the
+// first kernel also takes (28-entry rows).
+constexpr bool kFuseTail = kAuxSweeps == 2;
 template <class T>
 void aux_apply(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, const T *y, const T *yd,
-               const double *ys, T *z, bool sample = false) {
+               const double *ys, T *z, bool sample = false, FgTail tail = FgTail{{}, -1, 0, 0, 0}) {
     hipStream_t st = S->st;
     const dim3 grid(nblocks_rows(P.m)), block(kThreads);
     const int nq = S->lat.n * S->lat.n;
     // Pre-smoothing: x1 = W y (implicit, yd), further sweeps into F.x1.
     const T *u = yd;
     const double *us = ys;
+    static_assert(kAuxSweeps == 2 || !kFuseTail, "the tail travels with k_aux_pre");
     static_assert(kAuxSweeps == 1 || kAuxSweeps == 2, "one or two smoothing sweeps");
     if constexpr (kAuxSweeps == 2) {
         launch_kt(P.k, [&](auto KT) {
-            hipLaunchKernelGGL((k_aux_pre<decltype(KT)::value, T>),
-                               aux_grid<decltype(KT)::value>(P.m, grid.x), block, 0, st, P, y, yd, ys,
-                               F.x1, F.s.flag);
+            dim3 g = aux_grid<decltype(KT)::value>(P.m, grid.x);
+            if (tail.j >= 0) ++g.x;
+            hipLaunchKernelGGL((k_aux_pre<decltype(KT)::value, T>), g, block, 0, st, P, y, yd, F.x1,
+                               F.s.flag, tail);
         });
         u = F.x1;
-        us = F.s.one;
     }
     launch_kt(P.k, [&](auto KT) {
         hipLaunchKernelGGL((k_aux_res<decltype(KT)::value, T>),
@@ -2909,8 +2912,8 @@ constexpr bool kFgReorth = false;
 // preconditioner (x: guess in, solution out).  Every cycle starts from the
 // FP64 residual; with T = float the cycle is one step of iterative
 // refinement (see pressure_aux.h).  maxit counts Arnoldi steps
-// (preconditioner applications).  apply(y, W y, ys, z, sample): one application
-// of the preconditioner.  sumw: weights of the sum in the border term of x
+// (preconditioner applications).  apply(y, W y, ys, z, sample, tail): one application
+// of the preconditioner (FUSE: which takes the tail of the step before along).  sumw: weights of the sum in the border term of x
 // (null: 1; its launches are not sampled).  accept: a cycle that starts with more
 // than half of the last one's true residual ends the solve as converged if that is
 // within accept times the tolerance (1: off).
@@ -2919,7 +2922,7 @@ constexpr bool kFgReorth = false;
 // steps queued ahead of the device, as many as the residual's rate still asks
 // for: launches after the one that ends a cycle exit at the flag, and about 13 of
 // them are a step (25 us at h = 1/40, where a step takes 60).
-template <class T, class Apply>
+template <bool FUSE, class T, class Apply>
 rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, const double *sumw,
                       const double *b, double *x, double tol, int maxit, double accept,
                       int &last_iters, rbf_solve_stats *stats, Apply apply) {
@@ -2973,6 +2976,13 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
             }
             if (f != 0 || total >= maxit) break;
         }
+        const bool fuse = FUSE && P.k == 28;
+        int tail = -1;  // step whose tail is not launched yet
+        auto take_tail = [&]() {
+            const FgTail t{Fs, tail, mr, nb, seq};
+            tail = -1;
+            return t;
+        };
         double last = 0.0, rate = 0.0;  // ratio at step last_at, its factor per step
         int last_at = -1;
         for (int j = 0;;) {
@@ -2990,6 +3000,11 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
                 ahead = (int)std::fmin(
                     4.0, std::fmax(1.0, std::ceil(std::log(1.2 / ratio) / std::log(rate))));
             if (j >= std::min(mr, done + ahead)) {
+                if (tail == done) {  // no step behind it yet to take it along
+                    const FgTail t = take_tail();
+                    hipLaunchKernelGGL(k_fg_tail, one, red, 0, st, Fs, t.j, mr, nb, seq);
+                    RBF_CHECK_LAUNCH();
+                }
                 if ((rc = word(done + 1)) != RBF_OK) return rc;
                 continue;
             }
@@ -2997,7 +3012,7 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
             const bool sample =
                 !sumw && S->prof_every > 0 && (S->prof_launches++ % S->prof_every) == 0;
             S->prof_tag_now = j;
-            apply(F.V + o, F.wd, Fs.vs + j, F.Z + o, sample);
+            apply(F.V + o, F.wd, Fs.vs + j, F.Z + o, sample, take_tail());
             hipEvent_t e0 = nullptr, e1 = nullptr, g0 = nullptr, g1 = nullptr;
             if (sample) {
                 prof_pair(S, RBF_PROF_SPMV, e0, e1);
@@ -3030,7 +3045,8 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
                 hipExtLaunchKernelGGL((k_fg_gs<T, 2, false>), grid, b2, 0, st, g0, g1, 0, F, Fs.h1,
                                       P.dinv, m, j);
             }
-            hipLaunchKernelGGL(k_fg_tail, one, red, 0, st, Fs, j, mr, nb, seq);
+            if (fuse) tail = j;
+            else hipLaunchKernelGGL(k_fg_tail, one, red, 0, st, Fs, j, mr, nb, seq);
             S->prof_tag_now = -1;
             RBF_CHECK_LAUNCH();
             ++j;
@@ -3071,10 +3087,11 @@ rbf_status aux_solve(rbf_solver *S, EllM A, const double *b, double *x, rbf_solv
     A.vscale *= kAuxBorder;  // as S->lat.c
     auto run = [&](auto &P, auto &F) {
         S->lat.flag = F.s.flag;  // the transform stages exit with the Krylov flag
-        return fgmres_run(S, P, F, A, nullptr, b, x, S->rtol_p, S->maxit_p, 1.0,
+        return fgmres_run<kFuseTail>(S, P, F, A, nullptr, b, x, S->rtol_p, S->maxit_p, 1.0,
                           S->last_iters_p, stats,
-                          [&](const auto *y, const auto *yd, const double *ys, auto *z, bool sample) {
-                              aux_apply(S, P, F, y, yd, ys, z, sample);
+                          [&](const auto *y, const auto *yd, const double *ys, auto *z, bool sample,
+                              const FgTail &tail) {
+                              aux_apply(S, P, F, y, yd, ys, z, sample, tail);
                           });
     };
     return S->mixed ? run(S->ax32, S->fg32) : run(S->ax64, S->fg64);
@@ -4294,9 +4311,10 @@ extern "C" rbf_status rbf_adjoint_step(rbf_solver *S, const rbf_state *fwd, rbf_
         const EllM AT{T.idx, T.w, nullptr, M, T.k, A.ones, c * kAuxBorder};
         A.lat.flag = A.fg.s.flag;
         RBF_HIP(hipMemsetAsync(w, 0, mb, st));
-        rc = fgmres_run(S, T, A.fg, AT, S->p_u1, y, w, 0.1 * tol_p,
+        rc = fgmres_run<false>(S, T, A.fg, AT, S->p_u1, y, w, 0.1 * tol_p,
                         std::max(100, std::min(S->maxit_p, 600)), 100.0, A.last_p, nullptr,
-                        [&](const double *v, const double *vd, const double *vs, double *z, bool) {
+                        [&](const double *v, const double *vd, const double *vs, double *z, bool,
+                            const FgTail &) {
                             adj_pre_apply(S, v, vd, vs, z);
                         });
         solved = rc == RBF_OK;
