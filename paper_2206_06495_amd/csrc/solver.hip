@@ -463,7 +463,7 @@ __global__ void __launch_bounds__(kThreads) k_resid(EllM A, const double *__rest
 // Q^-1 X on the matrix cores (k_pc_gemm, FP64 MFMA); for each x-mode k the
 // y-direction system (T + lam_k I) w = h^2 t is tridiagonal and is solved by
 // one wavefront per mode (k_pc_tri: elimination inside per-lane chunks, then
-// cyclic reduction across the lanes); the product Q W returns to the
+// cyclic reduction across the lanes; k_pc_modes does both up to n = 128); the product Q W returns to the
 // lattice.  Mode k = 0 is
 // singular: its right-hand side loses its mean (recorded: it fixes the
 // constant through the border), the last unknown is fixed and the solution
@@ -813,29 +813,14 @@ __global__ void __launch_bounds__(64 * kGemmWaves) k_pc_gemm(Lat L) {
 // solution is shifted to zero mean.  Writes W row-major and the sum of
 // W o V over the mode into partW[k].
 constexpr int kTriChunk = 8;  // rows per lane: n <= 64 kTriChunk (K <= 513)
-template <class TP>
-__global__ void __launch_bounds__(64) k_pc_tri(Lat L) {
-    __shared__ double sz[64 * kTriChunk];
-    const int n = L.n, k = blockIdx.x, lane = threadIdx.x;
-    const TP *T = static_cast<const TP *>(L.T);
-    // Every global load of the kernel is issued before the flag test, so
-    // that the whole kernel waits on one memory round trip.
-    double tv[kTriChunk], vv[kTriChunk];
-#pragma unroll
-    for (int m = 0; m < kTriChunk; ++m) {
-        const int i = lane + 64 * m;
-        tv[m] = (i < n) ? (double)T[(int64_t)k * n + i] : 0.0;
-        vv[m] = (i < n) ? L.V[(int64_t)k * n + i] : 0.0;
-    }
-    const double lamk = L.lam[k];
-    if (*L.flag != 0) return;
-    double tsum = 0.0;
-#pragma unroll
-    for (int m = 0; m < kTriChunk; ++m) {
-        const int i = lane + 64 * m;
-        if (i < n) sz[i] = tv[m];
-        tsum += tv[m];
-    }
+
+// One wavefront's solve of mode k: sz holds the row of T (this lane's entries are
+// summed in tsum), vv[m] V at entry lane + 64 m.  At most TC rows per lane and 64 NM
+// entries.
+template <class TP, int TC, int NM>
+__device__ __forceinline__ void pc_tri_mode(const Lat &L, int k, int lane, double *sz, double tsum,
+                                            const double (&vv)[NM], double lamk) {
+    const int n = L.n;
     const int size = (k == 0) ? n - 1 : n;
     double shift = 0.0;
     if (k == 0) {  // block-uniform branch
@@ -857,10 +842,10 @@ __global__ void __launch_bounds__(64) k_pc_tri(Lat L) {
     };
     // Downward sweep: row j >= 1 becomes ap_j x_first + x_j + cp_j x_{j+1} = dp_j
     // (row 0 normalised: ap_0 couples to the previous chunk's last unknown).
-    double ap[kTriChunk], cp[kTriChunk], dp[kTriChunk];
+    double ap[TC], cp[TC], dp[TC];
     double fa = 0.0, fc = 0.0, fd = 0.0;  // last row: fa x_first + x_last + fc x_next = fd
 #pragma unroll
-    for (int j = 0; j < kTriChunk; ++j) {
+    for (int j = 0; j < TC; ++j) {
         ap[j] = cp[j] = dp[j] = 0.0;
         if (j < len) {
             double a, b, c, d;
@@ -885,7 +870,7 @@ __global__ void __launch_bounds__(64) k_pc_tri(Lat L) {
     }
     // Upward sweep: rows 1..len-2 become ap_j x_first + x_j + cp_j x_last = dp_j.
 #pragma unroll
-    for (int j = kTriChunk - 3; j >= 1; --j) {
+    for (int j = TC - 3; j >= 1; --j) {
         if (j <= len - 3) {
             ap[j] -= cp[j] * ap[j + 1];
             dp[j] -= cp[j] * dp[j + 1];
@@ -915,7 +900,7 @@ __global__ void __launch_bounds__(64) k_pc_tri(Lat L) {
         C = -ec * fc;
         D = ed - em * fd_m - ec * fd;
     }
-    for (int st = 1; st < 64; st <<= 1) {
+    for (int st = 1; st < nch; st <<= 1) {
         const bool lo = lane >= st, hi = lane + st < 64;
         const int sl = lo ? lane - st : lane, sh = hi ? lane + st : lane;
         const double am = __shfl(A, sl, 64), bm = __shfl(B, sl, 64), cm = __shfl(C, sl, 64),
@@ -937,7 +922,7 @@ __global__ void __launch_bounds__(64) k_pc_tri(Lat L) {
     __syncthreads();
     if (k == 0 && lane == 0) sz[n - 1] = 0.0;  // the dropped last unknown of mode 0
 #pragma unroll
-    for (int j = 0; j < kTriChunk; ++j) {
+    for (int j = 0; j < TC; ++j) {
         if (j < len) {
             const double z = (j == 0) ? x0 : (j == len - 1) ? xl : dp[j] - ap[j] * x0 - cp[j] * xl;
             sz[r0 + j] = z;
@@ -952,7 +937,7 @@ __global__ void __launch_bounds__(64) k_pc_tri(Lat L) {
     }
     double acc = 0.0;
 #pragma unroll
-    for (int m = 0; m < kTriChunk; ++m) {
+    for (int m = 0; m < NM; ++m) {
         const int i = lane + 64 * m;
         if (i < n) {
             const double z = sz[i] - zmean;
@@ -962,6 +947,91 @@ __global__ void __launch_bounds__(64) k_pc_tri(Lat L) {
     }
     acc = rbf::wave_sum(acc);
     if (lane == 0) L.partW[k] = acc;
+}
+
+template <class TP>
+__global__ void __launch_bounds__(64) k_pc_tri(Lat L) {
+    __shared__ double sz[64 * kTriChunk];
+    const int n = L.n, k = blockIdx.x, lane = threadIdx.x;
+    const TP *T = static_cast<const TP *>(L.T);
+    // Every global load of the kernel is issued before the flag test, so
+    // that the whole kernel waits on one memory round trip.
+    double tv[kTriChunk], vv[kTriChunk];
+#pragma unroll
+    for (int m = 0; m < kTriChunk; ++m) {
+        const int i = lane + 64 * m;
+        tv[m] = (i < n) ? (double)T[(int64_t)k * n + i] : 0.0;
+        vv[m] = (i < n) ? L.V[(int64_t)k * n + i] : 0.0;
+    }
+    const double lamk = L.lam[k];
+    if (*L.flag != 0) return;
+    double tsum = 0.0;
+#pragma unroll
+    for (int m = 0; m < kTriChunk; ++m) {
+        const int i = lane + 64 * m;
+        if (i < n) sz[i] = tv[m];
+        tsum += tv[m];
+    }
+    pc_tri_mode<TP, kTriChunk, kTriChunk>(L, k, lane, sz, tsum, vv, lamk);
+}
+
+// k_pc_gemm<0> and k_pc_tri in one launch for lattices of n <= 64 NB, NB <= 2: the
+// workgroup of mode k makes its row of T itself, each of kModeWaves waves from
+// every kModeWaves-th row of X (the whole of X, 80 KB at n = 100, is read by
+// every workgroup, from L2), and wave 0 solves it.  At these sizes a launch is
+// latency: 3.5 us for the product and 5.1 for the solves at n = 41, 5.0 for this; 3.8
+// and 5.2 at n = 101, 6.5 for this.  Beyond n = 128 the loads no longer fit the
+// registers at once and the product is worth the matrix cores.
+constexpr int kModeWaves = 8;
+constexpr int kModeMax = 128;
+template <class TP, int NB>
+__global__ void __launch_bounds__(64 * kModeWaves) k_pc_modes(Lat L) {
+    constexpr int AM = 64 * NB / kModeWaves;  // rows of X per wave
+    __shared__ double sz[64 * NB], part[kModeWaves][64 * NB];
+    const int n = L.n, k = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const TP *X = static_cast<const TP *>(L.X);
+    TP xv[AM][NB];
+#pragma unroll
+    for (int i = 0; i < AM; ++i) {
+        const int a = wv + kModeWaves * i;
+#pragma unroll
+        for (int c = 0; c < NB; ++c) {
+            const int b = lane + 64 * c;
+            xv[i][c] = (a < n && b < n) ? X[(int64_t)a * n + b] : TP(0);
+        }
+    }
+    const int al = wv + kModeWaves * lane;
+    const double q =
+        (lane < AM && al < n) ? (double)static_cast<const TP *>(L.Qi)[k + (int64_t)al * n] : 0.0;
+    double vv[NB];
+#pragma unroll
+    for (int c = 0; c < NB; ++c) {
+        const int b = lane + 64 * c;
+        vv[c] = (wv == 0 && b < n) ? L.V[(int64_t)k * n + b] : 0.0;
+    }
+    const double lamk = L.lam[k];
+    if (*L.flag != 0) return;
+    double acc[NB] = {};
+#pragma unroll
+    for (int i = 0; i < AM; ++i) {
+        const double qi = rbf::readlane_double(q, i);
+#pragma unroll
+        for (int c = 0; c < NB; ++c) acc[c] = fma(qi, (double)xv[i][c], acc[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < NB; ++c) part[wv][lane + 64 * c] = acc[c];
+    __syncthreads();
+    if (wv != 0) return;
+    double tsum = 0.0;
+#pragma unroll
+    for (int c = 0; c < NB; ++c) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < kModeWaves; ++w) t += part[w][lane + 64 * c];
+        sz[lane + 64 * c] = t;
+        tsum += t;
+    }
+    pc_tri_mode<TP, 3, NB>(L, k, lane, sz, tsum, vv, lamk);
 }
 
 // Lattice value of L5^-1 at node (i, j), before the constant shift (Z in X).
@@ -2219,9 +2289,15 @@ rbf_status pc_apply(rbf_solver *S, const Lat &L, bool sample = false) {
     const bool one = (steps + kGemmWaves - 1) / kGemmWaves <= kGemmChunk;
     auto run = [&](auto tp) {
         using TP = decltype(tp);
-        if (one) hipExtLaunchKernelGGL((k_pc_gemm<0, true, TP>), g, b, 0, S->st, e0, e1, 0, L);
-        else hipExtLaunchKernelGGL((k_pc_gemm<0, false, TP>), g, b, 0, S->st, e0, e1, 0, L);
-        hipLaunchKernelGGL(k_pc_tri<TP>, gt, bt, 0, S->st, L);
+        if (L.n <= kModeMax) {
+            const dim3 bm(64 * kModeWaves);
+            if (L.n <= 64) hipExtLaunchKernelGGL((k_pc_modes<TP, 1>), gt, bm, 0, S->st, e0, e1, 0, L);
+            else hipExtLaunchKernelGGL((k_pc_modes<TP, 2>), gt, bm, 0, S->st, e0, e1, 0, L);
+        } else {
+            if (one) hipExtLaunchKernelGGL((k_pc_gemm<0, true, TP>), g, b, 0, S->st, e0, e1, 0, L);
+            else hipExtLaunchKernelGGL((k_pc_gemm<0, false, TP>), g, b, 0, S->st, e0, e1, 0, L);
+            hipLaunchKernelGGL(k_pc_tri<TP>, gt, bt, 0, S->st, L);
+        }
         if (one) hipLaunchKernelGGL((k_pc_gemm<1, true, TP>), g, b, 0, S->st, L);
         else hipLaunchKernelGGL((k_pc_gemm<1, false, TP>), g, b, 0, S->st, L);
     };
