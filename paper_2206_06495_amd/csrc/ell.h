@@ -49,17 +49,37 @@ __device__ __forceinline__ void ell_row(const int *__restrict__ idx, const doubl
             }
         }
     } else {
-#pragma unroll 4
-        for (int s = 0; s < k; ++s) {
-            const int j = ld_stream(idx + (int64_t)s * rows + r);
+        // GC slots at a time with their loads in flight together, then the rest.
+        constexpr int GC = (NW * Gather::NV <= 2) ? 8 : 4;
+        auto take = [&](int j, const double(&ws)[NW]) {
             double v[Gather::NV];
             g(j, v);
 #pragma unroll
-            for (int o = 0; o < NW; ++o) {
-                const double ws = ld_stream(w[o] + (int64_t)s * rows + r);
+            for (int o = 0; o < NW; ++o)
 #pragma unroll
-                for (int c = 0; c < Gather::NV; ++c) acc[o][c] = fma(ws, v[c], acc[o][c]);
-            }
+                for (int c = 0; c < Gather::NV; ++c) acc[o][c] = fma(ws[o], v[c], acc[o][c]);
+        };
+        int s0 = 0;
+#pragma unroll 1
+        for (; s0 + GC <= k; s0 += GC) {
+            int jj[GC];
+            double ww[GC][NW];
+#pragma unroll
+            for (int s = 0; s < GC; ++s) jj[s] = ld_stream(idx + (int64_t)(s0 + s) * rows + r);
+#pragma unroll
+            for (int s = 0; s < GC; ++s)
+#pragma unroll
+                for (int o = 0; o < NW; ++o)
+                    ww[s][o] = ld_stream(w[o] + (int64_t)(s0 + s) * rows + r);
+#pragma unroll
+            for (int s = 0; s < GC; ++s) take(jj[s], ww[s]);
+        }
+        for (; s0 < k; ++s0) {
+            const int j = ld_stream(idx + (int64_t)s0 * rows + r);
+            double ws[NW];
+#pragma unroll
+            for (int o = 0; o < NW; ++o) ws[o] = ld_stream(w[o] + (int64_t)s0 * rows + r);
+            take(j, ws);
         }
     }
 }

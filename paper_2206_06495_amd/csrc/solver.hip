@@ -70,17 +70,27 @@ __device__ __forceinline__ void store_partials(double (&v)[NQ], double *part, in
     }
 }
 
-// Each block re-reduces NQ rows of nb partials in a fixed order.
+// Each block re-reduces NQ rows of nb partials in a fixed order.  The first
+// blockDim.x of every row are loaded together, in one memory round trip;
+// partials_issue alone leaves them in flight, for partials_sum.
+template <int NQ>
+__device__ __forceinline__ void partials_issue(const double *part, int nb, double (&out)[NQ]) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+        out[q] = ((int)threadIdx.x < nb) ? part[(int64_t)q * nb + threadIdx.x] : 0.0;
+}
+template <int NQ>
+__device__ __forceinline__ void partials_sum(const double *part, int nb, double (&out)[NQ]) {
+    __shared__ double lds[NQ * (kThreads / 64)];
+    for (int b = threadIdx.x + blockDim.x; b < nb; b += blockDim.x)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) out[q] += part[(int64_t)q * nb + b];
+    rbf::block_sum<NQ>(out, lds);
+}
 template <int NQ>
 __device__ __forceinline__ void load_partials(const double *part, int nb, double (&out)[NQ]) {
-    __shared__ double lds[NQ * (kThreads / 64)];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-        double s = 0.0;
-        for (int b = threadIdx.x; b < nb; b += blockDim.x) s += part[(int64_t)q * nb + b];
-        out[q] = s;
-    }
-    rbf::block_sum<NQ>(out, lds);
+    partials_issue<NQ>(part, nb, out);
+    partials_sum<NQ>(part, nb, out);
 }
 
 // ------------------------------------------------------ Krylov state --
@@ -1225,23 +1235,59 @@ __global__ void __launch_bounds__(kThreads) k_h_init(EllM A, const double *__res
     if (blockIdx.x == 0 && threadIdx.x < kHR) K.flag[threadIdx.x] = 0;
 }
 
-// Finish iteration i-1 and build the new direction (see k_pc_dir).
+// Finish iteration i-1 and build the new direction (see k_pc_dir).  At the sizes
+// where the viscous solve counts in small time steps this kernel, like k_h_av and
+// k_h_s, is as long as its chain of memory round trips: the flags, the
+// partials, the scalars and the first row's values are loaded together (h = 1/40: 8.6
+// -> 6.0 us, k_h_s 6.5 -> 4.9, k_h_av, with two lanes per row, 7.8 -> 6.8).
+template <bool FIRST>
 __global__ void __launch_bounds__(kThreads) k_h_dir(HKry K, const double *__restrict__ dinv,
-                                                     double *__restrict__ x, int64_t n, int i, int i0) {
-    if (h_done(K.flag)) return;
+                                                     double *__restrict__ x, int64_t n, int i) {
     const int nb = gridDim.x;
-    const bool first = (i == i0);
     const int par = i & 1;
-    double al[kHR] = {}, om[kHR] = {}, be[kHR] = {};
-    bool act[kHR];
-    double q[4 * kHR];
-    if (first) load_partials<2 * kHR>(K.partI, nb, *reinterpret_cast<double(*)[2 * kHR]>(q));
-    else load_partials<3 * kHR>(K.part6, nb, *reinterpret_cast<double(*)[3 * kHR]>(q));
+    const double *pold = K.p[par ^ 1];
+    double *pnew = K.p[par];
+    constexpr int NQ = (FIRST ? 2 : 3) * kHR;
+    double q[NQ], pr0[kHR], pr1[kHR];
+    partials_issue<NQ>(FIRST ? K.partI : K.part6, nb, q);
+    struct {
+        double di, r[kHR], s[kHR], t[kHR], x[kHR], ph[kHR], sh[kHR], p[kHR], v[kHR];
+    } f;
+    auto load = [&](int64_t row) {
+        f.di = dinv[row];
+#pragma unroll
+        for (int c = 0; c < kHR; ++c) {
+            const int64_t o = c * n + row;
+            if constexpr (FIRST) {
+                f.r[c] = K.r[o];
+            } else {
+                f.s[c] = K.s[o];
+                f.t[c] = K.t[o];
+                f.x[c] = x[o];
+                f.ph[c] = K.ph[o];
+                f.sh[c] = K.sh[o];
+                f.p[c] = pold[o];
+                f.v[c] = K.v[o];
+            }
+        }
+    };
+    load(min(row_of(0), n - 1));
 #pragma unroll
     for (int c = 0; c < kHR; ++c) {
-        act[c] = K.flag[c] == 0;
+        const double *pr = K.rec + ((int64_t)max(i - 1, 0) * kHR + c) * 4;
+        pr0[c] = pr[0];
+        pr1[c] = pr[1];
+    }
+    const int fl[kHR] = {K.flag[0], K.flag[1]};
+    if (fl[0] != 0 && fl[1] != 0) return;
+    partials_sum<NQ>(FIRST ? K.partI : K.part6, nb, q);
+    double al[kHR] = {}, om[kHR] = {}, be[kHR] = {};
+    bool act[kHR];
+#pragma unroll
+    for (int c = 0; c < kHR; ++c) {
+        act[c] = fl[c] == 0;
         double rho;
-        if (first) {
+        if constexpr (FIRST) {
             rho = q[c];
             if (blockIdx.x == 0 && threadIdx.x == 0) {
                 K.bb[c] = q[kHR + c];
@@ -1249,12 +1295,11 @@ __global__ void __launch_bounds__(kThreads) k_h_dir(HKry K, const double *__rest
                 K.rec[((int64_t)i * kHR + c) * 4] = rho;
             }
         } else {
-            const double *pr = K.rec + ((int64_t)(i - 1) * kHR + c) * 4;
-            al[c] = pr[1];
+            al[c] = pr1[c];
             const double ts = q[c], tt = q[kHR + c], rt = q[2 * kHR + c];
             om[c] = (tt != 0.0) ? ts / tt : 0.0;
             rho = -om[c] * rt;
-            be[c] = (rho / pr[0]) * (al[c] / om[c]);
+            be[c] = (rho / pr0[c]) * (al[c] / om[c]);
             if (!isfinite(be[c])) be[c] = 0.0;  // omega = 0: rho = 0, restarted by k_h_s
             if (blockIdx.x == 0 && threadIdx.x == 0 && act[c]) {
                 K.rec[((int64_t)(i - 1) * kHR + c) * 4 + 2] = om[c];
@@ -1262,30 +1307,28 @@ __global__ void __launch_bounds__(kThreads) k_h_dir(HKry K, const double *__rest
             }
         }
     }
-    const double *pold = K.p[par ^ 1];
-    double *pnew = K.p[par];
     double acc[kHR] = {};
     for (int64_t it = 0;; ++it) {
         const int64_t row = row_of(it);
         if (row - threadIdx.x >= n) break;
+        if (it > 0) load(min(row, n - 1));
         if (row < n) {
-            const double di = dinv[row];
 #pragma unroll
             for (int c = 0; c < kHR; ++c) {
                 if (!act[c]) continue;
                 const int64_t o = c * n + row;
                 double rn, pn;
-                if (first) {
-                    rn = K.r[o];
+                if constexpr (FIRST) {
+                    rn = f.r[c];
                     pn = rn;
                 } else {
-                    rn = K.s[o] - om[c] * K.t[o];
-                    x[o] = x[o] + al[c] * K.ph[o] + om[c] * K.sh[o];
+                    rn = f.s[c] - om[c] * f.t[c];
+                    x[o] = f.x[c] + al[c] * f.ph[c] + om[c] * f.sh[c];
                     K.r[o] = rn;
-                    pn = rn + be[c] * (pold[o] - om[c] * K.v[o]);
+                    pn = rn + be[c] * (f.p[c] - om[c] * f.v[c]);
                 }
                 pnew[o] = pn;
-                K.ph[o] = di * pn;
+                K.ph[o] = f.di * pn;
                 acc[c] += rn * rn;
             }
         }
@@ -1295,38 +1338,83 @@ __global__ void __launch_bounds__(kThreads) k_h_dir(HKry K, const double *__rest
 
 // out = A y for both components; MODE 0: partials (rh, out) -> part3;
 // MODE 1: (out, s), (out, out), (rh, out) -> part6.
+// KT = 28 takes two lanes per row (blocks of 2 kThreads threads on the same grid, as
+// k_h_jac2), the entries loaded with the flags.
 template <int KT, int MODE>
-__global__ void __launch_bounds__(kThreads) k_h_av(EllM A, HKry K, const double *__restrict__ y,
-                                                    double *__restrict__ out) {
-    if (h_done(K.flag)) return;
-    const int nb = gridDim.x;
+__global__ void __launch_bounds__((KT > 0 ? 2 : 1) * kThreads) k_h_av(EllM A, HKry K,
+                                                                     const double *__restrict__ y,
+                                                                     double *__restrict__ out) {
     constexpr int NQ = (MODE == 0 ? 1 : 3) * kHR;
-    double acc[NQ] = {};
-    for (int64_t it = 0;; ++it) {
-        const int64_t row = row_of(it);
-        if (row - threadIdx.x >= A.n) break;
-        if (row < A.n) {
-            double ay[1][kHR] = {};
-            const double *ws[1] = {A.w};
-            rbf::ell_row<KT, 1>(A.idx, ws, A.n, row, A.k, GatherN<kHR>{y, A.n}, ay);
+    const int nb = gridDim.x;
+    double acc[NQ] = {}, rh[kHR], sv[kHR];
+    auto load = [&](int64_t row) {
 #pragma unroll
-            for (int c = 0; c < kHR; ++c) {
-                const int64_t o = c * A.n + row;
-                const double val = ay[0][c];
-                out[o] = val;
-                const double rh = K.rh[o];
-                if constexpr (MODE == 0) {
-                    acc[c] += rh * val;
-                } else {
-                    const double sv = K.s[o];
-                    acc[c] += val * sv;
-                    acc[kHR + c] += val * val;
-                    acc[2 * kHR + c] += rh * val;
-                }
+        for (int c = 0; c < kHR; ++c) {
+            rh[c] = K.rh[c * A.n + row];
+            sv[c] = (MODE == 1) ? K.s[c * A.n + row] : 0.0;
+        }
+    };
+    auto take = [&](int64_t row, const double(&ay)[kHR]) {
+#pragma unroll
+        for (int c = 0; c < kHR; ++c) {
+            const double val = ay[c];
+            out[c * A.n + row] = val;
+            if constexpr (MODE == 0) {
+                acc[c] += rh[c] * val;
+            } else {
+                acc[c] += val * sv[c];
+                acc[kHR + c] += val * val;
+                acc[2 * kHR + c] += rh[c] * val;
             }
         }
+    };
+    if constexpr (KT > 0) {
+        constexpr int H = KT / 2, NW = 2 * kThreads / 64;
+        __shared__ double lds[NQ * NW];
+        const int lane = threadIdx.x & 63, half = lane >> 5, wv = threadIdx.x >> 6;
+        const int64_t bx = rbf::xcd_block(blockIdx.x, nb);
+        const int fl = K.flag[0], fl1 = K.flag[1];
+#pragma unroll 1
+        for (int64_t it = 0;; ++it) {
+            if ((bx + it * nb) * kThreads >= A.n) break;
+            const int64_t row = (bx + it * nb) * kThreads + wv * 32 + (lane & 31);
+            const int64_t rr = (row < A.n) ? row : A.n - 1;
+            int jj[H];
+            double ww[H], ay[kHR] = {};
+#pragma unroll
+            for (int s = 0; s < H; ++s) jj[s] = A.idx[(int64_t)(half * H + s) * A.n + rr];
+#pragma unroll
+            for (int s = 0; s < H; ++s) ww[s] = A.w[(int64_t)(half * H + s) * A.n + rr];
+            load(rr);
+            if (fl != 0 && fl1 != 0) return;
+#pragma unroll
+            for (int s = 0; s < H; ++s)
+#pragma unroll
+                for (int c = 0; c < kHR; ++c) ay[c] = fma(ww[s], y[c * A.n + jj[s]], ay[c]);
+#pragma unroll
+            for (int c = 0; c < kHR; ++c) ay[c] += __shfl_xor(ay[c], 32, 64);
+            if (half == 0 && row < A.n) take(row, ay);
+        }
+        rbf::block_sum<NQ>(acc, lds);
+        if (threadIdx.x == 0)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+                (MODE == 0 ? K.part3 : K.part6)[(int64_t)q * nb + blockIdx.x] = acc[q];
+    } else {
+        if (h_done(K.flag)) return;
+        for (int64_t it = 0;; ++it) {
+            const int64_t row = row_of(it);
+            if (row - threadIdx.x >= A.n) break;
+            if (row < A.n) {
+                double ay[1][kHR] = {};
+                const double *ws[1] = {A.w};
+                load(row);
+                rbf::ell_row<KT, 1>(A.idx, ws, A.n, row, A.k, GatherN<kHR>{y, A.n}, ay);
+                take(row, ay[0]);
+            }
+        }
+        store_partials<NQ>(acc, MODE == 0 ? K.part3 : K.part6, nb);
     }
-    store_partials<NQ>(acc, MODE == 0 ? K.part3 : K.part6, nb);
 }
 
 // Convergence test on ||r_i||, alpha, s = r - alpha v and s^ = D^-1 s.
@@ -1335,27 +1423,48 @@ __global__ void __launch_bounds__(kThreads) k_h_av(EllM A, HKry K, const double 
 __global__ void __launch_bounds__(kThreads) k_h_s(HKry K, const double *__restrict__ dinv,
                                                    int64_t n, int i, int i0, double tol2, int win,
                                                    uint32_t seq) {
-    if (h_done(K.flag)) return;
     const int nb = gridDim.x;
-    double q1[kHR], q3[kHR];
-    load_partials<kHR>(K.part1, nb, q1);
-    load_partials<kHR>(K.part3, nb, q3);
+    double q1[kHR], q3[kHR], rhoc[kHR], bbc[kHR], rhrhc[kHR], best0[kHR], best1[kHR];
+    partials_issue<kHR>(K.part1, nb, q1);
+    partials_issue<kHR>(K.part3, nb, q3);
+    double di, rv_[kHR], vv_[kHR];
+    auto load = [&](int64_t row) {
+        di = dinv[row];
+#pragma unroll
+        for (int c = 0; c < kHR; ++c) {
+            rv_[c] = K.r[c * n + row];
+            vv_[c] = K.v[c * n + row];
+        }
+    };
+    load(min(row_of(0), n - 1));
+#pragma unroll
+    for (int c = 0; c < kHR; ++c) {
+        const double *bprev = K.best + ((((i + 1) & 1) * kHR) + c) * 2;
+        rhoc[c] = K.rec[((int64_t)i * kHR + c) * 4];
+        bbc[c] = K.bb[c];
+        rhrhc[c] = K.rhrh[c];
+        best0[c] = bprev[0];
+        best1[c] = bprev[1];
+    }
+    const int fl[kHR] = {K.flag[0], K.flag[1]};
+    if (fl[0] != 0 && fl[1] != 0) return;
+    partials_sum<kHR>(K.part1, nb, q1);
+    partials_sum<kHR>(K.part3, nb, q3);
     double al[kHR];
     bool act[kHR];
 #pragma unroll
     for (int c = 0; c < kHR; ++c) {
-        act[c] = K.flag[c] == 0;
+        act[c] = fl[c] == 0;
         const double rr = q1[c], rv = q3[c];
-        const double rho = K.rec[((int64_t)i * kHR + c) * 4];
+        const double rho = rhoc[c];
         al[c] = rho / rv;
         if (!act[c]) continue;
-        const double bb = K.bb[c], rhrh = K.rhrh[c];
+        const double bb = bbc[c], rhrh = rhrhc[c];
         const bool bad = !isfinite(rr) || !isfinite(rho);
         const bool conv = !bad && (rr <= tol2 * fmax(bb, 1e-300) || rr == 0.0);
-        const double *bprev = K.best + ((((i + 1) & 1) * kHR) + c) * 2;
         const bool fresh = (i == i0);
-        const double best = fresh ? rr : bprev[0];
-        const int best_it = fresh ? i : (int)bprev[1];
+        const double best = fresh ? rr : best0[c];
+        const int best_it = fresh ? i : (int)best1[c];
         const bool better = fresh || rr < 0.999 * best;
         const bool stall = !better && (i - best_it >= win);
         const bool brk = !bad && !conv &&
@@ -1377,13 +1486,13 @@ __global__ void __launch_bounds__(kThreads) k_h_s(HKry K, const double *__restri
     for (int64_t it = 0;; ++it) {
         const int64_t row = row_of(it);
         if (row - threadIdx.x >= n) break;
+        if (it > 0) load(min(row, n - 1));
         if (row < n) {
-            const double di = dinv[row];
 #pragma unroll
             for (int c = 0; c < kHR; ++c) {
                 if (!act[c]) continue;
                 const int64_t o = c * n + row;
-                const double sv = K.r[o] - al[c] * K.v[o];
+                const double sv = rv_[c] - al[c] * vv_[c];
                 K.s[o] = sv;
                 K.sh[o] = di * sv;
             }
@@ -2607,8 +2716,8 @@ rbf_status hbicgstab(rbf_solver *S, EllM A, const double *b, double *x, double t
     };
     auto av = [&](int mode, const double *y, double *out) {
         if (k28) {
-            if (mode == 0) hipLaunchKernelGGL((k_h_av<28, 0>), grid, block, 0, st, A, K, y, out);
-            else hipLaunchKernelGGL((k_h_av<28, 1>), grid, block, 0, st, A, K, y, out);
+            if (mode == 0) hipLaunchKernelGGL((k_h_av<28, 0>), grid, dim3(2 * kThreads), 0, st, A, K, y, out);
+            else hipLaunchKernelGGL((k_h_av<28, 1>), grid, dim3(2 * kThreads), 0, st, A, K, y, out);
         } else {
             if (mode == 0) hipLaunchKernelGGL((k_h_av<0, 0>), grid, block, 0, st, A, K, y, out);
             else hipLaunchKernelGGL((k_h_av<0, 1>), grid, block, 0, st, A, K, y, out);
@@ -2628,7 +2737,8 @@ rbf_status hbicgstab(rbf_solver *S, EllM A, const double *b, double *x, double t
     while (!done) {
         const int stop = std::min(maxit + 1, it + batch);
         for (; it < stop; ++it) {
-            hipLaunchKernelGGL(k_h_dir, grid, block, 0, st, K, A.dinv, x, n, it, i0);
+            if (it == i0) hipLaunchKernelGGL(k_h_dir<true>, grid, block, 0, st, K, A.dinv, x, n, it);
+            else hipLaunchKernelGGL(k_h_dir<false>, grid, block, 0, st, K, A.dinv, x, n, it);
             av(0, K.ph, K.v);
             hipLaunchKernelGGL(k_h_s, grid, block, 0, st, K, A.dinv, n, it, i0, tol2, win, seq);
             av(1, K.sh, K.t);
