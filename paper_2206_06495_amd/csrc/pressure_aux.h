@@ -90,7 +90,6 @@ struct FgScal {
     double *H;       // [(mr+1) * mr] Hessenberg matrix, column-major
     double *cs, *sn; // [mr] Givens rotations
     double *g;       // [mr+1] rotated right-hand side
-    double *y;       // [mr] coefficients of the update
     double *partZ;   // [kMaxBlocks] sums of J e (interpolated correction)
     double *partO;   // [kMaxBlocks] sums of z (border term of A z)
     double *one;     // [1] = 1.0 (unit scale of an explicit input vector)
@@ -570,13 +569,11 @@ __global__ void __launch_bounds__(kThreads) k_fg_init(EllM A, const double *__re
     store_partials<1>(v1, part + kMaxBlocks, nb);
 }
 
-// Reduce nq rows of nb block partials (row q at q * kMaxBlocks) into
-// out[q]: one workgroup per row, a fixed order.  GATE: exit when the flag
-// is set (inside an Arnoldi step).
-template <bool GATE>
-__global__ void __launch_bounds__(256) k_fg_reduce(const double *part, int nb, int nq,
-                                                   double *out, const int *flag) {
-    if (GATE && *flag != 0) return;
+// Reduce rows of nb block partials (row q at q * kMaxBlocks) into out[q]: one
+// workgroup per row, a fixed order; exits when the flag is set.
+__global__ void __launch_bounds__(256) k_fg_reduce(const double *part, int nb, double *out,
+                                                   const int *flag) {
+    if (*flag != 0) return;
     const int q = blockIdx.x;
     double v[1] = {0.0};
     for (int b = threadIdx.x; b < nb; b += 256) v[0] += part[(int64_t)q * kMaxBlocks + b];
@@ -585,13 +582,24 @@ __global__ void __launch_bounds__(256) k_fg_reduce(const double *part, int nb, i
     if (threadIdx.x == 0) out[q] = v[0];
 }
 
-// Cycle start, one thread: beta = ||r||, the cycle's target (FP64:
+// Cycle start, one workgroup: beta = ||r||, the cycle's target (FP64:
 // tol ||b||; mixed: also kMixedInner beta), convergence of the true
-// residual (flag 1), g = beta e_1.  red: {||r||^2, ||b||^2}; ||b|| is
-// taken from the first cycle.
-__global__ void k_fg_start(FgScal F, const double *red, double tol, int mixed, int first,
-                           uint32_t seq) {
-    const double rr = red[0], bbv = first ? red[1] : F.stat[1];
+// residual (flag 1), g = beta e_1.  ||r||^2 and ||b||^2 from the nb block partials
+// of k_fg_init; ||b|| is taken from the first cycle.
+__global__ void __launch_bounds__(256) k_fg_start(FgScal F, int nb, double tol, int mixed,
+                                                   int first, uint32_t seq) {
+    double v[2] = {0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < kMaxBlocks / 256; ++q) {
+        const int at = threadIdx.x + 256 * q;
+        v[0] += (at < nb) ? F.part[at] : 0.0;
+        v[1] += (at < nb) ? F.part[kMaxBlocks + at] : 0.0;
+    }
+    const double bb0 = F.stat[1];
+    __shared__ double lds[2 * 4];
+    rbf::block_sum<2>(v, lds);
+    if (threadIdx.x != 0) return;
+    const double rr = v[0], bbv = first ? v[1] : bb0;
     const double beta = sqrt(rr);
     const double goal = tol * sqrt(fmax(bbv, 1e-300));
     F.stat[1] = bbv;
@@ -906,35 +914,61 @@ __global__ void __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_
     }
 }
 
-// End of a cycle of nstep steps, one thread: back substitution H y = g.
-__global__ void __launch_bounds__(256) k_fg_solve(FgScal F, int nstep, int mr) {
-    __shared__ double Hs[kFgMax * kFgMax], gs[kFgMax], ys[kFgMax];
-    for (int e = threadIdx.x; e < nstep * nstep; e += blockDim.x) {
-        const int l = e / nstep, i = e % nstep;  // column l, row i
-        Hs[l * kFgMax + i] = F.H[(int64_t)l * (mr + 1) + i];
-    }
-    for (int i = threadIdx.x; i < nstep; i += blockDim.x) gs[i] = F.g[i];
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    for (int i = nstep - 1; i >= 0; --i) {
-        double s = gs[i];
-        for (int l = i + 1; l < nstep; ++l) s -= Hs[l * kFgMax + i] * ys[l];
-        const double d = Hs[i * kFgMax + i];
-        ys[i] = (d != 0.0) ? s / d : 0.0;
-    }
-    for (int i = 0; i < nstep; ++i) F.y[i] = ys[i];
-}
-
-// x += sum_i y_i Z_i (FP64 iterate).
+// End of a cycle of nstep steps: back substitution H y = g and x += sum_i y_i Z_i
+// (FP64 iterate), with block sums of the new x (weighted by sumw unless null) for
+// the next cycle's border term.  The substitution is done by the first wave of
+// every block, one unknown per lane, while the rows' Z are on their way: as a
+// launch of its own, one thread's chain of 30 divisions, it took 9.7 us, the
+// update 6.2 and the sum 2.5; 7.2 us for the three at h = 1/40.
 template <class T>
-__global__ void __launch_bounds__(kThreads) k_fg_x(const T *__restrict__ Z, const double *ycoef,
-                                                    int nstep, int64_t m, double *__restrict__ x) {
-    for (int64_t r = blockIdx.x * (int64_t)kThreads + threadIdx.x; r < m;
-         r += (int64_t)gridDim.x * kThreads) {
-        double s = x[r];
-        for (int i = 0; i < nstep; ++i) s += ycoef[i] * (double)Z[(int64_t)i * m + r];
-        x[r] = s;
+__global__ void __launch_bounds__(kThreads) k_fg_x(FgScal F, const T *__restrict__ Z, int nstep,
+                                                    int mr, int64_t m, double *__restrict__ x,
+                                                    const double *__restrict__ sumw, double *partX) {
+    __shared__ double ys[kFgMax];
+    double zv[kFgMax], xv, wv = 1.0;
+    auto load = [&](int64_t r) {
+#pragma unroll
+        for (int i = 0; i < kFgMax; ++i) zv[i] = (i < nstep) ? (double)Z[(int64_t)i * m + r] : 0.0;
+        xv = x[r];
+        if (sumw) wv = sumw[r];
+    };
+    load(min(row_of(0), m - 1));
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        double h[kFgMax];
+#pragma unroll
+        for (int l = 0; l < kFgMax; ++l)
+            h[l] = (l < nstep && lane <= l) ? F.H[(int64_t)l * (mr + 1) + lane] : 0.0;
+        double g = (lane < nstep) ? F.g[lane] : 0.0, y = 0.0;
+        const double d = (lane < nstep) ? F.H[(int64_t)lane * (mr + 1) + lane] : 1.0;
+        const double inv = (d != 0.0) ? 1.0 / d : 0.0;
+#pragma unroll
+        for (int l = kFgMax - 1; l >= 0; --l) {
+            if (l >= nstep) continue;
+            const double gl = rbf::readlane_double(g, l), il = rbf::readlane_double(inv, l),
+                         dl = rbf::readlane_double(d, l);
+            const double y0 = gl * il, yl = fma(fma(-y0, dl, gl), il, y0);  // g / d, corrected
+            if (lane == l) y = yl;
+            g = fma(-h[l], yl, g);
+        }
+        if (lane < kFgMax) ys[lane] = y;
     }
+    __syncthreads();
+    double acc[1] = {0.0};
+    for (int64_t it = 0;; ++it) {
+        const int64_t r = row_of(it);
+        if (r - threadIdx.x >= m) break;
+        if (it > 0) load(min(r, m - 1));
+        if (r < m) {
+            double s = xv;
+#pragma unroll
+            for (int i = 0; i < kFgMax; ++i)
+                if (i < nstep) s += ys[i] * zv[i];
+            x[r] = s;
+            acc[0] += wv * s;
+        }
+    }
+    store_partials<1>(acc, partX, gridDim.x);
 }
 
 // l1 row norms of the stored Poisson rows: dinv = omega / sum |w|, and

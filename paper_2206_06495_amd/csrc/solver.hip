@@ -3139,14 +3139,15 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
     };
     rbf_status rc = RBF_OK;
     for (;;) {
-        if (sumw) hipLaunchKernelGGL(k_wsum, grid, block, 0, st, m, sumw, x, S->kp.partX);
-        else if (A.u1) hipLaunchKernelGGL((k_sum<1>), grid, block, 0, st, m, x, S->kp.partX);
+        if (cycles == 0 && sumw)  // (a later cycle's sum is left by k_fg_x)
+            hipLaunchKernelGGL(k_wsum, grid, block, 0, st, m, sumw, x, S->kp.partX);
+        else if (cycles == 0 && A.u1)
+            hipLaunchKernelGGL((k_sum<1>), grid, block, 0, st, m, x, S->kp.partX);
         launch_kt(A.k, [&](auto KT) {
             hipLaunchKernelGGL((k_fg_init<decltype(KT)::value, T>), grid, block, 0, st, A, b, x,
                                S->kp.partX, F.V, P.dinv, F.wd, Fs.part);
         });
-        hipLaunchKernelGGL(k_fg_reduce<false>, dim3(2), red, 0, st, Fs.part, nb, 2, Fs.h1, Fs.flag);
-        hipLaunchKernelGGL(k_fg_start, one, one, 0, st, Fs, Fs.h1, tol, mixed,
+        hipLaunchKernelGGL(k_fg_start, one, red, 0, st, Fs, nb, tol, mixed,
                            cycles == 0 ? 1 : 0, ++S->pub_seq);
         RBF_CHECK_LAUNCH();
         seq = S->pub_seq;
@@ -3215,13 +3216,13 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
                                       A.vscale, F, j);
             const bool sum = !kFgReorth && nb <= kSumBlocks;
             if (!sum)
-                hipLaunchKernelGGL(k_fg_reduce<true>, dim3(j + 1), red, 0, st, Fs.part, nb, j + 1,
+                hipLaunchKernelGGL(k_fg_reduce, dim3(j + 1), red, 0, st, Fs.part, nb,
                                    Fs.h1, Fs.flag);
             const dim3 b2(2 * kThreads);
             if constexpr (kFgReorth) {
                 hipExtLaunchKernelGGL((k_fg_gs<T, 1, false>), grid, b2, 0, st, g0, g1, 0, F,
                                       Fs.h1, P.dinv, m, j);
-                hipLaunchKernelGGL(k_fg_reduce<true>, dim3(j + 1), red, 0, st, Fs.part, nb, j + 1,
+                hipLaunchKernelGGL(k_fg_reduce, dim3(j + 1), red, 0, st, Fs.part, nb,
                                    Fs.h2, Fs.flag);
                 hipLaunchKernelGGL((k_fg_gs<T, 2, false>), grid, b2, 0, st, F, Fs.h2, P.dinv, m, j);
             } else if (sum) {
@@ -3245,8 +3246,8 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
         }
         if (f == 1 || f == -1) break;
         std::memcpy(&beta_prev, Fs.pub + 2, sizeof(beta_prev));
-        hipLaunchKernelGGL(k_fg_solve, one, red, 0, st, Fs, nstep, mr);
-        hipLaunchKernelGGL((k_fg_x<T>), grid, block, 0, st, F.Z, Fs.y, nstep, m, x);
+        hipLaunchKernelGGL((k_fg_x<T>), grid, block, 0, st, Fs, F.Z, nstep, mr, m, x, sumw,
+                           S->kp.partX);
         ++cycles;
     }
     std::memcpy(&bb, Fs.pub + 1, sizeof(bb));
@@ -3303,7 +3304,6 @@ rbf_status alloc_fg(rbf_solver *S, FgDev<T> &F, int64_t M) {
     ALLOC(s.cs, mr);
     ALLOC(s.sn, mr);
     ALLOC(s.g, mr + 1);
-    ALLOC(s.y, mr);
     ALLOC(s.partZ, kMaxBlocks);
     ALLOC(s.partO, kMaxBlocks);
     ALLOC(s.one, 1);
