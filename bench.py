@@ -13,7 +13,7 @@ Workload (one JSON line on stdout):
   * roofline of the dominant kernel of the step (the longest of the sampled
     pressure-solve kernels: the FGMRES product k_fg_av2, the smoothing product
     k_aux_post2, the Gram-Schmidt update k_fg_gs<2>, the auxiliary
-    lattice transform k_pc_gemm<0>), its average duration sampled with the
+    lattice transform k_pc_fold), its average duration sampled with the
     launch's own start/end stamps on the solver's stream during the timed
     steps, against its algorithmic bytes per launch.
   * mixed: the same steps with FP32 restart cycles inside FP64 iterative
@@ -65,10 +65,9 @@ FP64_VALU_PEAK_TFLOPS = 78.6
 # Traffic beyond L2 per launch of the roofline kernels at the headline
 # workload, from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE scaled by the same
 # counters on a plain 256 MiB copy (2.0 and 1.0), mean over the working
-# launches of 3 steps from rest (mean Arnoldi index 11.9 for k_fg_av2 and
-# k_fg_gs<2>); None for a kernel changed since it was measured.
-TRAFFIC_BYTES = {"k_fg_av2": 87.05e6, "k_aux_post2": 68.84e6, "k_fg_gs<2>": 26.30e6,
-                 "k_pc_gemm<0>": 22.76e6}
+# launches of 3 steps from rest; None for a kernel changed since it was
+# measured.
+TRAFFIC_BYTES = {"k_fg_av2": None, "k_aux_post2": None, "k_fg_gs<2>": None, "k_pc_fold": None}
 
 
 def parse():
@@ -608,7 +607,7 @@ def main():
         f"{steps_per_ts:.1f}  |u|max {umax:.3f}")
     # Dominant kernel among the sampled ones (each runs once per FGMRES step).
     names = {"spmv": "k_fg_av2", "smooth": "k_aux_post2", "gs": "k_fg_gs<2>",
-             "gemm": "k_pc_gemm<0>"}
+             "gemm": "k_pc_fold"}
     nbytes = kernel_bytes(M, prof, steps_per_ts / max(1, cycles))
     kern = {}
     for slot, name in names.items():
@@ -619,9 +618,9 @@ def main():
                 kern[name]["bytes_per_launch"] = nbytes[name]
                 kern[name]["GB/s"] = nbytes[name] / (ms * 1e-3) / 1e9
     dom = max(kern, key=lambda k: kern[k]["avg_us"]) if kern else None
-    if dom == "k_pc_gemm<0>":
+    if dom == "k_pc_fold":
         n = info["aux_cells"] - 1
-        flops = 2.0 * n ** 3
+        flops = 1.0 * n ** 3  # half of the plain product's, by symmetry
         ach = flops / (kern[dom]["avg_us"] * 1e-6) / 1e12
         roof = {"kernel": f"{dom} (auxiliary-lattice transform, {n}^3 FP64 product)",
                 "bound": "mfma", "achieved": ach, "peak": FP64_MFMA_PEAK_TFLOPS,

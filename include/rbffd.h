@@ -501,13 +501,14 @@ rbf_status rbf_solver_apply_precond(rbf_solver *s, const double *y, double *z);
  * rbf_solver_profile -- sample kernel durations of the pressure solve on the
  * solver's stream:
  *   RBF_PROF_GEMM    the first transform of the lattice preconditioner or of
- *                    the auxiliary lattice (k_pc_gemm<0>, an n x n x n FP64
+ *                    the auxiliary lattice (k_pc_fold, an n x n x n FP64
  *                    or FP32 product, n = cells per side - 1; k_pc_modes,
  *                    which also solves the modes, up to n = 128);
  *   RBF_PROF_SPMV    the Krylov product with the Poisson matrix (k_pc_av with
  *                    the lattice preconditioner, k_kry_a without one, k_fg_av2
- *                    or, on at most 256 blocks, k_fg_av2_few in FGMRES (k_fg_av for stencils other than 28 nodes): the
- *                    product plus the Gram-Schmidt dots);
+ *                    in FGMRES (k_fg_av2_few on at most 256 blocks, k_fg_av
+ *                    for stencils other than 28 nodes): the product plus the
+ *                    Gram-Schmidt dots);
  *   RBF_PROF_SMOOTH  the post-smoothing product of the auxiliary-lattice
  *                    preconditioner (k_aux_post2; k_aux_post for stencils
  *                    other than 28 nodes);

@@ -25,6 +25,8 @@
 // go() is asked once the first loads are issued; false (uniform over the
 // workgroup) ends the block.
 // Every wave of the workgroup must call it (it synchronises when S > 1).
+//
+// mfma_wave_sum is its sum over the waves for a kernel with loads of its own.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -118,6 +120,19 @@ __device__ __forceinline__ bool mfma_block(int n, const T *__restrict__ A, const
         }
     }
     return true;
+}
+
+// Sum of the partial tiles of the workgroup's S waves, in a fixed order; complete on
+// wave 0.  Every wave must call it.
+template <class T, int S>
+__device__ __forceinline__ void mfma_wave_sum(typename mfma16<T>::acc4 &acc) {
+    __shared__ typename mfma16<T>::acc4 red[S - 1][64];
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+    if (w > 0) red[w - 1][l] = acc;
+    __syncthreads();
+    if (w != 0) return;
+#pragma unroll
+    for (int v = 0; v < S - 1; ++v) acc += red[v][l];
 }
 
 }  // namespace rbf

@@ -1,7 +1,7 @@
 // Pressure solve on general node sets: flexible GMRES (Saad 1993) right-
 // preconditioned by a two-level auxiliary-lattice method.  Included by
 // solver.hip inside its anonymous namespace (it uses the solver's Krylov
-// helpers, the lattice transforms k_pc_gemm / k_pc_tri and rbf_solver).
+// helpers, the lattice transforms k_pc_fold / k_pc_tri / k_pc_gemm and rbf_solver).
 //
 // System: the row-scaled bordered Poisson operator of eq. (18),
 //   A x = S A0 x + u1 c (1^T x),   S the row scale, u1 = S chi, c = vscale,

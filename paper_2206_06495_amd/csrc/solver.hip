@@ -470,10 +470,10 @@ __global__ void __launch_bounds__(kThreads) k_resid(EllM A, const double *__rest
 // interior nodes the separable operator (T (x) I + I (x) T) / h^2, T the
 // 1-D second difference with Neumann ends.  The x-direction is
 // diagonalised by the DCT-II basis Q (T = Q Lam Q^-1): a dense product
-// Q^-1 X on the matrix cores (k_pc_gemm, FP64 MFMA); for each x-mode k the
+// Q^-1 X on the matrix cores (k_pc_fold, FP64 MFMA); for each x-mode k the
 // y-direction system (T + lam_k I) w = h^2 t is tridiagonal and is solved by
 // one wavefront per mode (k_pc_tri: elimination inside per-lane chunks, then
-// cyclic reduction across the lanes; k_pc_modes does both up to n = 128); the product Q W returns to the
+// cyclic reduction across the lanes; k_pc_modes does both up to n = 128); the product Q W (k_pc_gemm) returns to the
 // lattice.  Mode k = 0 is
 // singular: its right-hand side loses its mean (recorded: it fixes the
 // constant through the border), the last unknown is fixed and the solution
@@ -492,7 +492,7 @@ __global__ void __launch_bounds__(kThreads) k_resid(EllM A, const double *__rest
 // The transform arrays are FP64, or FP32 when f32 is set (mixed precision:
 // the preconditioner only shapes the iteration, the residuals stay FP64).
 struct Lat {
-    int K, n, ntiles, f32;
+    int K, n, f32;
     double h, c;           // spacing; border scale
     const double *rs;      // [M] row scale of the stored Poisson rows
     const int *cell;       // [M] lower-left lattice node of the cell holding the node
@@ -787,27 +787,73 @@ __global__ void __launch_bounds__(kThreads) k_pc_pre(Lat L, const double *__rest
     store_partials<1>(acc, partG, gridDim.x);
 }
 
-// The two transforms of the interior solve, one 16x16 tile per workgroup of
-// kGemmWaves waves.  STAGE 0: T = Q^-1 X; STAGE 1: Z = Q W (into X).
+// The second transform of the interior solve, Z = Q W (into X), one 16x16 tile per
+// workgroup of kGemmWaves waves.
 // Split-K factor and chunk: with n <= 4 kGemmWaves kGemmChunk (K <= 449)
 // a wave's whole k-share is loaded before its MFMAs (ONESHOT).
 constexpr int kGemmWaves = 8;
 constexpr int kGemmChunk = 14;
-template <int STAGE, bool ONESHOT, class TP>
+template <bool ONESHOT, class TP>
 __global__ void __launch_bounds__(64 * kGemmWaves) k_pc_gemm(Lat L) {
     const int n = L.n, nt = (n + 15) / 16;
     const int ti = (int)(blockIdx.x % nt), tj = (int)(blockIdx.x / nt);
-    const TP *A = static_cast<const TP *>(STAGE == 0 ? L.Qi : L.Q);
-    const TP *B = static_cast<const TP *>(STAGE == 0 ? L.X : L.W);
-    TP *C = static_cast<TP *>(STAGE == 0 ? L.T : L.X);
-    // T row-major (one mode per row, read whole by k_pc_tri), Z column-major.
-    // The flag travels with the first operand loads; the block ends there once
-    // it is set.
+    TP *Z = static_cast<TP *>(L.X);
+    // Z column-major.  The flag travels with the first operand loads; the block
+    // ends there once it is set.
     rbf::mfma_block<TP, 1, 1, kGemmWaves, kGemmChunk, ONESHOT>(
-        n, A, B, ti, tj, [&]() { return *L.flag == 0; }, [&](int i, int j, TP v) {
-            if constexpr (STAGE == 0) C[(int64_t)i * n + j] = v;
-            else C[i + (int64_t)j * n] = v;
-        });
+        n, static_cast<const TP *>(L.Q), static_cast<const TP *>(L.W), ti, tj,
+        [&]() { return *L.flag == 0; }, [&](int i, int j, TP v) { Z[i + (int64_t)j * n] = v; });
+}
+
+// The first transform, T = Q^-1 X, for lattices above kModeMax, likewise, but with the
+// symmetry of the cosine basis: Qi(p, n-1-a) is Qi(p, a) for the h = ceil(n/2) even
+// modes, stored first, and -Qi(p, a) for the odd ones, so that
+//   T(p, j) = sum over a < h of Qi(p, a) (X(a, j) +- X(n-1-a, j))
+// takes half the multiplications and half the reads of Qi (n = 408: 9.9 -> 7.8 us;
+// the operands' way through L2 bounds it).  Z = Q W was no faster this way: with
+// both halves' sums in a workgroup it has half the workgroups, 338 at n = 408, and
+// twice the operands in registers (9.8 us against 10.2; 3.75 against 3.45 at
+// n = 41; with twice the waves 11.5).
+constexpr int kFoldSteps = 8;  // per wave: h <= 4 kGemmWaves kFoldSteps, n <= 512
+inline int fold_tiles(int n) {
+    const int h = (n + 1) / 2;
+    return ((h + 15) / 16 + (n - h + 15) / 16) * ((n + 15) / 16);
+}
+template <class TP>
+__global__ void __launch_bounds__(64 * kGemmWaves) k_pc_fold(Lat L) {
+    using M = rbf::mfma16<TP>;
+    const int n = L.n, h = (n + 1) / 2, nt = (n + 15) / 16, nth = (h + 15) / 16;
+    const int ti = (int)(blockIdx.x / nt), tj = (int)(blockIdx.x % nt);
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    const int steps = (h + 3) >> 2, per = (steps + kGemmWaves - 1) / kGemmWaves;
+    const int s0 = w * per, s1 = min(steps, s0 + per);
+    const bool odd = ti >= nth;
+    const int i0 = odd ? h + 16 * (ti - nth) : 16 * ti, iend = odd ? n : h, i = i0 + lr;
+    const int j = tj * 16 + lr;
+    const TP *Qi = static_cast<const TP *>(L.Qi), *X = static_cast<const TP *>(L.X);
+    TP *T = static_cast<TP *>(L.T);
+    TP q[kFoldSteps], xa[kFoldSteps], xb[kFoldSteps];
+#pragma unroll
+    for (int g = 0; g < kFoldSteps; ++g) {
+        const int a = 4 * (s0 + g) + lk, b = n - 1 - a;
+        const bool ok = s0 + g < s1 && a < h;
+        q[g] = (ok && i < iend) ? Qi[i + (int64_t)a * n] : TP(0);
+        xa[g] = (ok && j < n) ? X[j + (int64_t)a * n] : TP(0);
+        xb[g] = (ok && j < n && b != a) ? X[j + (int64_t)b * n] : TP(0);
+    }
+    if (*L.flag != 0) return;
+    typename M::acc4 acc = {0, 0, 0, 0};
+#pragma unroll
+    for (int g = 0; g < kFoldSteps; ++g)
+        if (s0 + g < s1) acc = M::step(q[g], odd ? xa[g] - xb[g] : xa[g] + xb[g], acc);
+    rbf::mfma_wave_sum<TP, kGemmWaves>(acc);
+    if (w != 0 || j >= n) return;
+    // T row-major: one mode per row, read whole by k_pc_tri.
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int io = i0 + M::row(r, lk);
+        if (io < iend) T[(int64_t)io * n + j] = acc[r];
+    }
 }
 
 // For each x-mode k (one wavefront): (T + lam_k I) w = h^2 t along y.  The
@@ -985,7 +1031,7 @@ __global__ void __launch_bounds__(64) k_pc_tri(Lat L) {
     pc_tri_mode<TP, kTriChunk, kTriChunk>(L, k, lane, sz, tsum, vv, lamk);
 }
 
-// k_pc_gemm<0> and k_pc_tri in one launch for lattices of n <= 64 NB, NB <= 2: the
+// k_pc_fold and k_pc_tri in one launch for lattices of n <= 64 NB, NB <= 2: the
 // workgroup of mode k makes its row of T itself, each of kModeWaves waves from
 // every kModeWaves-th row of X (the whole of X, 80 KB at n = 100, is read by
 // every workgroup, from L2), and wave 0 solves it.  At these sizes a launch is
@@ -2389,13 +2435,10 @@ rbf_status bicgstab(rbf_solver *S, KDev &K, EllM A, const double *b, double *x, 
 // One application of the lattice preconditioner's interior solve:
 // T = Q^-1 X, tridiagonal solves along y per x-mode, Z = Q W.
 rbf_status pc_apply(rbf_solver *S, const Lat &L, bool sample = false) {
-    const dim3 g(L.ntiles), b(64 * kGemmWaves);
-    const dim3 gt(L.n), bt(64);
+    const dim3 b(64 * kGemmWaves), gt(L.n), bt(64);
     // A sample times the first product (its own start and end stamps).
     hipEvent_t e0 = nullptr, e1 = nullptr;
     const bool timed = sample && prof_pair(S, RBF_PROF_GEMM, e0, e1);
-    const int steps = (L.n + 3) / 4;
-    const bool one = (steps + kGemmWaves - 1) / kGemmWaves <= kGemmChunk;
     auto run = [&](auto tp) {
         using TP = decltype(tp);
         if (L.n <= kModeMax) {
@@ -2403,12 +2446,13 @@ rbf_status pc_apply(rbf_solver *S, const Lat &L, bool sample = false) {
             if (L.n <= 64) hipExtLaunchKernelGGL((k_pc_modes<TP, 1>), gt, bm, 0, S->st, e0, e1, 0, L);
             else hipExtLaunchKernelGGL((k_pc_modes<TP, 2>), gt, bm, 0, S->st, e0, e1, 0, L);
         } else {
-            if (one) hipExtLaunchKernelGGL((k_pc_gemm<0, true, TP>), g, b, 0, S->st, e0, e1, 0, L);
-            else hipExtLaunchKernelGGL((k_pc_gemm<0, false, TP>), g, b, 0, S->st, e0, e1, 0, L);
+            hipExtLaunchKernelGGL(k_pc_fold<TP>, dim3(fold_tiles(L.n)), b, 0, S->st, e0, e1, 0, L);
             hipLaunchKernelGGL(k_pc_tri<TP>, gt, bt, 0, S->st, L);
         }
-        if (one) hipLaunchKernelGGL((k_pc_gemm<1, true, TP>), g, b, 0, S->st, L);
-        else hipLaunchKernelGGL((k_pc_gemm<1, false, TP>), g, b, 0, S->st, L);
+        const int nt = (L.n + 15) / 16, per = ((L.n + 3) / 4 + kGemmWaves - 1) / kGemmWaves;
+        const dim3 g(nt * nt);
+        if (per <= kGemmChunk) hipLaunchKernelGGL((k_pc_gemm<true, TP>), g, b, 0, S->st, L);
+        else hipLaunchKernelGGL((k_pc_gemm<false, TP>), g, b, 0, S->st, L);
     };
     if (L.f32) run(float{});
     else run(double{});
@@ -2418,7 +2462,7 @@ rbf_status pc_apply(rbf_solver *S, const Lat &L, bool sample = false) {
 
 // Right-preconditioned BiCGSTAB on the pressure system (one right-hand side)
 // with the lattice preconditioner; same contract as bicgstab<1, false>.
-// Per iteration: k_pc_dir, P^-1 (k_pc_gemm, k_pc_tri, k_pc_gemm, k_pc_post),
+// Per iteration: k_pc_dir, P^-1 (k_pc_fold, k_pc_tri, k_pc_gemm, k_pc_post),
 // k_pc_av (v), k_pc_s, P^-1, k_pc_av (t).
 rbf_status pbicgstab(rbf_solver *S, EllM A, const double *b, double *x, double tol, int maxit,
                      int &last_iters, rbf_solve_stats *stats) {
@@ -2816,20 +2860,22 @@ rbf_status poisson_solve(rbf_solver *S, const double *b, double *x, rbf_solve_st
 // DCT-II eigenbasis of the 1-D Neumann second difference on n points
 // (tridiag(1, -2, 1) with -1 at both ends): q_k(a) = cos(pi k (a + 1/2) / n),
 // lam_k = -4 sin^2(pi k / (2 n)).  Q(a, k) at Q[a + k n]; Q^-1(k, a) =
-// d_k Q(a, k) with d_0 = 1/n, d_k = 2/n, at Qi[k + a n].
+// d_k Q(a, k) with d_0 = 1/n, d_k = 2/n, at Qi[k + a n].  Modes are stored in
+// the order k = 0, 2, 4, .., 1, 3, .. (even ones first, for k_pc_fold).
 void dct2_basis(int n, std::vector<double> &Q, std::vector<double> &Qi, std::vector<double> &lam) {
     Q.assign((size_t)n * n, 0.0);
     Qi.assign((size_t)n * n, 0.0);
     lam.assign(n, 0.0);
     const double pi = 3.14159265358979323846;
-    for (int k = 0; k < n; ++k) {
+    for (int p = 0; p < n; ++p) {
+        const int h = (n + 1) / 2, k = (p < h) ? 2 * p : 2 * (p - h) + 1;
         const double sk = std::sin(pi * k / (2.0 * n));
-        lam[k] = -4.0 * sk * sk;
+        lam[p] = -4.0 * sk * sk;
         for (int a = 0; a < n; ++a) {
             const int64_t mth = ((int64_t)k * (2 * a + 1)) % (4LL * n);  // angle pi mth / (2n)
             const double c = std::cos(pi * (double)mth / (2.0 * n));
-            Q[(size_t)a + (size_t)k * n] = c;
-            Qi[(size_t)k + (size_t)a * n] = (k == 0 ? 1.0 / n : 2.0 / n) * c;
+            Q[(size_t)a + (size_t)p * n] = c;
+            Qi[(size_t)p + (size_t)a * n] = (k == 0 ? 1.0 / n : 2.0 / n) * c;
         }
     }
 }
@@ -2904,9 +2950,7 @@ rbf_status setup_lattice_pc(rbf_solver *S, const rbf_grid *g, int mode) {
             V[(size_t)k * n + b] = ek + ((b == 0 || b == n - 1) ? sk + ek : 0.0);
     }
     const size_t nn = (size_t)n * n;
-    const int nt = (n + 15) / 16;
     Lat &L = S->lat;
-    L.ntiles = nt * nt;
     L.f32 = S->mixed ? 1 : 0;
     const size_t es = L.f32 ? sizeof(float) : sizeof(double);
     int *dcell;
@@ -3398,9 +3442,7 @@ rbf_status setup_aux_pc(rbf_solver *S, const rbf_grid *g, int mode) {
     // k, (T_y + (hy/hx)^2 lam_k) w = hy^2 t.
     for (double &l : lam) l *= (hya / hxa) * (hya / hxa);
     const size_t nn = (size_t)n * n;
-    const int nt = (n + 15) / 16;
     Lat &L = S->lat;
-    L.ntiles = nt * nt;
     L.f32 = S->mixed ? 1 : 0;
     const size_t es = L.f32 ? sizeof(float) : sizeof(double);
     int *dcell, *drptr, *drcol;

@@ -1,6 +1,6 @@
 """The lattice preconditioner at the sizes where its transform changes kernels (n = K - 1
 lattice points a side: one launch for product and mode solves up to 64 and up to
-128, two beyond) against its plain statement, in FP64 and FP32."""
+128, two beyond; odd and even n, and the largest) against its plain statement, in FP64 and FP32."""
 import pytest
 
 import rbf_inputs as ri
@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
-@pytest.mark.parametrize("n", [7, 8, 63, 64, 65, 126, 127, 128, 129])
+@pytest.mark.parametrize("n", [7, 8, 63, 64, 65, 126, 127, 128, 129, 256, 257, 512])
 def test_transform_sizes(gpu, n, precision):
     import paper_2206_06495_amd as P
     K = n + 1
