@@ -152,8 +152,10 @@ rbf_status rbf_knn_noalloc(const double *xq, int64_t nq, const double *xs, int64
  * discarded.  Coordinates are shifted to x_r and divided by the power of two
  * s = 2^e with 1/4 <= max_j |x_j - x_r|^2 / s^2 < 1 (exact); weights are
  * returned in physical units (local weights times s^-order).  Each system is
- * solved by LU with partial pivoting in FP64 followed by one step of
- * iterative refinement with a double-FP64 residual.
+ * solved in FP64 followed by one step of iterative refinement with a residual
+ * summed beyond FP64: for the paper's stencil (k = 28, m = 7, q = 3) by an LDL^T
+ * factorisation on the null space of P^T, where A is definite; systems found
+ * not clearly definite, and other stencils, by LU with partial pivoting.
  *
  * xq: device [2][nq]; xs: device [2][ns]; idx: device int32 [k][nq] (from
  * rbf_knn); w: device FP64 [popcount(op_mask)][k][nq], operators in
