@@ -65,9 +65,10 @@ FP64_VALU_PEAK_TFLOPS = 78.6
 # Traffic beyond L2 per launch of the roofline kernels at the headline
 # workload, from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE scaled by the same
 # counters on a plain 256 MiB copy (2.0 and 1.0), mean over the working
-# launches of 3 steps from rest; None for a kernel changed since it was
-# measured.
-TRAFFIC_BYTES = {"k_fg_av2": None, "k_aux_post2": None, "k_fg_gs<2>": None, "k_pc_fold": None}
+# launches of 3 steps from rest (mean Arnoldi index 12.1 for k_fg_av2 and
+# k_fg_gs<2>); None for a kernel changed since it was measured.
+TRAFFIC_BYTES = {"k_fg_av2": 87.57e6, "k_aux_post2": 68.98e6, "k_fg_gs<2>": 26.17e6,
+                 "k_pc_fold": 17.39e6}
 
 
 def parse():
