@@ -41,8 +41,8 @@
 // FGMRES(mr) with classical Gram-Schmidt (one pass per step, or two when
 // the solver enables re-orthogonalisation); the Hessenberg
 // column, the Givens rotations and the residual estimate are updated on the
-// device by one workgroup per step; the host reads a status block after each
-// batch of steps.  All reductions are fixed-order (block partials reduced by
+// device by one workgroup per step; the host follows a word that it
+// publishes in pinned memory.  All reductions are fixed-order (block partials reduced by
 // one workgroup), so a solve is repeatable bit for bit.
 #pragma once
 
