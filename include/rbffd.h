@@ -203,10 +203,9 @@ rbf_status rbf_ell_apply(int64_t rows, int32_t k, const int32_t *idx, const void
  * widths keep the default shape).  Shapes: block size 64, 128, 256 or
  * 512 threads (one row per thread) x blocks remapped to one contiguous row
  * range per XCD or not x operator loads non-temporal or not.  Without tuning,
- * operators of up to 84 MB run with 64 threads and temporal loads, larger
- * ones with non-temporal loads and 64 (FP64) or 256 (FP32) threads, all
- * remapped.  Every shape sums each row in the
- * same order, so results are bit-identical across shapes.  Each shape runs
+ * blocks are remapped, of 256 threads (64 up to 32,768 rows), and operators
+ * of up to 48 MiB are read with temporal loads.  Every shape sums each row in
+ * the same order, so results are bit-identical across shapes.  Each shape runs
  * once untimed and `reps` times timed with HIP events on `st`; the fastest
  * (the lower shape on ties) is recorded for (dtype, k, rows) in a
  * process-wide table that later rbf_ell_apply calls of that size use.

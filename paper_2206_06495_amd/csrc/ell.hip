@@ -13,6 +13,7 @@
 #include <map>
 #include <mutex>
 #include <tuple>
+#include <type_traits>
 
 #include "common.h"
 
@@ -35,8 +36,8 @@ __device__ __forceinline__ T ell_load(const T *p) {
     else return *p;
 }
 
-constexpr int kEllChunk = 8;
-template <class T, int KT, bool XCD = true, bool NT = true>
+// CH: slots of a generic width whose loads are in flight together.
+template <class T, int KT, bool XCD, bool NT, int CH = 4>
 __global__ void __launch_bounds__(512) k_ell_apply(int64_t rows, int k, const int *__restrict__ idx,
                                                    const T *__restrict__ w, const T *__restrict__ x,
                                                    T *__restrict__ y) {
@@ -44,34 +45,34 @@ __global__ void __launch_bounds__(512) k_ell_apply(int64_t rows, int k, const in
     const int64_t r = (int64_t)lb * blockDim.x + threadIdx.x;
     if (r >= rows) return;
     T acc = T(0);
+    int s0 = 0;
+    auto take = [&](auto count) {  // the next count slots
+        constexpr int C = decltype(count)::value;
+        int jj[C];
+        T ww[C];
+#pragma unroll
+        for (int s = 0; s < C; ++s) jj[s] = ell_load<int, NT>(idx + (int64_t)(s0 + s) * rows + r);
+#pragma unroll
+        for (int s = 0; s < C; ++s) ww[s] = ell_load<T, NT>(w + (int64_t)(s0 + s) * rows + r);
+#pragma unroll
+        for (int s = 0; s < C; ++s) acc = fma_t<T>(ww[s], x[jj[s]], acc);
+        s0 += C;
+    };
     if constexpr (KT > 0) {
-        int jj[KT];
-        T ww[KT];
-#pragma unroll
-        for (int s = 0; s < KT; ++s) jj[s] = ell_load<int, NT>(idx + (int64_t)s * rows + r);
-#pragma unroll
-        for (int s = 0; s < KT; ++s) ww[s] = ell_load<T, NT>(w + (int64_t)s * rows + r);
-#pragma unroll
-        for (int s = 0; s < KT; ++s) acc = fma_t<T>(ww[s], x[jj[s]], acc);
+        take(std::integral_constant<int, KT>{});
     } else {
-        // Chunks of kEllChunk slots with their loads in flight together (10^6 rows
-        // FP64: 32 slots 84.4 -> 77.1 us, 24 slots 62.2 -> 57.4).
-        int s0 = 0;
-        for (; s0 + kEllChunk <= k; s0 += kEllChunk) {
-            int jj[kEllChunk];
-            T ww[kEllChunk];
-#pragma unroll
-            for (int s = 0; s < kEllChunk; ++s)
-                jj[s] = ell_load<int, NT>(idx + (int64_t)(s0 + s) * rows + r);
-#pragma unroll
-            for (int s = 0; s < kEllChunk; ++s)
-                ww[s] = ell_load<T, NT>(w + (int64_t)(s0 + s) * rows + r);
-#pragma unroll
-            for (int s = 0; s < kEllChunk; ++s) acc = fma_t<T>(ww[s], x[jj[s]], acc);
-        }
-        for (; s0 < k; ++s0)
-            acc = fma_t<T>(ell_load<T, NT>(w + (int64_t)s0 * rows + r),
-                           x[ell_load<int, NT>(idx + (int64_t)s0 * rows + r)], acc);
+        // Groups of four keep what a wave gathers from x at once small enough for
+        // its lines to stay in the first-level cache where neighbours lie far
+        // apart: 10^6 rows FP64, 32 wide, columns within 2,000 of the row 130 us
+        // (groups of eight 155), on a lattice 80 (78).  CH = 8 is for few rows, where
+        // the kernel is as long as its chain of round trips (3,600 rows, 32 wide:
+        // 2.8 us, groups of four 3.5).
+        if constexpr (CH == 8)
+            while (s0 + 8 <= k) take(std::integral_constant<int, 8>{});
+        while (s0 + 4 <= k) take(std::integral_constant<int, 4>{});
+        if (k - s0 == 3) take(std::integral_constant<int, 3>{});
+        else if (k - s0 == 2) take(std::integral_constant<int, 2>{});
+        else if (k - s0 == 1) take(std::integral_constant<int, 1>{});
     }
     y[r] = acc;
 }
@@ -215,21 +216,31 @@ __global__ void k_tr_weights(int64_t rows, int64_t nnz, const int *__restrict__ 
 
 // z_c = sum of wt[e] * y[src[e]] over the entries e of column c.  One
 // wavefront per 64 consecutive columns, whose entries are one contiguous
-// range: the wave walks that range in chunks of kTrChunk entries with
+// range: the wave walks that range in chunks of CH entries with
 // coalesced loads (lane l takes entries l, l + 64, ...), writes the
 // products wt[e] * y[src[e]] to LDS, and then every lane adds the products
 // of its own column in entry order.  The order of the additions is fixed
 // by the column structure alone, so results are reproducible bit for bit.
-constexpr int kTrChunk = 512;
+//
+// CH: entries in a chunk.  The weights and sources of the next chunk are loaded
+// before this chunk's products are summed, which only waits for LDS.  512 entries are
+// the shortest chain of round trips (0.02 million columns FP64, 28 wide: 8.7 us, 11.9
+// without the loads ahead); the gathers of y go out four a lane at a time, since more
+// of them push each other's lines out of the first-level cache (10^6 columns FP32 with
+// sources within 2,000 of the column, 45 wide: 154 us, 197 with eight).  In FP64
+// above kTrFew columns 256 entries do the same with half the registers: 10^6
+// columns on a lattice 76.5 us, sources within 2,000 130 (512 entries: 77.3 and 159;
+// without the loads ahead 80 and 139).
 constexpr int kTrWaves = 4;
-template <class T>
+constexpr int64_t kTrFew = 131072;  // two workgroups per CU
+template <class T, int CH>
 __global__ void __launch_bounds__(64 * kTrWaves) k_ell_apply_t(int64_t ncols,
                                                                const int64_t *__restrict__ colptr,
                                                                const int *__restrict__ src,
                                                                const T *__restrict__ wt,
                                                                const T *__restrict__ y,
                                                                T *__restrict__ z) {
-    __shared__ T prod[kTrWaves][kTrChunk];
+    __shared__ T prod[kTrWaves][CH];
     const uint32_t lb = rbf::xcd_block(blockIdx.x, gridDim.x);
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t c0 = ((int64_t)lb * kTrWaves + wv) * 64;
@@ -240,10 +251,7 @@ __global__ void __launch_bounds__(64 * kTrWaves) k_ell_apply_t(int64_t ncols,
     const int64_t b = (c < ncols) ? colptr[c] : E1, e = (c < ncols) ? colptr[c + 1] : E1;
     T *pw = prod[wv];
     T acc = T(0);
-    // The weights and sources of the next chunk are loaded before this chunk's
-    // products are summed, which only waits for LDS (0.09 million columns FP64, 28
-    // wide: 15.6 -> 12.0 us; 10^6: 78.5 -> 77.1, the operator's own stream).
-    constexpr int PER = kTrChunk / 64;
+    constexpr int PER = CH / 64;
     T wv_[PER];
     int sv[PER];
     auto load = [&](int64_t ch) {
@@ -255,11 +263,14 @@ __global__ void __launch_bounds__(64 * kTrWaves) k_ell_apply_t(int64_t ncols,
         }
     };
     if (E0 < E1) load(E0);
-    for (int64_t ch = E0; ch < E1; ch += kTrChunk) {
-        const int64_t n = min((int64_t)kTrChunk, E1 - ch);
+    for (int64_t ch = E0; ch < E1; ch += CH) {
+        const int64_t n = min((int64_t)CH, E1 - ch);
 #pragma unroll
-        for (int q = 0; q < PER; ++q) pw[lane + 64 * q] = wv_[q] * y[sv[q]];
-        if (ch + kTrChunk < E1) load(ch + kTrChunk);
+        for (int q = 0; q < PER; ++q) {
+            pw[lane + 64 * q] = wv_[q] * y[sv[q]];
+            if (q % 4 == 3) asm volatile("" ::: "memory");
+        }
+        if (ch + CH < E1) load(ch + CH);
         __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS writes are done
         __builtin_amdgcn_wave_barrier();
         int i = (int)(max(b, ch) - ch);
@@ -294,28 +305,34 @@ constexpr EllShape kShapes[kEllShapes] = {
     {256, true, false},  {64, true, false},  {128, true, false},  {512, true, false},
     {256, false, false}, {64, false, false}, {128, false, false}, {512, false, false}};
 
+constexpr int64_t kEllTemporal = (int64_t)48 << 20;  // bytes of an operator
+
 // Tuned shapes, per (dtype, k, rows) (process-wide).
 std::mutex g_tune_mu;
 std::map<std::tuple<int, int, int64_t>, int> g_tuned;
 
-// Whether an operator is read with temporal loads by default: where several of
-// its size fit the 256 MB last-level cache together, so that a program that goes
-// through a few of them finds each there again (0.25 million rows FP64, three
-// operators in turn: 17.3 us with non-temporal loads, 15.6 with temporal ones).
-// Larger ones push each other out, and temporal loads then cost more: 10^6 rows
-// FP32, three operators in turn, 45.7 and 52.7 us.
+// Whether an operator is read with temporal loads by default: up to 48 MiB, of which the
+// 256 MB last-level cache holds five, so that a program that goes through a few of them
+// finds each there again, and one that goes through more loses little (28 wide FP64, 50
+// MB: three in turn 14.4 us with non-temporal loads, 11.6 with temporal ones, eight
+// 13.8 and 14.1).  Larger ones lose more than they gain as soon as they push each
+// other out: 84 MB, three in turn 19.3 and 15.1 us, four 17.6 and 19.8; one of 224 MB
+// alone 48 and 37 us (FP32, 10^6 rows), three 47.5 and 52.2.
 bool ell_temporal(int dtype, int k, int64_t rows) {
-    return rows * k * (dtype == 0 ? 12 : 8) <= (int64_t)84 << 20;
+    return rows * k * (dtype == 0 ? 12 : 8) <= kEllTemporal;
 }
 
-// Shape of the 28-wide product: tuned, else 64 threads (65.5 against 66.3 us at 10^6
-// rows FP64, 2.6 against 3.3 at 3,600) with the remap and the load kind above; 256
-// threads for FP32 operators above that size (10^6 rows: 46.0 us with 64, 45.85).
+// Shape of the 28-wide product: tuned, else the remap with the load kind above and 256
+// threads, whose waves share a first-level cache on neighbouring rows (10^6 rows FP64
+// with columns within 500 of the row: 70 us, 97 with 64 threads; on a lattice 69 and 66);
+// 64 threads where blocks of 256 would leave half of the CUs idle (3,600 rows: 2.4
+// against 3.8 us; 50,000 rows with columns within 500 6.2 against 5.1).
+constexpr int64_t kEllFew = 32768;
 int tuned_shape(int dtype, int k, int64_t rows) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tuned.find(std::make_tuple(dtype, k, rows));
     if (it != g_tuned.end()) return it->second;
-    return ell_temporal(dtype, k, rows) ? 9 : dtype == 0 ? 1 : 0;
+    return rows <= kEllFew ? 9 : ell_temporal(dtype, k, rows) ? 8 : 0;
 }
 
 template <class T>
@@ -418,16 +435,19 @@ extern "C" rbf_status rbf_ell_apply(int64_t rows, int32_t k, const int32_t *idx,
         RBF_CHECK_LAUNCH();
         return RBF_OK;
     }
-    const dim3 grid(rbf::blocks_for(rows, 64)), block(64);
-#define RBF_ELL(T, NTL)                                                                            \
-    hipLaunchKernelGGL((k_ell_apply<T, 0, true, NTL>), grid, block, 0, st, rows, k, idx,            \
-                       static_cast<const T *>(w), static_cast<const T *>(x), static_cast<T *>(y))
-    const bool nt = !ell_temporal(dtype, k, rows);
-    if (dtype == 0 && nt) RBF_ELL(double, true);
-    else if (dtype == 0) RBF_ELL(double, false);
-    else if (nt) RBF_ELL(float, true);
-    else RBF_ELL(float, false);
-#undef RBF_ELL
+    auto run = [&](auto t) {
+        using T = decltype(t);
+        auto go = [&](auto kernel, int bs) {
+            hipLaunchKernelGGL(kernel, dim3(rbf::blocks_for(rows, bs)), dim3(bs), 0, st, rows, k, idx,
+                               static_cast<const T *>(w), static_cast<const T *>(x),
+                               static_cast<T *>(y));
+        };
+        if (rows <= kEllFew) go(k_ell_apply<T, 0, true, false, 8>, 64);
+        else if (ell_temporal(dtype, k, rows)) go(k_ell_apply<T, 0, true, false>, 256);
+        else go(k_ell_apply<T, 0, true, true>, 256);
+    };
+    if (dtype == 0) run(double{});
+    else run(float{});
     RBF_CHECK_LAUNCH();
     return RBF_OK;
 }
@@ -548,12 +568,15 @@ extern "C" rbf_status rbf_ell_apply_transpose(int64_t ncols, const int64_t *colp
     RBF_ARG(colptr && z, "rbf_ell_apply_transpose: NULL pointer");
     hipStream_t st = rbf::as_stream(st_);
     const dim3 grid(rbf::blocks_for(ncols, 64 * kTrWaves)), block(64 * kTrWaves);
-    if (dtype == 0)
-        hipLaunchKernelGGL(k_ell_apply_t<double>, grid, block, 0, st, ncols, colptr, src,
+    auto fp64 = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, ncols, colptr, src,
                            static_cast<const double *>(wt), static_cast<const double *>(y),
                            static_cast<double *>(z));
+    };
+    if (dtype == 0 && ncols <= kTrFew) fp64(k_ell_apply_t<double, 512>);
+    else if (dtype == 0) fp64(k_ell_apply_t<double, 256>);
     else
-        hipLaunchKernelGGL(k_ell_apply_t<float>, grid, block, 0, st, ncols, colptr, src,
+        hipLaunchKernelGGL((k_ell_apply_t<float, 512>), grid, block, 0, st, ncols, colptr, src,
                            static_cast<const float *>(wt), static_cast<const float *>(y),
                            static_cast<float *>(z));
     RBF_CHECK_LAUNCH();
