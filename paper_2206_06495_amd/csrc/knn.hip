@@ -10,8 +10,8 @@
 // the sources by cell), then one thread per query (k_query): the cells that
 // cover a square of half-width R around it, R from the density of the 5 x 5
 // cells there, are scanned row by row (the sources of neighbouring cells of a
-// row are contiguous); when the k-th distance exceeds R, again with R raised
-// to it, which is then final.
+// row are contiguous), R being raised until they hold k; when the k-th distance
+// exceeds R, again with R raised to it, which is then final.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -22,17 +22,11 @@
 namespace {
 
 // Cell grid, made on the device (k_grid).  err: 1 non-finite sources, 2
-// non-finite queries (nothing is searched then).  left: queries that k_query
-// left to k_query_general.
+// non-finite queries (nothing is searched then).
 struct Grid {
     double x0, y0, c, inv_c;
     int gx, gy, err;
-    unsigned left;
 };
-
-__device__ __forceinline__ bool key_less(double d, int i, double bd, int bi) {
-    return d < bd || (d == bd && i < bi);
-}
 
 __device__ __forceinline__ int cell_coord(double v, double v0, double inv_c, int g) {
     const double t = floor((v - v0) * inv_c);
@@ -237,49 +231,64 @@ __device__ __forceinline__ double dist2(double2 s, double qx, double qy) {
 }
 
 // Calls f(p, |s_p - q|^2) for every source p of the cells x0..x1, y0..y1; the
-// next row's range is loaded while a row is scanned.
-template <class F>
+// next row's range and the next U sources are loaded while these are looked at.
+template <int U, class F>
 __device__ __forceinline__ void scan_cells(const int *__restrict__ start,
                                            const double2 *__restrict__ sxy, int gx, int x0, int x1,
                                            int y0, int y1, double qx, double qy, F f) {
     int64_t row = (int64_t)y0 * gx;
     int pa = start[row + x0], pb = start[row + x1 + 1];
     for (int y = y0; y <= y1; ++y) {
-        row += gx;
-        const int64_t nrow = (y < y1) ? row : row - gx;
-        const int na = start[nrow + x0], nb = start[nrow + x1 + 1];
-        int p = pa;
-        for (; p + 1 < pb; p += 2) {
-            const double2 s0 = sxy[p], s1 = sxy[p + 1];
-            f(p, dist2(s0, qx, qy));
-            f(p + 1, dist2(s1, qx, qy));
+        if (y < y1) row += gx;
+        const int na = start[row + x0], nb = start[row + x1 + 1];
+        if (pa < pb) {
+            int p = pa;
+            double2 s[U], t[U];
+            auto load = [&](double2(&v)[U], int at) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = sxy[min(at + u, pb - 1)];
+            };
+            load(s, p);
+            for (; p + U <= pb; p += U) {
+                load(t, p + U);
+#pragma unroll
+                for (int u = 0; u < U; ++u) f(p + u, dist2(s[u], qx, qy));
+#pragma unroll
+                for (int u = 0; u < U; ++u) s[u] = t[u];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (p + u < pb) f(p + u, dist2(s[u], qx, qy));
         }
-        if (p < pb) f(p, dist2(sxy[p], qx, qy));
         pa = na;
         pb = nb;
     }
 }
 
-// One query per thread, k <= KMAX.  Pass A keeps the KMAX smallest squared
+// One query per thread, k <= KMAX.  `nearest` keeps the KMAX smallest squared
 // distances, sorted, in registers: each candidate goes through one min/max
-// chain (two instructions per entry, no indices).  Pass B lists the sources
-// within the k-th distance (LDS), and each goes to the place that the number of
-// smaller distances gives; equal distances are inserted by index.
-// A query with more sources than the list holds (many at one distance) is left
-// to k_query_general: its first entry is set to -1 and counted.
-// Bound by the instructions of the chain.  10^6 queries, k = 28: 452 us; an
-// insertion of (distance, index) pairs by compare and select, ring by ring,
-// took 1,928 us (5,700 queries: 82 against 326 us).
+// chain (two instructions per entry, no indices).  Then the sources
+// within the k-th distance are listed (LDS), and each goes to the place that the number
+// of smaller distances gives; equal distances are inserted by index.
+// The chain's instructions take most of the time on even sets: 10^6 queries,
+// k = 28: 452 us; an insertion of (distance, index) pairs by compare and select,
+// ring by ring, took 1,928 us (5,700 queries: 82 against 326 us).  On uneven sets, where
+// a cell holds thousands of sources, it is the latency of the loads: hence those of
+// the next U sources ahead, and a second pass only over a window that holds more
+// sources (30,000 sources normal^3, 10,000 queries, whole call: k = 28 4.0 ms,
+// k = 64 11.9; two sources ahead and every window again in full 5.4 and 15.4; ring
+// by ring 4.2 and 13.4).
 constexpr int kQueryT = 64, kListMore = 12;
 template <int KMAX>
 __global__ void __launch_bounds__(kQueryT) k_query(const double *__restrict__ xq, int64_t nq, int k,
-                                                   Grid *__restrict__ gp,
+                                                   const Grid *__restrict__ gp,
                                                    const int *__restrict__ start,
                                                    const double2 *__restrict__ sxy,
                                                    const int *__restrict__ sid,
                                                    int *__restrict__ idx) {
     constexpr int CAP = KMAX + kListMore;
     constexpr int kEmpty = 255;
+    constexpr int U = KMAX <= 48 ? 4 : 3;  // 10^6 queries, k = 64: 1,955 us, 2,105 with 4
     __shared__ int list[CAP][kQueryT];             // accepted sources, then their indices
     __shared__ unsigned char place[KMAX][kQueryT];  // list entry at each place of the stencil
     static_assert(CAP < kEmpty, "list entries are numbered in bytes");
@@ -288,18 +297,24 @@ __global__ void __launch_bounds__(kQueryT) k_query(const double *__restrict__ xq
     if (q >= nq || g.err) return;
     const int t = threadIdx.x;
     const double qx = xq[q], qy = xq[nq + q];
-    int x0, x1, y0, y1;  // cells scanned
-    double R;
+    int x0, x1, y0, y1;  // cells scanned: the window
+    auto count = [&]() {  // sources in them
+        int n = 0;
+        for (int y = y0; y <= y1; ++y)
+            n += start[(int64_t)y * g.gx + x1 + 1] - start[(int64_t)y * g.gx + x0];
+        return n;
+    };
+    double out, r;  // distance to the box of the grid; reach of the window into it
     {
         // Radius of 1.5 k sources at the density of the 5 x 5 cells here.
         const int cx = cell_coord(qx, g.x0, g.inv_c, g.gx), cy = cell_coord(qy, g.y0, g.inv_c, g.gy);
         x0 = max(cx - 2, 0), x1 = min(cx + 2, g.gx - 1);
         y0 = max(cy - 2, 0), y1 = min(cy + 2, g.gy - 1);
-        int n = 0;
-        for (int y = y0; y <= y1; ++y)
-            n += start[(int64_t)y * g.gx + x1 + 1] - start[(int64_t)y * g.gx + x0];
+        const int n = count();
         const double cells = (double)((x1 - x0 + 1) * (y1 - y0 + 1));
-        R = g.c * sqrt(1.5 / M_PI * (double)k * cells / (double)max(n, 1));
+        r = g.c * sqrt(1.5 / M_PI * (double)k * cells / (double)max(n, 1));
+        out = fmax(fmax(g.x0 - qx, qx - (g.x0 + g.gx * g.c)), fmax(g.y0 - qy, qy - (g.y0 + g.gy * g.c)));
+        out = (out > 0.0) ? out : 0.0;
     }
     double bd[KMAX], T;
     // Cells that hold every source within r (with a margin for rounding;
@@ -309,12 +324,14 @@ __global__ void __launch_bounds__(kQueryT) k_query(const double *__restrict__ xq
         x0 = cell_coord(qx - m, g.x0, g.inv_c, g.gx), x1 = cell_coord(qx + m, g.x0, g.inv_c, g.gx);
         y0 = cell_coord(qy - m, g.y0, g.inv_c, g.gy), y1 = cell_coord(qy + m, g.y0, g.inv_c, g.gy);
     };
-    for (;;) {
-        window(R);
+    int n;
+    // The smallest squared distances of the window's sources, of those below limit; n
+    // sources seen, T the k-th.
+    auto nearest = [&](double limit) {
 #pragma unroll
-        for (int s = 0; s < KMAX; ++s) bd[s] = INFINITY;
-        int n = 0;
-        scan_cells(start, sxy, g.gx, x0, x1, y0, y1, qx, qy, [&](int, double d) {
+        for (int s = 0; s < KMAX; ++s) bd[s] = limit;
+        n = 0;
+        scan_cells<U>(start, sxy, g.gx, x0, x1, y0, y1, qx, qy, [&](int, double d) {
             ++n;
             if (d < bd[KMAX - 1]) {
 #pragma unroll
@@ -325,26 +342,55 @@ __global__ void __launch_bounds__(kQueryT) k_query(const double *__restrict__ xq
         T = bd[KMAX - 1];
 #pragma unroll
         for (int s = 0; s < KMAX - 1; ++s) T = (s == k - 1) ? bd[s] : T;
-        // Final when every source outside is farther than T: R^2 must be in the
-        // normal range for that, else all cells are scanned.
-        const double R2 = R * R;
-        const bool all = x0 == 0 && y0 == 0 && x1 == g.gx - 1 && y1 == g.gy - 1;
-        if (all || (n >= k && T <= R2 && T < INFINITY && R2 > 1e-290)) break;
-        if (n < k) R *= 1.5;
-        else R = (T < INFINITY && T > 1e-290) ? fmax(sqrt(T) * (1.0 + 1e-15), R) : INFINITY;
+    };
+    auto all = [&]() { return x0 == 0 && y0 == 0 && x1 == g.gx - 1 && y1 == g.gy - 1; };
+    // A query outside the box whose window is most of it takes all of it, so that the
+    // queries of a wave read the same sources together (30,000 normal sources, queries ten
+    // box sides away: 4.0 ms, up to 11 with windows of their own).
+    auto widen = [&]() {
+        if (out > 0.0 && 2 * (int64_t)(x1 - x0 + 1) * (y1 - y0 + 1) > (int64_t)g.gx * g.gy)
+            x0 = y0 = 0, x1 = g.gx - 1, y1 = g.gy - 1;
+    };
+    // Until k sources are in the window.  (The queries of a wave reach the second part
+    // together: windows grown by each in its own pass cost them one another's.)
+    double R = out + r;
+    window(R);
+    for (;;) {
+        nearest(INFINITY);
+        if (n >= k || all()) break;
+        do {
+            R = out + (r *= 1.1);
+            window(R);
+        } while (count() < k && !all());
     }
-    if (T < INFINITY && T > 1e-290) window(sqrt(T) * (1.0 + 1e-15));
-    int n = 0;
-    scan_cells(start, sxy, g.gx, x0, x1, y0, y1, qx, qy, [&](int p, double d) {
+    // Final when every source outside is farther than T: R^2 must be in the normal
+    // range for that.  Else again with the cells that cover T (all where that cannot
+    // be told) if they hold more, with only what is nearer than (1 + 1e-15) T of
+    // interest.
+    if (!all() && !(T <= R * R && T < INFINITY && R * R > 1e-290)) {
+        const bool known = T < INFINITY && T > 1e-290;
+        window(known ? fmax(sqrt(T) * (1.0 + 1e-15), R) : INFINITY);
+        widen();
+        if (count() > n) nearest(known ? T * (1.0 + 1e-15) : INFINITY);
+    }
+    // (Where T is below 1e-290: a difference above its root has a larger square.)
+    if (T < INFINITY) window(sqrt(fmax(T, 1e-290)) * (1.0 + 1e-15));
+    widen();
+    n = 0;
+    scan_cells<U>(start, sxy, g.gx, x0, x1, y0, y1, qx, qy, [&](int p, double d) {
         if (d <= T) {
             if (n < CAP) list[n][t] = p;
             ++n;
         }
     });
-    if (n > CAP) {
-        idx[q] = -1;
-        atomicAdd(&gp->left, 1u);
-        return;
+    // More than the list holds, many at the k-th distance: the nearer ones, fewer than
+    // k, are listed again; of those at it the lowest indices follow below.
+    const bool over = n > CAP;
+    if (over) {
+        n = 0;
+        scan_cells<U>(start, sxy, g.gx, x0, x1, y0, y1, qx, qy, [&](int p, double d) {
+            if (d < T) list[n++][t] = p;
+        });
     }
     bool tie = n > k;
 #pragma unroll
@@ -383,90 +429,25 @@ __global__ void __launch_bounds__(kQueryT) k_query(const double *__restrict__ xq
             }
         }
     }
+    const int m = min(n, k);
 #pragma unroll 1
-    for (int s = 0; s < k; ++s) idx[(int64_t)s * nq + q] = list[place[s][t]][t];
-}
-
-// The same search for the queries that k_query left (idx[q] = -1): square rings
-// of cells outward, the best k candidates as a list of (distance, index) sorted
-// by insertion.
-template <int KMAX>
-__global__ void __launch_bounds__(128) k_query_general(const double *__restrict__ xq, int64_t nq,
-                                                       int k, const Grid *__restrict__ gp,
-                                                       const int *__restrict__ start,
-                                                       const double2 *__restrict__ sxy,
-                                                       const int *__restrict__ sid,
-                                                       int *__restrict__ idx) {
-    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (q >= nq || idx[q] != -1) return;
-    const Grid g = *gp;
-    const double qx = xq[q], qy = xq[nq + q];
-    const int cx = cell_coord(qx, g.x0, g.inv_c, g.gx);
-    const int cy = cell_coord(qy, g.y0, g.inv_c, g.gy);
-    double bd[KMAX];
-    int bi[KMAX];
+    for (int s = 0; s < m; ++s) idx[(int64_t)s * nq + q] = list[place[s][t]][t];
+    if (!over) return;
+    int id[KMAX];  // the lowest indices at distance T, sorted
 #pragma unroll
-    for (int s = 0; s < KMAX; ++s) {
-        bd[s] = INFINITY;
-        bi[s] = INT_MAX;
-    }
-    double thr_d = INFINITY;
-    int thr_i = INT_MAX;
-    const int rmax = max(max(cx, g.gx - 1 - cx), max(cy, g.gy - 1 - cy));
-    for (int r = 0; r <= rmax; ++r) {
-        const int ylo = cy - r, yhi = cy + r;
-        for (int iy = max(ylo, 0); iy <= min(yhi, g.gy - 1); ++iy) {
-            const bool full_row = (iy == ylo) || (iy == yhi);
-            const int step = full_row ? 1 : 2 * r;
-            for (int ix = cx - r; ix <= cx + r; ix += (step > 0 ? step : 1)) {
-                if (ix < 0 || ix >= g.gx) continue;
-                const int c = iy * g.gx + ix;
-                const int pe = start[c + 1];
-                for (int p = start[c]; p < pe; ++p) {
-                    const double d2 = dist2(sxy[p], qx, qy);
-                    const int id = sid[p];
-                    if (!key_less(d2, id, thr_d, thr_i)) continue;
-                    // Sorted insertion; the former last entry drops out.
+    for (int s = 0; s < KMAX; ++s) id[s] = INT_MAX;
+    scan_cells<U>(start, sxy, g.gx, x0, x1, y0, y1, qx, qy, [&](int p, double d) {
+        if (d != T) return;
+        const int i = sid[p];
+        if (i < id[KMAX - 1]) {
 #pragma unroll
-                    for (int s = KMAX - 1; s > 0; --s) {
-                        const bool before_prev = key_less(d2, id, bd[s - 1], bi[s - 1]);
-                        const bool before_cur = key_less(d2, id, bd[s], bi[s]);
-                        if (before_prev) {
-                            bd[s] = bd[s - 1];
-                            bi[s] = bi[s - 1];
-                        } else if (before_cur) {
-                            bd[s] = d2;
-                            bi[s] = id;
-                        }
-                    }
-                    if (key_less(d2, id, bd[0], bi[0])) {
-                        bd[0] = d2;
-                        bi[0] = id;
-                    }
-#pragma unroll
-                    for (int s = 0; s < KMAX; ++s)
-                        if (s == k - 1) {
-                            thr_d = bd[s];
-                            thr_i = bi[s];
-                        }
-                }
-                if (step == 0) break;
-            }
+            for (int s = KMAX - 1; s > 0; --s) id[s] = min(id[s], max(id[s - 1], i));
+            id[0] = min(id[0], i);
         }
-        if (thr_d == INFINITY) continue;  // fewer than k candidates so far
-        // Distance from the query to the nearest cell outside the block.
-        double bound = INFINITY;
-        if (cx - r > 0) bound = fmin(bound, qx - (g.x0 + (double)(cx - r) * g.c));
-        if (cx + r < g.gx - 1) bound = fmin(bound, (g.x0 + (double)(cx + r + 1) * g.c) - qx);
-        if (cy - r > 0) bound = fmin(bound, qy - (g.y0 + (double)(cy - r) * g.c));
-        if (cy + r < g.gy - 1) bound = fmin(bound, (g.y0 + (double)(cy + r + 1) * g.c) - qy);
-        if (bound == INFINITY) break;
-        bound -= 1e-9 * g.c;  // margin for the rounding of cell assignment
-        if (bound > 0.0 && thr_d < bound * bound) break;
-    }
+    });
 #pragma unroll
     for (int s = 0; s < KMAX; ++s)
-        if (s < k) idx[(int64_t)s * nq + q] = bi[s];
+        if (m + s < k) idx[(int64_t)(m + s) * nq + q] = id[s];
 }
 
 // Device buffers of one kNN call besides its inputs and output.
@@ -508,7 +489,7 @@ rbf_status knn_check_args(const double *xq, int64_t nq, const double *xs, int64_
 }
 
 // Cell grid, counting sort of the sources by cell, then the queries; one
-// synchronisation at the end (two when queries are left to k_query_general).
+// synchronisation at the end.
 rbf_status knn_search(const double *xq, int64_t nq, const double *xs, int64_t ns, int32_t k,
                       int32_t *idx, hipStream_t st, const KnnScratch &s) {
     const int64_t ncell = max_cells(ns);
@@ -534,15 +515,6 @@ rbf_status knn_search(const double *xq, int64_t nq, const double *xs, int64_t ns
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(&g, s.grid, sizeof(g), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e == hipSuccess && !g.err && g.left > 0) {
-        const dim3 gg(rbf::blocks_for(nq, 128)), bg(128);
-        if (k <= 32)
-            hipLaunchKernelGGL(k_query_general<32>, gg, bg, 0, st, xq, nq, k, s.grid, s.start, s.sxy, s.sid, idx);
-        else
-            hipLaunchKernelGGL(k_query_general<64>, gg, bg, 0, st, xq, nq, k, s.grid, s.start, s.sxy, s.sid, idx);
-        e = hipGetLastError();
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-    }
     if (e != hipSuccess) {
         rbf::set_error("rbf_knn: %s", hipGetErrorString(e));
         return RBF_E_DEVICE;
