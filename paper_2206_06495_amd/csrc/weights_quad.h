@@ -38,14 +38,13 @@
 // V-nodes at h = 1/400).  A two-part split with 24 bits each left up to 1.9 times
 // that error.
 //
-// Measured (10^6 V-nodes, D_x, D_y, Lap): 5.3 ms against 18.3 ms of
+// Measured (10^6 V-nodes, D_x, D_y, Lap): 5.2 ms against 18.3 ms of
 // k_weights_pair; bound by FP64 instruction issue, about 6,600 instructions per
 // wavefront of four systems (4,068 per system before).
 //
 // A system that is not clearly definite on these pivots (coincident nodes,
 // nodes on a cubic curve, non-finite coordinates, an index out of range) is
-// left to the pivoted kernels: its first weight is set to NaN and counted in
-// *todo.
+// left to the pivoted kernels: its first weight is set to NaN, and *todo to 1.
 
 constexpr int kQuadTri = kPairN * (kPairN - 1) / 2;  // 378 pairs of nodes
 
@@ -263,6 +262,17 @@ k_weights_quad(const double *__restrict__ xq, int64_t nq, const double *__restri
     const bool valid = row_ < nq;
     const int64_t row = valid ? row_ : nq - 1;
     bool suspect = false;
+    auto leave = [&]() {
+        w[row] = NAN;  // slot 0 of the first operator marks the row
+        // (Looked at first: 160,000 rows that all add to it take 1.5 ms.)
+        if (__hip_atomic_load(todo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0)
+            __hip_atomic_store(todo, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto all_left = [&]() {
+        unsigned long long sm = __ballot(suspect);
+        sm |= sm >> 8, sm |= sm >> 4, sm |= sm >> 2, sm |= sm >> 1;
+        return (sm & 0x0001000100010001ull) == 0x0001000100010001ull;
+    };
 
     // Stencil nodes l and 16 + l, shifted and scaled by a power of two.
     const bool has1 = l < N - 16;
@@ -335,17 +345,6 @@ k_weights_quad(const double *__restrict__ xq, int64_t nq, const double *__restri
     // coordinates again is, instead of being kept in registers.
 #define QUAD_STEP() \
     asm volatile("" : "+v"(x0), "+v"(y0), "+v"(x1), "+v"(y1), "+v"(r0), "+v"(r1) : : "memory")
-    // A, one evaluation per pair (24 rounds of 16 pairs).
-#pragma unroll 4
-    for (int e0 = 0; e0 < kQuadTri; e0 += 16) {
-        const unsigned ij = kPairs.v[e0 + l];
-        const double2 ci = S.c[ij >> 8], cj = S.c[ij & 255];
-        const double dx = ci.x - cj.x, dy = ci.y - cj.y;
-        const double dd = dx * dx + dy * dy;
-        S.a[e0 + l] = ((dd * dd) * dd) * sqrt_normal(dd);
-    }
-
-    QUAD_STEP();
     // 2. P_B = L U in slot 0 (rows 10 and 11 are eliminated along).
     double p0[KP], m[KP], myui = 0.0;
     quad_mono(x0, y0, p0);
@@ -362,6 +361,24 @@ k_weights_quad(const double *__restrict__ xq, int64_t nq, const double *__restri
         p0[k] = (l > k) ? lk : p0[k];
         fmac_self<k, KP - 1 - k>(p0 + k + 1, nl);
     });
+    // A wavefront whose four systems are all left ends here: where all rows are (nodes
+    // squeezed to 1:100), a call with 160,000 takes 3.07 ms, 3.85 if they run to the end,
+    // and 2.98 without this kernel.
+    if (all_left()) {
+        if (valid && l == 0) leave();
+        return;
+    }
+    // A, one evaluation per pair (24 rounds of 16 pairs).
+#pragma unroll 4
+    for (int e0 = 0; e0 < kQuadTri; e0 += 16) {
+        const unsigned ij = kPairs.v[e0 + l];
+        const double2 ci = S.c[ij >> 8], cj = S.c[ij & 255];
+        const double dx = ci.x - cj.x, dy = ci.y - cj.y;
+        const double dd = dx * dx + dy * dy;
+        S.a[e0 + l] = ((dd * dd) * dd) * sqrt_normal(dd);
+    }
+
+    QUAD_STEP();
     // Columns of P_B^-1: lane k < 10 holds column k.
     double v[KP];
 #pragma unroll
@@ -689,15 +706,12 @@ k_weights_quad(const double *__restrict__ xq, int64_t nq, const double *__restri
         wf1[o] = ldexp(wf1[o] + ws1[o], -e * ops.order[o]);
         finite = finite && isfinite(wf0[o]) && isfinite(wf1[o]);
     }
-    const unsigned long long sm = __ballot(suspect || !finite);
-    const bool redo = (sm >> (lane & 48) & 0xffffull) != 0;
+    suspect = suspect || !finite;
+    const bool redo = (__ballot(suspect) >> (lane & 48) & 0xffffull) != 0;
     if (!valid) return;
     const int n0 = S.node[r0], n1 = S.node[r1];
     if (redo) {
-        if (l == 0) {
-            w[row] = NAN;  // slot 0 of the first operator marks the row
-            atomicAdd(todo, 1ull);
-        }
+        if (l == 0) leave();
         return;
     }
 #pragma unroll
