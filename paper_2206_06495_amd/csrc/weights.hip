@@ -298,8 +298,9 @@ __device__ __forceinline__ void weights_system(const double *__restrict__ xq, in
     const int s = n + kp;
     const int nops = FIXED ? NOPS : ops.n;
     // marked: only rows whose first weight is NaN get weights (the others have
-    // theirs from k_weights_quad); the estimate is made for every row.
-    const bool solve = !marked || isnan(w[row]);
+    // theirs from k_weights_quad, which takes fixed forms only); the estimate is made
+    // for every row.
+    const bool solve = !FIXED || !marked || isnan(w[row]);
 
     // 1. Stencil in shifted coordinates; exact power-of-two scaling.
     // A stencil index outside [0, ns) marks the row bad before any load
@@ -971,7 +972,7 @@ extern "C" rbf_status rbf_assemble_weights(const double *xq, int64_t nq, const d
         }
     }
     hipStream_t st = rbf::as_stream(st_);
-    unsigned long long *dbad = nullptr;  // lowest bad row, rows left by k_weights_quad
+    unsigned long long *dbad = nullptr;  // lowest bad row, whether k_weights_quad left any
     RBF_HIP(hipMalloc(&dbad, 2 * sizeof(unsigned long long)));
     const unsigned long long init[2] = {~0ull, 0};
     unsigned long long hb[2] = {~0ull, 0};
