@@ -63,6 +63,14 @@ __device__ __forceinline__ T ld_stream(const T *p) {
     return __builtin_nontemporal_load(p);
 }
 
+// Order of LDS accesses among the lanes of one wavefront, which its LDS instructions
+// keep by themselves: no wait and no barrier, so other waves of the workgroup need not
+// reach it (nor be alive).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Store to pinned host memory, past the caches, for a host that polls it.
 __device__ __forceinline__ void publish(uint64_t *p, uint64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);

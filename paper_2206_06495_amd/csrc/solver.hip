@@ -872,7 +872,8 @@ constexpr int kTriChunk = 8;  // rows per lane: n <= 64 kTriChunk (K <= 513)
 
 // One wavefront's solve of mode k: sz holds the row of T (this lane's entries are
 // summed in tsum), vv[m] V at entry lane + 64 m.  At most TC rows per lane and 64 NM
-// entries.
+// entries.  The wave orders its LDS accesses by itself: the others of a workgroup may
+// have ended.
 template <class TP, int TC, int NM>
 __device__ __forceinline__ void pc_tri_mode(const Lat &L, int k, int lane, double *sz, double tsum,
                                             const double (&vv)[NM], double lamk) {
@@ -883,7 +884,7 @@ __device__ __forceinline__ void pc_tri_mode(const Lat &L, int k, int lane, doubl
         shift = rbf::wave_sum(tsum) / n;
         if (lane == 0) *L.mean = shift;
     }
-    __syncthreads();
+    rbf::wave_sync();
     const double h2 = L.h * L.h;
     const int nch = min(64, max(1, size / 2));
     const int base = size > 0 ? size / nch : 0, extra = size > 0 ? size % nch : 0;
@@ -975,7 +976,7 @@ __device__ __forceinline__ void pc_tri_mode(const Lat &L, int k, int lane, doubl
     const double x0 = D / B;
     const double xn = __shfl(x0, lane < 63 ? lane + 1 : lane, 64);
     const double xl = fd - fa * x0 - fc * xn;
-    __syncthreads();
+    rbf::wave_sync();
     if (k == 0 && lane == 0) sz[n - 1] = 0.0;  // the dropped last unknown of mode 0
 #pragma unroll
     for (int j = 0; j < TC; ++j) {
@@ -984,7 +985,7 @@ __device__ __forceinline__ void pc_tri_mode(const Lat &L, int k, int lane, doubl
             sz[r0 + j] = z;
         }
     }
-    __syncthreads();
+    rbf::wave_sync();
     double zmean = 0.0;
     if (k == 0) {
         double s = 0.0;
