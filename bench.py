@@ -12,7 +12,7 @@ Workload (one JSON line on stdout):
     (node-steps/s).
   * roofline of the dominant kernel of the step (the longest of the sampled
     pressure-solve kernels: the FGMRES product k_fg_av2, the smoothing product
-    k_aux_post2, the Gram-Schmidt update k_fg_gs<2>, the auxiliary
+    k_aux_post2, the Gram-Schmidt update k_fg_gs (reported as k_fg_gs<2>), the auxiliary
     lattice transform k_pc_fold), its average duration sampled with the
     launch's own start/end stamps on the solver's stream during the timed
     steps, against its algorithmic bytes per launch.

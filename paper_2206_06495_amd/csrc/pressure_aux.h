@@ -7,9 +7,9 @@
 //   A x = S A0 x + u1 c (1^T x),   S the row scale, u1 = S chi, c = vscale,
 // A0: D_Lap^PP on interior rows, n . grad on wall rows (see k_build_poisson).
 //
-// Preconditioner z = B^-1 y (one application; kAuxSweeps smoothing sweeps
-// on each side of the lattice correction):
-//   x1 = W y, then x1 += W (y - A_s x1)  (kAuxSweeps sweeps from 0)
+// Preconditioner z = B^-1 y (one application; two smoothing sweeps on each
+// side of the lattice correction, the second of each pair weighted by w2):
+//   x1 = W y, then x1 += w2 W (y - A_s x1)
 //                                 W = omega / (l1 norm of A's rows)
 //   r1 = y - A_s x1               A_s: the sparse part of A
 //   g  = R (S^-1 r1)              R: normalised bilinear restriction of the
@@ -26,9 +26,9 @@
 //                                 mu = (lam / c - sum J e) / m carries the
 //                                 border's constant (the exact form for the
 //                                 bordered operator A0 + chi c 1^T)
-//   z  = x2, then z += W (y - A_s z)   (kAuxSweeps post-smoothing sweeps)
-// The auxiliary lattice is coarser than the nodes (about two node spacings
-// per cell): the smoother removes what the lattice cannot represent, the
+//   z  = x2 + W (y - A_s x2), then z += w2 W (y - A_s z)
+// The auxiliary lattice has about one node spacing per cell: the smoother
+// removes what the lattice cannot represent, the
 // lattice solve removes the smooth error the smoother cannot.  A_s 1 = 0
 // (the rows reproduce constants), so mu needs no product.
 //
@@ -38,8 +38,11 @@
 // FP32-stored weights, vectors and transforms with FP64 dot products, and
 // the correction is added to the FP64 iterate).
 //
-// FGMRES(mr) with classical Gram-Schmidt (one pass per step, or two when
-// the solver enables re-orthogonalisation); the Hessenberg
+// FGMRES(mr) with classical Gram-Schmidt, one pass per step: a second one took the same
+// number of steps to the same true residual on the h = 1/400 cavity and the cylinder
+// (32.3 and 35.2 per time step) for a reduction and a pass over the basis more, and
+// convergence is only declared from the true residual recomputed at a restart, so a
+// loss of orthogonality can cost steps but not accuracy.  The Hessenberg
 // column, the Givens rotations and the residual estimate are updated on the
 // device by one workgroup per step; the host follows a word that it
 // publishes in pinned memory.  All reductions are fixed-order (block partials reduced by
@@ -59,11 +62,9 @@ constexpr double kAuxOmega = 2.0;
 // or less of it).
 constexpr double kAuxBorder = 0.1;
 constexpr double kMixedInner = 1e-4;  // mixed: per-cycle residual reduction
-// Smoothing sweeps before and after the lattice correction.  Two each cost
-// two more products per FGMRES step and cut the steps per solve by about a
-// third (h = 1/100, rtol 1e-10: 71 steps with one sweep, 48 with two, 39
-// with three).
-constexpr int kAuxSweeps = 2;
+// (Two smoothing sweeps on each side cost two more products per FGMRES step than one and
+// cut the steps per solve by about a third: h = 1/100, rtol 1e-10, 71 steps with one
+// sweep, 48 with two, 39 with three.)
 
 template <class T>
 struct AuxOps {
@@ -86,7 +87,7 @@ struct AuxOps {
 struct FgScal {
     double *vs;      // [mr+1] inverse norms
     double *part;    // [kFgMax + 2][kMaxBlocks] partial sums
-    double *h1, *h2; // [mr+1] Gram-Schmidt coefficients of the two passes
+    double *h1;      // [mr+1] Gram-Schmidt coefficients
     double *H;       // [(mr+1) * mr] Hessenberg matrix, column-major
     double *cs, *sn; // [mr] Givens rotations
     double *g;       // [mr+1] rotated right-hand side
@@ -196,11 +197,11 @@ inline dim3 aux_grid(int64_t m, int nb) {
 
 constexpr int kNormRow = kFgMax + 1;  // row of FgScal::part that takes ||w||^2
 
-// Arnoldi step j, one workgroup: Hessenberg column j = h1 + h2 with
+// Arnoldi step j, one workgroup: Hessenberg column j = h1 with
 // H(j+1, j) = ||w||, previous rotations applied, a new rotation, the
 // residual estimate |g_{j+1}| and the status (4: the cycle's target met or
 // an exact breakdown; 3: the cycle is full; -1: non-finite).
-// ||w||^2 is reduced here from the block partials of k_fg_gs<2> (row kNormRow of
+// ||w||^2 is reduced here from the block partials of k_fg_gs (row kNormRow of
 // part, nb blocks).  One wave per quarter of the partials, every load in one
 // round trip; the column and the rotations are held one entry per lane of wave
 // 0, which runs the recurrence on values read by lane.
@@ -214,7 +215,7 @@ __device__ __forceinline__ void fg_tail(const FgScal &F, int j, int mr, int nb, 
         pv[q] = (b < nb) ? pn[b] : 0.0;
     }
     const bool first = t < 64;
-    const double hl = (first && lane <= j) ? F.h1[lane] + F.h2[lane] : 0.0;
+    const double hl = (first && lane <= j) ? F.h1[lane] : 0.0;
     const double cl = (first && lane < j) ? F.cs[lane] : 0.0;
     const double sl = (first && lane < j) ? F.sn[lane] : 0.0;
     const double gj = F.g[j], target = F.stat[0];
@@ -378,7 +379,7 @@ __global__ void k_aux_scale(AuxOps<T> P, const T *__restrict__ y, T *__restrict_
 }
 
 // Stage 2: restriction to the interior lattice points, X(q) = sum rval res
-// (about 18 entries per point with two node spacings per cell): 4 lanes per
+// (about five entries per point with one node spacing per cell): 4 lanes per
 // point take every 4th entry, then combine in a fixed order.
 template <class T>
 __global__ void __launch_bounds__(256) k_aux_restrict(AuxOps<T> P, Lat L,
@@ -409,7 +410,7 @@ __device__ __forceinline__ double aux_lattice(const Lat &L, int i, int j) {
     return lat_load(L, L.X, (int64_t)(ci - 1) + (int64_t)(cj - 1) * L.n);
 }
 
-// Stage 3: t1 = W y + J e (W y from yd), and block sums of J e.
+// Stage 3: t1 = su u + J e for the smoothed vector su u, and block sums of J e.
 template <class T>
 __global__ void __launch_bounds__(kThreads) k_aux_interp(AuxOps<T> P, Lat L,
                                                           const T *__restrict__ u,
@@ -810,22 +811,19 @@ k_fg_av2_few(AuxOps<T> P, const double *__restrict__ u1, double vscale, FgDev<T>
     fg_av2_rows<T, true>(P, u1, vscale, F, j);
 }
 
-// Gram-Schmidt update w -= sum_i h_i vs_i V_i (i <= j).  PASS 1 (the first
-// of two passes): then block partial dots (V_i vs_i, w) for the second;
-// PASS 2 (the last pass, the only one by default): then block partial
+// Gram-Schmidt update w -= sum_i h_i vs_i V_i (i <= j), then block partial
 // ||w||^2, and W w for the next preconditioner application.
 // Blocks of 2 kThreads threads on the kThreads-rows grid: lanes l and l + 32
 // of a wave share row l, each reading the basis vectors of one parity
-// (slot c: i = 2c + h), which serve both the update and, in PASS 1, the
-// dots with the updated w.
+// (slot c: i = 2c + h).
 constexpr int kSumBlocks = 64;         // SUM: largest grid
-template <class T, int PASS, bool SUM>
+template <class T, bool SUM>
 __global__ void __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_eu(4))) k_fg_gs(FgDev<T> F, const double *h,
                                                          const T *__restrict__ dinv, int64_t m,
                                                          int j) {
     constexpr int NW = 2 * kThreads / 64;
     __shared__ double c[kFgMax + 1];
-    __shared__ double lds[2 * kFgSlots * NW];
+    __shared__ double lds[NW];
     const int lane = threadIdx.x & 63, half = lane >> 5, wv = threadIdx.x >> 6;
     const int nb = gridDim.x;
     const int ns = (j + 2) >> 1;
@@ -843,7 +841,7 @@ __global__ void __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int q = 0; q < kFgSlots; ++q) vv[q] = (q < ns) ? (double)Vh[(int64_t)(2 * q) * m] : 0.0;
         wr = (double)w[rr];
-        di = (PASS == 2) ? dinv[rr] : (T)0;
+        di = dinv[rr];
     };
     // The first row iteration's loads, the coefficients and the flag in one
     // round trip.  SUM: the coefficients are summed here from the block partials
@@ -880,7 +878,6 @@ __global__ void __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_
         c[threadIdx.x] = hs * vsq;
     }
     __syncthreads();
-    if constexpr (PASS == 1) fg_slot_zero<NW>(ns, lds);
 #pragma unroll 1
     for (int64_t it = 0;; ++it) {
         if ((bx + it * nb) * kThreads >= m) break;
@@ -893,25 +890,13 @@ __global__ void __launch_bounds__(2 * kThreads) __attribute__((amdgpu_waves_per_
         const T wt = (T)(wr - s);
         if (half == 0 && r < m) {
             w[r] = wt;
-            if constexpr (PASS == 2) F.wd[r] = wt * di;
+            F.wd[r] = wt * di;
             nrm[0] += (double)wt * (double)wt;
         }
-        if constexpr (PASS == 1) {
-            const double wq = (r < m) ? (double)wt : 0.0;
-            double prod[kFgSlots];
-#pragma unroll
-            for (int q = 0; q < kFgSlots; ++q)
-                prod[q] = (q < ns && 2 * q + half <= j) ? vv[q] * wq : 0.0;
-            fg_slot_add<NW>(prod, ns, lds);
-        }
     }
-    if constexpr (PASS == 1) {
-        fg_slot_partials<NW>(j, ((int)threadIdx.x <= j) ? F.s.vs[threadIdx.x] : 0.0, F.s.part, lds);
-    } else {
-        // Row kNormRow: the partials of the dots (row 0 on) may still be read.
-        rbf::block_sum<1>(nrm, lds);
-        if (threadIdx.x == 0) F.s.part[(int64_t)kNormRow * kMaxBlocks + blockIdx.x] = nrm[0];
-    }
+    // Row kNormRow: the partials of the dots (row 0 on) may still be read.
+    rbf::block_sum<1>(nrm, lds);
+    if (threadIdx.x == 0) F.s.part[(int64_t)kNormRow * kMaxBlocks + blockIdx.x] = nrm[0];
 }
 
 // End of a cycle of nstep steps: back substitution H y = g and x += sum_i y_i Z_i

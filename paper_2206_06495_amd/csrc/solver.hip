@@ -3079,65 +3079,43 @@ rbf_status copy_in(rbf_solver *S, void *dst, const void *src, size_t bytes) {
 // (pressure_aux.h): smoother, residual, restriction, lattice transform
 // solve, interpolation, smoother.  tail: the Arnoldi step before, whose tail the
 // first kernel also takes (28-entry rows).
-constexpr bool kFuseTail = kAuxSweeps == 2;
 template <class T>
 void aux_apply(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, const T *y, const T *yd,
                const double *ys, T *z, bool sample = false, FgTail tail = FgTail{{}, -1, 0, 0, 0}) {
     hipStream_t st = S->st;
     const dim3 grid(nblocks_rows(P.m)), block(kThreads);
     const int nq = S->lat.n * S->lat.n;
-    // Pre-smoothing: x1 = W y (implicit, yd), further sweeps into F.x1.
-    const T *u = yd;
-    const double *us = ys;
-    static_assert(kAuxSweeps == 2 || !kFuseTail, "the tail travels with k_aux_pre");
-    static_assert(kAuxSweeps == 1 || kAuxSweeps == 2, "one or two smoothing sweeps");
-    if constexpr (kAuxSweeps == 2) {
-        launch_kt(P.k, [&](auto KT) {
-            dim3 g = aux_grid<decltype(KT)::value>(P.m, grid.x);
-            if (tail.j >= 0) ++g.x;
-            hipLaunchKernelGGL((k_aux_pre<decltype(KT)::value, T>), g, block, 0, st, P, y, yd, F.x1,
-                               F.s.flag, tail);
-        });
-        u = F.x1;
-    }
+    // Pre-smoothing: x1 = W y (implicit, yd), the second sweep into F.x1.
+    launch_kt(P.k, [&](auto KT) {
+        dim3 g = aux_grid<decltype(KT)::value>(P.m, grid.x);
+        if (tail.j >= 0) ++g.x;
+        hipLaunchKernelGGL((k_aux_pre<decltype(KT)::value, T>), g, block, 0, st, P, y, yd, F.x1,
+                           F.s.flag, tail);
+    });
     launch_kt(P.k, [&](auto KT) {
         hipLaunchKernelGGL((k_aux_res<decltype(KT)::value, T>),
-                           aux_grid<decltype(KT)::value>(P.m, grid.x), block, 0, st, P, y, ys, u,
-                           us, F.res, F.s.flag);
+                           aux_grid<decltype(KT)::value>(P.m, grid.x), block, 0, st, P, y, ys, F.x1,
+                           ys, F.res, F.s.flag);
     });
     hipLaunchKernelGGL(k_aux_restrict<T>, dim3(rbf::blocks_for(4 * (int64_t)nq, 256)), dim3(256), 0,
                        st, P, S->lat, F.res, nq);
     pc_apply(S, S->lat, sample);
-    hipLaunchKernelGGL(k_aux_interp<T>, grid, block, 0, st, P, S->lat, u, us, F.t1, F.s.partZ);
+    hipLaunchKernelGGL(k_aux_interp<T>, grid, block, 0, st, P, S->lat, F.x1, ys, F.t1, F.s.partZ);
     // Post-smoothing: the first sweep adds the border's constant.
-    T *zin = F.t1;
-    if constexpr (kAuxSweeps == 2) {
-        if (P.k == 28)
-            hipLaunchKernelGGL((k_aux_post2<T, true>), grid, dim3(2 * kThreads), 0, st, P, S->lat, y,
-                               ys, F.t1, F.s.partZ, F.z1, F.s.partO);
-        else
-            hipLaunchKernelGGL((k_aux_post<0, T, true>), grid, block, 0, st, P, S->lat, y, ys, F.t1,
-                               F.s.partZ, F.z1, F.s.partO);
-        zin = F.z1;
-    }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (sample) prof_pair(S, RBF_PROF_SMOOTH, e0, e1);
-    if (P.k == 28)
-        hipExtLaunchKernelGGL((k_aux_post2<T, kAuxSweeps == 1>), grid, dim3(2 * kThreads), 0, st, e0,
-                              e1, 0, P, S->lat, y, ys, zin, F.s.partZ, z, F.s.partO);
-    else
-        hipExtLaunchKernelGGL((k_aux_post<0, T, kAuxSweeps == 1>), grid, block, 0, st, e0, e1, 0, P,
-                              S->lat, y, ys, zin, F.s.partZ, z, F.s.partO);
+    if (P.k == 28) {
+        hipLaunchKernelGGL((k_aux_post2<T, true>), grid, dim3(2 * kThreads), 0, st, P, S->lat, y, ys,
+                           F.t1, F.s.partZ, F.z1, F.s.partO);
+        hipExtLaunchKernelGGL((k_aux_post2<T, false>), grid, dim3(2 * kThreads), 0, st, e0, e1, 0, P,
+                              S->lat, y, ys, F.z1, F.s.partZ, z, F.s.partO);
+    } else {
+        hipLaunchKernelGGL((k_aux_post<0, T, true>), grid, block, 0, st, P, S->lat, y, ys, F.t1,
+                           F.s.partZ, F.z1, F.s.partO);
+        hipExtLaunchKernelGGL((k_aux_post<0, T, false>), grid, block, 0, st, e0, e1, 0, P, S->lat, y,
+                              ys, F.z1, F.s.partZ, z, F.s.partO);
+    }
 }
-
-// Orthogonalisation of the Arnoldi vectors: classical Gram-Schmidt once
-// (h2 stays zero), or applied twice when true.  One pass takes the same
-// number of steps to the same true residual on the h = 1/400 cavity and the
-// cylinder (32.3 and 35.2 per time step) and saves a reduction and a pass
-// over the basis per step; convergence is only declared from the true
-// residual recomputed at a restart, so a loss of orthogonality can cost
-// steps but not accuracy.
-constexpr bool kFgReorth = false;
 
 // Flexible GMRES(kFgMax) on the pressure system with the two-level
 // preconditioner (x: guess in, solution out).  Every cycle starts from the
@@ -3259,24 +3237,17 @@ rbf_status fgmres_run(rbf_solver *S, const AuxOps<T> &P, FgDev<T> &F, EllM A, co
             else
                 hipExtLaunchKernelGGL((k_fg_av<0, T>), grid, block, 0, st, e0, e1, 0, P, A.u1,
                                       A.vscale, F, j);
-            const bool sum = !kFgReorth && nb <= kSumBlocks;
+            const bool sum = nb <= kSumBlocks;
             if (!sum)
                 hipLaunchKernelGGL(k_fg_reduce, dim3(j + 1), red, 0, st, Fs.part, nb,
                                    Fs.h1, Fs.flag);
             const dim3 b2(2 * kThreads);
-            if constexpr (kFgReorth) {
-                hipExtLaunchKernelGGL((k_fg_gs<T, 1, false>), grid, b2, 0, st, g0, g1, 0, F,
-                                      Fs.h1, P.dinv, m, j);
-                hipLaunchKernelGGL(k_fg_reduce, dim3(j + 1), red, 0, st, Fs.part, nb,
-                                   Fs.h2, Fs.flag);
-                hipLaunchKernelGGL((k_fg_gs<T, 2, false>), grid, b2, 0, st, F, Fs.h2, P.dinv, m, j);
-            } else if (sum) {
-                hipExtLaunchKernelGGL((k_fg_gs<T, 2, true>), grid, b2, 0, st, g0, g1, 0, F, Fs.h1,
+            if (sum)
+                hipExtLaunchKernelGGL((k_fg_gs<T, true>), grid, b2, 0, st, g0, g1, 0, F, Fs.h1,
                                       P.dinv, m, j);
-            } else {
-                hipExtLaunchKernelGGL((k_fg_gs<T, 2, false>), grid, b2, 0, st, g0, g1, 0, F, Fs.h1,
+            else
+                hipExtLaunchKernelGGL((k_fg_gs<T, false>), grid, b2, 0, st, g0, g1, 0, F, Fs.h1,
                                       P.dinv, m, j);
-            }
             if (fuse) tail = j;
             else hipLaunchKernelGGL(k_fg_tail, one, red, 0, st, Fs, j, mr, nb, seq);
             S->prof_tag_now = -1;
@@ -3319,7 +3290,7 @@ rbf_status aux_solve(rbf_solver *S, EllM A, const double *b, double *x, rbf_solv
     A.vscale *= kAuxBorder;  // as S->lat.c
     auto run = [&](auto &P, auto &F) {
         S->lat.flag = F.s.flag;  // the transform stages exit with the Krylov flag
-        return fgmres_run<kFuseTail>(S, P, F, A, nullptr, b, x, S->rtol_p, S->maxit_p, 1.0,
+        return fgmres_run<true>(S, P, F, A, nullptr, b, x, S->rtol_p, S->maxit_p, 1.0,
                           S->last_iters_p, stats,
                           [&](const auto *y, const auto *yd, const double *ys, auto *z, bool sample,
                               const FgTail &tail) {
@@ -3343,8 +3314,6 @@ rbf_status alloc_fg(rbf_solver *S, FgDev<T> &F, int64_t M) {
     ALLOC(s.vs, mr + 1);
     ALLOC(s.part, (int64_t)(kFgMax + 2) * kMaxBlocks);
     ALLOC(s.h1, mr + 1);
-    ALLOC(s.h2, mr + 1);
-    RBF_HIP(hipMemsetAsync(s.h2, 0, (mr + 1) * sizeof(double), S->st));
     ALLOC(s.H, (int64_t)(mr + 1) * mr);
     ALLOC(s.cs, mr);
     ALLOC(s.sn, mr);
