@@ -451,7 +451,8 @@ rbf_status rbf_solver_create(rbf_solver **out, const rbf_grid *grid, const rbf_o
  * Transactional: each step is computed in solver workspace and committed
  * only if every solve converged and stayed finite; on error `state` holds the
  * last committed step and stats (host, nullable) says where it stopped.
- * Reads back a convergence flag every few Krylov iterations (synchronises).
+ * The host follows the solves by words that their kernels store in pinned
+ * memory; the stream is synchronised at the end of the call.
  * Errors: RBF_E_ARG, RBF_E_NOCONV, RBF_E_NAN, RBF_E_DEVICE.
  */
 rbf_status rbf_step(rbf_solver *s, int32_t nsteps, rbf_state *state, rbf_step_stats *stats);
@@ -612,17 +613,47 @@ rbf_status rbf_solver_forces(rbf_solver *s, const rbf_grid *grid, const rbf_stat
  * dnu: host, accumulated: the derivative with respect to nu (through
  * H = I - (dt nu / 2) D_Lap and the right-hand side of eq. (16)).
  * The transposed solves: the viscous matrix by Jacobi-scaled BiCGSTAB on
- * H^T (both components at once), the bordered pressure system (A_s + u1 c
- * 1^T)^T (the transpose of the zero-mean bordered solve) by flexible GMRES
- * with the transpose of the auxiliary-lattice preconditioner, or by BiCGSTAB
- * on node sets that it does not fit and if it fails, with the solver's
- * tolerances (pressure: a tenth of rtol_p or better).  The first call builds
- * the transposed operators (rbf_ell_transpose).  Synchronises.
+ * H^T (both components at once) to rtol_h, the bordered pressure system (A_s
+ * + u1 c 1^T)^T (the transpose of the zero-mean bordered solve) by flexible
+ * GMRES with the transpose of the auxiliary-lattice preconditioner, which
+ * aims at 0.01 rtol_p, or by BiCGSTAB, which aims at 0.1 rtol_p, on node sets
+ * that the preconditioner does not fit and if the former fails; where a solve
+ * stagnates, a true residual of up to rtol_p is accepted.  rbf_adjoint_query
+ * says which solvers ran.  The first call builds the transposed operators
+ * (rbf_ell_transpose).  Synchronises.
  * Errors: RBF_E_ARG (NULL arguments), RBF_E_NOCONV, RBF_E_NAN, those of
  * rbf_step for the recomputed forward step.
  */
 rbf_status rbf_adjoint_step(rbf_solver *s, const rbf_state *fwd, rbf_state *adj, double *grad_bc,
                             double *dnu);
+
+/*
+ * rbf_adjoint_query -- how the transposed solves of the last rbf_adjoint_step
+ * ran (host struct, filled; zeros before the first):
+ *   pressure_steps  Arnoldi steps of preconditioned FGMRES; 0 where BiCGSTAB
+ *                   solved the pressure system;
+ *   viscous_iters   iterations of the two-component BiCGSTAB; 0 where the
+ *                   components were solved one after the other;
+ *   fallbacks       solves since the solver's creation that the first method
+ *                   failed and the second took over.
+ * Errors: RBF_E_ARG (NULL).
+ */
+typedef struct {
+    int32_t pressure_steps, viscous_iters;
+    int64_t fallbacks;
+} rbf_adjoint_info;
+rbf_status rbf_adjoint_query(rbf_solver *s, rbf_adjoint_info *info);
+
+/*
+ * rbf_adjoint_apply_precond -- z = P^-T y, the transpose of the
+ * auxiliary-lattice preconditioner that the adjoint's pressure solve uses
+ * (for a solver whose forward solve runs on it in FP64 the transpose of
+ * rbf_solver_apply_precond).  For tests and diagnostics.  y, z: device [n_p],
+ * distinct.  The first call builds the transposed operators.  Synchronises the
+ * solver's stream.  Errors: RBF_E_ARG (NULL, outflow or symmetry rows, or a node
+ * set that the preconditioner does not fit).
+ */
+rbf_status rbf_adjoint_apply_precond(rbf_solver *s, const double *y, double *z);
 
 /* Release a solver (NULL is ignored). */
 void rbf_solver_destroy(rbf_solver *s);

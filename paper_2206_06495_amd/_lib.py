@@ -28,6 +28,7 @@ EXPORTED = [
     "rbf_ell_transpose_weights", "rbf_ell_apply_transpose", "rbf_solver_create",
     "rbf_step", "rbf_step_batch", "rbf_solve_pressure", "rbf_solver_apply_precond", "rbf_solver_profile", "rbf_solver_query",
     "rbf_solver_diagnostics", "rbf_solver_forces", "rbf_adjoint_step",
+    "rbf_adjoint_query", "rbf_adjoint_apply_precond",
     "rbf_solver_destroy",
 ]
 
@@ -81,6 +82,11 @@ class SolverInfo(ctypes.Structure):
                 ("jacobi_bound", ctypes.c_double), ("aux_precond", ctypes.c_int32),
                 ("aux_cells", ctypes.c_int32), ("viscous_mixed", ctypes.c_int32),
                 ("aux_smooth_weight", ctypes.c_double)]
+
+
+class AdjointInfo(ctypes.Structure):
+    _fields_ = [("pressure_steps", ctypes.c_int32), ("viscous_iters", ctypes.c_int32),
+                ("fallbacks", ctypes.c_int64)]
 
 
 class StepStats(ctypes.Structure):
@@ -160,6 +166,10 @@ def _load():
     lib.rbf_solver_forces.argtypes = [c_void_p, ctypes.POINTER(Grid), ctypes.POINTER(State),
                                       ctypes.c_int32, ctypes.c_double, ctypes.c_double,
                                       ctypes.c_double, ctypes.POINTER(ctypes.c_double)]
+    lib.rbf_adjoint_query.restype = S
+    lib.rbf_adjoint_query.argtypes = [c_void_p, ctypes.POINTER(AdjointInfo)]
+    lib.rbf_adjoint_apply_precond.restype = S
+    lib.rbf_adjoint_apply_precond.argtypes = [c_void_p, c_void_p, c_void_p]
     lib.rbf_adjoint_step.restype = S
     lib.rbf_adjoint_step.argtypes = [c_void_p, ctypes.POINTER(State), ctypes.POINTER(State),
                                      c_void_p, c_double_p]

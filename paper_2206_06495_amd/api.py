@@ -347,6 +347,21 @@ class Solver:
                                    ctypes.byref(dnu)))
         return dnu.value
 
+    def adjoint_info(self):
+        """How the last adjoint_step's transposed solves ran (rbf_adjoint_query):
+        {"pressure_steps", "viscous_iters", "fallbacks"}."""
+        inf = _lib.AdjointInfo()
+        check(lib.rbf_adjoint_query(self._h, ctypes.byref(inf)))
+        return {f: getattr(inf, f) for f, _ in inf._fields_}
+
+    def apply_precond_t(self, y):
+        """z = P^-T y, the adjoint pressure solve's preconditioner
+        (rbf_adjoint_apply_precond)."""
+        _dev(y, torch.float64, (self.M,), "y")
+        z = torch.empty_like(y)
+        check(lib.rbf_adjoint_apply_precond(self._h, _ptr(y), _ptr(z)))
+        return z
+
     def diagnostics(self, state):
         """Health figures of a state: {"div_max", "div_rms", "kinetic_energy",
         "speed_max", "cfl"} (rbf_solver_diagnostics)."""

@@ -2180,7 +2180,8 @@ struct rbf_solver {
         Lat lat{};
         FgDev<double> fg{};
         double *ones = nullptr;
-        int last_p = 0, last_h = 0;
+        int last_p = 0, last_h = 0;  // steps and iterations of the newest solves
+        rbf_adjoint_info info{};
         int *ht_idx = nullptr;
         double *ht_w = nullptr, *hb = nullptr, *hx = nullptr;
         int ht_k = 0;
@@ -4517,8 +4518,10 @@ extern "C" rbf_status rbf_adjoint_step(rbf_solver *S, const rbf_state *fwd, rbf_
                         });
         solved = rc == RBF_OK;
         if (rc == RBF_E_DEVICE || rc == RBF_E_NOMEM) return rc;
+        if (!solved) ++A.info.fallbacks;
         rbf::clear_error();
     }
+    A.info.pressure_steps = solved ? A.last_p : 0;
     if (!solved)
         ADJ(adj_bicgstab(S, M, pois_t, nullptr, y, w, tol_p, std::max(S->maxit_p, 20000),
                          "rbf_adjoint_step (transposed pressure solve)"));
@@ -4548,10 +4551,12 @@ extern "C" rbf_status rbf_adjoint_step(rbf_solver *S, const rbf_state *fwd, rbf_
         rc = hbicgstab(S, HT, hb, A.hx, S->rtol_h, S->maxit_h, A.last_h, nullptr);
         solved = rc == RBF_OK;
         if (rc == RBF_E_DEVICE || rc == RBF_E_NOMEM) return rc;
+        if (!solved) ++A.info.fallbacks;
         rbf::clear_error();
         rub = A.hx;
         rvb = A.hx + N;
     }
+    A.info.viscous_iters = solved ? A.last_h : 0;
     if (!solved) {
         rub = V[2];
         rvb = V[3];
@@ -4695,6 +4700,31 @@ extern "C" rbf_status rbf_solve_pressure(rbf_solver *S, const double *rhs, doubl
         RBF_HIP(hipStreamSynchronize(S->st));
     }
     return rc;
+}
+
+extern "C" rbf_status rbf_adjoint_query(rbf_solver *S, rbf_adjoint_info *info) {
+    rbf::clear_error();
+    RBF_ARG(S && info, "rbf_adjoint_query: NULL argument");
+    *info = S->adj.info;
+    return RBF_OK;
+}
+
+extern "C" rbf_status rbf_adjoint_apply_precond(rbf_solver *S, const double *y, double *z) {
+    rbf::clear_error();
+    RBF_ARG(S && y && z, "rbf_adjoint_apply_precond: NULL argument");
+    RBF_ARG(!S->v_tag_open, "rbf_adjoint_apply_precond: needs Dirichlet boundary rows only (no outflow or symmetry rows)");
+    rbf_status rc;
+    auto &A = S->adj;
+    if (!A.ready && (rc = adj_setup(S)) != RBF_OK) return rc;
+    RBF_ARG(A.pre_on, "rbf_adjoint_apply_precond: the solver has no transposed preconditioner");
+    FgDev<double> &F = A.fg;
+    RBF_HIP(hipMemsetAsync(F.s.flag, 0, sizeof(int), S->st));
+    A.lat.flag = F.s.flag;
+    hipLaunchKernelGGL(k_aux_scale<double>, dim3(1024), dim3(256), 0, S->st, A.pre.P, y, F.wd);
+    adj_pre_apply(S, y, F.wd, F.s.one, z);
+    RBF_CHECK_LAUNCH();
+    RBF_HIP(hipStreamSynchronize(S->st));
+    return RBF_OK;
 }
 
 extern "C" rbf_status rbf_solver_apply_precond(rbf_solver *S, const double *y, double *z) {
