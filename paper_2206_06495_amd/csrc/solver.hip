@@ -16,6 +16,7 @@
 #include <atomic>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <string>
 #include <system_error>
 #include <thread>
@@ -4176,7 +4177,11 @@ rbf_status adj_pre_setup(rbf_solver *S) {
         g.n_p = M;
         g.xp = S->xp;
         g.p_tag = S->p_tag;
-        rc = setup_aux_pc(S, &g, RBF_PRECOND_AUTO);
+        try {
+            rc = setup_aux_pc(S, &g, RBF_PRECOND_AUTO);
+        } catch (const std::bad_alloc &) {  // (S gets its own structures back below)
+            rc = RBF_E_NOMEM;
+        }
         const bool on = rc == RBF_OK && S->aux_on;
         A.lat = S->lat;
         A.fg = S->fg64;
@@ -4287,6 +4292,19 @@ void adj_pre_apply(rbf_solver *S, const double *y, const double *yd, const doubl
     hipLaunchKernelGGL(k_at_row<4>, grid, block, 0, st, D, y, yd, ys, z, A.fg.s.partO, flag);
 }
 
+// H^T (identity on wall rows) as padded rows for the viscous BiCGSTAB of both components.
+rbf_status adj_pair_setup(rbf_solver *S) {
+    auto &A = S->adj;
+    const int64_t N = S->N;
+    rbf_status rc;
+    double *hT = nullptr;
+    ALLOC(hT, (int64_t)S->k * N);
+    ALLOC(A.hx, 2 * N);
+    if ((rc = rbf_ell_transpose_weights(N, S->k, A.src_vv, A.slot_vv, S->h_w, hT, 0, S->st)) != RBF_OK)
+        return rc;
+    return adj_pad(S, N, A.cp_vv, A.src_vv, hT, &A.ht_idx, &A.ht_w, A.ht_k);
+}
+
 rbf_status adj_setup(rbf_solver *S) {
     auto &A = S->adj;
     const int64_t N = S->N, M = S->M;
@@ -4313,15 +4331,17 @@ rbf_status adj_setup(rbf_solver *S) {
     for (auto &q : A.pm) ALLOC(q, M);
     for (auto &q : A.kr) ALLOC(q, std::max(N, M));
     ALLOC(A.part, 4 * kMaxBlocks);
-    // H^T (identity on wall rows) for the viscous BiCGSTAB of both components.
-    double *hT = nullptr;
-    ALLOC(hT, (int64_t)S->k * N);
-    if ((rc = rbf_ell_transpose_weights(N, S->k, A.src_vv, A.slot_vv, S->h_w, hT, 0, S->st)) != RBF_OK)
-        return rc;
-    if ((rc = adj_pad(S, N, A.cp_vv, A.src_vv, hT, &A.ht_idx, &A.ht_w, A.ht_k)) != RBF_OK) return rc;
     ALLOC(A.hb, 2 * N);
-    ALLOC(A.hx, 2 * N);
-    if ((rc = adj_pre_setup(S)) != RBF_OK) return rc;
+    // The faster solvers' structures: where their memory cannot be had the others run.
+    try {
+        if ((rc = adj_pair_setup(S)) == RBF_OK) rc = adj_pre_setup(S);
+    } catch (const std::bad_alloc &) {
+        rc = RBF_E_NOMEM;
+    }
+    if (rc != RBF_OK) {
+        (void)hipGetLastError();
+        rbf::clear_error();
+    }
     RBF_HIP(hipStreamSynchronize(S->st));
     A.ready = true;
     return RBF_OK;
