@@ -67,7 +67,7 @@ FP64_VALU_PEAK_TFLOPS = 78.6
 # counters on a plain 256 MiB copy (2.0 and 1.0), mean over the working
 # launches of 3 steps from rest (mean Arnoldi index 12.1 for k_fg_av2 and
 # k_fg_gs<2>); None for a kernel changed since it was measured.
-TRAFFIC_BYTES = {"k_fg_av2": 87.57e6, "k_aux_post2": 68.98e6, "k_fg_gs<2>": 26.17e6,
+TRAFFIC_BYTES = {"k_fg_av2": 87.52e6, "k_aux_post2": 68.88e6, "k_fg_gs<2>": 26.17e6,
                  "k_pc_fold": 17.39e6}
 
 

@@ -126,8 +126,8 @@ rbf_status rbf_knn(const double *xq, int64_t nq, const double *xs, int64_t ns, i
 
 /*
  * rbf_knn_noalloc -- rbf_knn for callers that cannot allocate device memory
- * (code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc).  Same arguments, result and errors as rbf_knn; the cell grid
+ * (tight serving loops, harnesses that forbid hipMalloc; not under HIP graph
+ * capture, as it waits for the stream).  Same arguments, result and errors as rbf_knn; the cell grid
  * lives in a fixed per-device scratch array of 64 MiB (held by each device
  * the library runs on until the process ends), so no allocation or
  * deallocation happens in the call.  Capacity: about 30 bytes per source

@@ -3479,8 +3479,8 @@ rbf_status setup_aux_pc(rbf_solver *S, const rbf_grid *g, int mode) {
     // (1 - nu)(1 - w2 nu) stays within 1 in magnitude for w2 <= 1 / (nu - 1);
     // w2 is 0.85 of that bound, between 1 and 1.6, with nu raised by 5 %
     // (80 power steps approach it from below, within 5 % when the top
-    // eigenvalues cluster).  The h = 1/400 cavity (nu = 1.47) gets about
-    // 1.55: 32 instead of 35 FGMRES steps per time step; the graded
+    // eigenvalues cluster).  The h = 1/400 cavity (nu = 1.51) gets 1.44:
+    // 32 instead of 35 FGMRES steps per time step; the graded
     // cylinder sets (nu = 1.74-1.88) stay near 1, where a fixed 1.5 made
     // their solves fail.
     {

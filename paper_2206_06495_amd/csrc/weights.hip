@@ -999,7 +999,7 @@ extern "C" rbf_status rbf_assemble_weights(const double *xq, int64_t nq, const d
         else RBF_WCOND(SM, FX, NP, false, false);                                                 \
     } while (0)
     // The paper's stencil: four systems per wavefront for r^7, whose A is
-    // definite on the null space of the constraints (5.3 ms per 10^6 systems
+    // definite on the null space of the constraints (5.1 ms per 10^6 systems
     // with three operators, 18.3 ms with two per wavefront and pivoting); two
     // per wavefront for other exponents.  The condition estimate needs the LU
     // factors of the one-system kernel, which then solves only the rows that

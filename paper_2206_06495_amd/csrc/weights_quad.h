@@ -38,9 +38,11 @@
 // V-nodes at h = 1/400).  A two-part split with 24 bits each left up to 1.9 times
 // that error.
 //
-// Measured (10^6 V-nodes, D_x, D_y, Lap): 5.2 ms against 18.3 ms of
-// k_weights_pair; bound by FP64 instruction issue, about 6,600 instructions per
-// wavefront of four systems (4,068 per system before).
+// Measured (10^6 V-nodes, D_x, D_y, Lap): 5.1 ms against 18.3 ms of
+// k_weights_pair.  Bound by the FP64 instructions at two waves a SIMD (256
+// VGPRs): 7,212 vector instructions per wavefront of four systems (4,068 per
+// system before), which keep the vector unit busy 62 % of the time; the rest is
+// the latency of the factorisation's chain.
 //
 // A system that is not clearly definite on these pivots (coincident nodes,
 // nodes on a cubic curve, non-finite coordinates, an index out of range) is
@@ -208,10 +210,12 @@ __device__ __forceinline__ unsigned row_max(unsigned k) {
     return max(k, (unsigned)__builtin_amdgcn_update_dpp(0, (int)k, kDppSwap1, 0xF, 0xF, false));
 }
 
-// Correctly rounded sqrt of a normal d (NaN for 0): reciprocal square root,
-// one Goldschmidt step and two Newton corrections by the exact residual.  The
-// library function's scaling of denormals is left out: a pair of nodes that
-// close makes the system singular, and it goes to k_weights_pair.
+// Square root of a normal d (NaN for 0), as by P. Markstein, "Software division
+// and square root using Goldschmidt's algorithms" (2004): from the reciprocal
+// square root one Goldschmidt step on g -> sqrt(d) and h -> 1 / (2 sqrt(d)), then
+// two corrections by the fused residual d - g^2.  No scaling for subnormal d: a
+// pair of nodes that close makes the system singular, and it goes to
+// k_weights_pair.
 __device__ __forceinline__ double sqrt_normal(double d) {
     const double y = __builtin_amdgcn_rsq(d);
     double g = d * y, h = 0.5 * y;
